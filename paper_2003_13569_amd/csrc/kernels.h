@@ -370,8 +370,6 @@ struct StageArgs {
   const double* lam[3];
   T kt[MAX_SPECIES];  // kappa_s tau
   T ha[MAX_SPECIES];  // alpha_s / 2
-  int lfly;
-  int lam_off;        // byte offset of the eigenvalue tables in dynamic LDS
   double* thp;        // adjoint Z kernels on L formed in the kernel: per-block kappa and
                       // alpha gradient partials [2 S][gridDim.x], accumulated (else G)
   int S;
@@ -556,16 +554,21 @@ __device__ __forceinline__ void stage_coefs_L(int mode, T L, T tau, T& c0, T& c1
     c2 = tau * (T(4) + L * (T(3) + L)) * iD;
     return;
   }
+  // both forms computed, then selected (no branch per point)
   const bool small = L < T(1);
   const T iDh = recip<T>(T(192) + L * (T(72) + L * (T(12) + L)));
   const T ph = T(96) + L * (T(12) + L);
   c1 = tau * ph * iDh;
-  if (mode <= 1) c0 = small ? L * ph * iDh : T(1) - T(24) * (T(8) - L) * iDh;
+  if (mode <= 1) {
+    const T lo = L * ph * iDh, hi = T(1) - T(24) * (T(8) - L) * iDh;
+    c0 = small ? lo : hi;
+  }
   if (mode != 0) {
     c2 = T(2) * tau * (T(4) + L) * iD;
     return;
   }
-  c2 = small ? L * (T(24) + L * (T(6) + L)) * iD : T(1) - (T(24) - T(6) * L) * iD;
+  const T lo = L * (T(24) + L * (T(6) + L)) * iD, hi = T(1) - (T(24) - T(6) * L) * iD;
+  c2 = small ? lo : hi;
   c3 = tau * (T(4) - L) * iD;
 }
 
@@ -855,8 +858,10 @@ __device__ __forceinline__ void p13_table_derivs(double L, double tau, double* c
   const double iD = 1.0 / D, iDh = 1.0 / Dh;
   const double R = (24.0 - 6.0 * L) * iD, Q = (192.0 - 24.0 * L) * iDh;
   const bool small = L < 1.0;
-  c[C_R] = small ? L * (24.0 + L * (6.0 + L)) * iD : 1.0 - R;
-  c[C_Q] = small ? L * (96.0 + L * (12.0 + L)) * iDh : 1.0 - Q;
+  const double rl = L * (24.0 + L * (6.0 + L)) * iD, rh = 1.0 - R;
+  const double ql = L * (96.0 + L * (12.0 + L)) * iDh, qh = 1.0 - Q;
+  c[C_R] = small ? rl : rh;
+  c[C_Q] = small ? ql : qh;
   c[C_PHI] = tau * (96.0 + L * (12.0 + L)) * iDh;
   c[C_PHI1] = tau * (4.0 - L) * iD;
   c[C_PHI2] = tau * (8.0 + 2.0 * L) * iD;
@@ -1229,7 +1234,7 @@ __global__ void k_coefs(CoefArgs c, T* out) {
 // part[q][block], q = 2s (kappa_s) and 2s+1 (alpha_s), of
 // sum_k omega_k G_k dL_k/dtheta with dL/dkappa = tau Lambda^(alpha/2),
 // dL/dalpha = L ln(Lambda)/2 and omega_k = cs * (Neumann spectral weights).
-__global__ void k_greduce(CoefArgs c, const double* G, double cs, int neumann, double* part) {
+static __global__ void k_greduce(CoefArgs c, const double* G, double cs, int neumann, double* part) {
   __shared__ double red[NTHREADS];
   double acc[2 * MAX_SPECIES];
   for (int q = 0; q < 2 * MAX_SPECIES; ++q) acc[q] = 0.0;
@@ -1250,7 +1255,7 @@ __global__ void k_greduce(CoefArgs c, const double* G, double cs, int neumann, d
 }
 
 // out[r] = sum over in[r][0..len) in a fixed order (one block per row).
-__global__ void k_rowsum(const double* in, long long len, double* out) {
+static __global__ void k_rowsum(const double* in, long long len, double* out) {
   __shared__ double red[NTHREADS];
   const double* row = in + blockIdx.x * len;
   double a = 0.0;
@@ -1277,7 +1282,7 @@ constexpr int CKPT_WORDS = 12;
 struct CkptHeader {
   long long w[CKPT_WORDS];
 };
-__global__ void k_header(long long* h, CkptHeader v) {
+static __global__ void k_header(long long* h, CkptHeader v) {
   const int i = threadIdx.x;
   if (blockIdx.x == 0 && i < CKPT_WORDS) h[i] = v.w[i];
 }

@@ -29,8 +29,8 @@
 #include "coef.h"
 #include "fft.h"
 #include "kernels.h"
-#include "mfma.h"
 #include "stability.h"
+#include "wave_parts.h"
 
 using namespace sfrde;
 
@@ -124,19 +124,18 @@ struct sfrde_plan_s {
   size_t w = 4;   // bytes per real
   Geom geom[3]{};
   size_t lds[3] = {0, 0, 0};
-  // matrix-core variant per axis (see mfma.h)
-  bool use_m[3] = {false, false, false};
+  // wave engine per axis (wave.h): size class (-1: not on it), tables, tiles
+  int wcls[3] = {-1, -1, -1};
+  WaveAxis wax[3]{};
+  WaveTiles wtl[3]{};
+  void* wA[3] = {nullptr, nullptr, nullptr};
+  bool lfly = false;     // Z kernels of the wave engine form L from the eigenvalues
   // long periodic axes of 256, 512 or 1024 points: FFT tile kernels (fft.h)
   bool use_f[3] = {false, false, false};
   Geom geom_f[3]{};
   size_t lds_f[3] = {0, 0, 0};
   unsigned thr_f[3] = {0, 0, 0};
   void* tw[3] = {nullptr, nullptr, nullptr};  // [N][2] cos, sin of 2 pi m / N
-  Geom geom_m[3]{};
-  size_t lds_m[3] = {0, 0, 0};
-  unsigned grid_m[3] = {0, 0, 0};
-  MfmaAxisDev mfax[3]{};
-  void* mf_A[3] = {nullptr, nullptr, nullptr};
   int n_cu = 256;
   int device = 0;
   // the static scratch array of the plan's device (allocation-free backward)
@@ -148,10 +147,8 @@ struct sfrde_plan_s {
   void* coef = nullptr;
   void* dcoef = nullptr;
   void* ltab = nullptr;  // P13 plans: L per species and point
-  bool lfly = false;     // FP32 P13 Z kernels form L from the eigenvalues
-  double* thp = nullptr;  // adjoint kappa/alpha partials per Z block [4][grid]
+  double* thp = nullptr;  // adjoint kappa/alpha partials per Z block [4][blocks]
   bool thp_on = false;    // this backward call accumulates them (else G)
-  size_t lam_off = 0;    // LDS byte offset of the eigenvalue tables (last axis kernels)
   void* P = nullptr;
   void* uhat = nullptr;
   void* ctil = nullptr;
@@ -336,89 +333,20 @@ void make_geom(sfrde_plan_s* p, int axis, long long min_tiles = 0) {
   p->lds[axis] = std::max<size_t>(tile, NTHREADS * sizeof(double));
 }
 
-// ------------------------------------------------------------------ matrix cores
-// Folded form of one axis matrix (mfma.h): the half matrices E and O over the
-// fold pairs (the same pairs fold_pair() computes on the device), from which
-// the fragment-ordered copies the waves load into registers are made.
-struct MfmaTables {
-  bool ok = false;
-  int hK = 0, RBe = 0, RB = 0, ns = 0, rowsE = 0, rowsO = 0;
-  std::vector<double> E, O;  // [rows][hK]
-};
-
-double axis_entry(int bc, long long n, long long k, long long j) {
-  const double pi = 3.14159265358979323846;
-  if (bc == SFRDE_BC_DIRICHLET) {
-    const long long N = n + 1;
-    return sin(pi * double(((k + 1) * (j + 1)) % (2 * N)) / double(N));
-  }
-  const long long N = n - 1;  // Neumann
-  double v = cos(pi * double((k * j) % (2 * N)) / double(N));
-  if (j == 0 || j == n - 1) v *= 0.5;
-  return v;
-}
-
-MfmaTables mfma_tables(int bc, long long n) {
-  const double pi = 3.14159265358979323846;
-  MfmaTables t;
-  std::vector<std::pair<long long, long long>> pairs;  // (a, b), b = -1: fixed point
-  if (bc == SFRDE_BC_PERIODIC) {
-    const long long N = n;
-    pairs.push_back({0, -1});
-    for (long long j = 1; j < (N + 1) / 2; ++j) pairs.push_back({j, N - j});
-    if (N % 2 == 0) pairs.push_back({N / 2, -1});
-    t.rowsE = (int)(N / 2 + 1);
-    t.rowsO = t.rowsE;
-  } else {
-    for (long long j = 0; j < n / 2; ++j) pairs.push_back({j, n - 1 - j});
-    if (n % 2 == 1) pairs.push_back({(n - 1) / 2, -1});
-    t.rowsE = (int)((n + 1) / 2);
-    t.rowsO = (int)(n / 2);
-  }
-  t.ns = (int)pairs.size();
-  t.hK = ((t.ns + 31) / 32) * 32;
-  t.RBe = (t.rowsE + 15) / 16;
-  t.RB = t.RBe + (t.rowsO + 15) / 16;
-  t.ok = t.hK <= 128 && t.RB <= MF_WAVES;
-  if (!t.ok) return t;
-  t.E.assign((size_t)t.rowsE * t.hK, 0.0);
-  t.O.assign((size_t)t.rowsO * t.hK, 0.0);
-  for (int i = 0; i < t.ns; ++i) {
-    const long long a = pairs[i].first;
-    const bool fixed = pairs[i].second < 0;
-    for (int m = 0; m < t.rowsE; ++m) {
-      double e, o;
-      if (bc == SFRDE_BC_PERIODIC) {
-        const double th = 2.0 * pi * double((m * a) % n) / double(n);
-        e = cos(th);
-        o = fixed ? 0.0 : sin(th);
-      } else {
-        e = axis_entry(bc, n, 2 * m, a);
-        o = (fixed || m >= t.rowsO) ? 0.0 : axis_entry(bc, n, 2 * m + 1, a);
-      }
-      t.E[(size_t)m * t.hK + i] = e;
-      if (m < t.rowsO) t.O[(size_t)m * t.hK + i] = o;
-    }
-  }
-  return t;
-}
-
+// ------------------------------------------------------------------ wave engine
 // binary16 bits of x rounded to nearest even (subnormals included; |x| is
 // far below the binary16 maximum here).
 unsigned short host_f16(double x) {
-  const unsigned short sign = std::signbit(x) ? 0x8000 : 0;
+  uint64_t b;
+  std::memcpy(&b, &x, sizeof(b));
+  const unsigned short sign = (unsigned short)((b >> 48) & 0x8000u);
+  b &= ~(1ull << 63);
   const double a = std::fabs(x);
-  if (a <= std::ldexp(1.0, -25)) return sign;  // 2^-25 is the tie with 0
-  int e;
-  std::frexp(a, &e);  // a in [2^(e-1), 2^e)
-  int E = std::max(e - 1, -14);
-  double m = std::nearbyint(a / std::ldexp(1.0, E - 10));
-  if (m >= 2048.0) {
-    m *= 0.5;
-    E += 1;
-  }
-  if (m < 1024.0) return (unsigned short)(sign | (unsigned)m);  // subnormal
-  return (unsigned short)(sign | ((unsigned)(E + 15) << 10) | ((unsigned)m - 1024u));
+  if (a < std::ldexp(1.0, -14))  // subnormal (or rounds up to the smallest normal)
+    return (unsigned short)(sign | (unsigned)std::nearbyint(a * 16777216.0));
+  b += (1ull << 41) - 1 + ((b >> 42) & 1);  // to nearest even at 10 fraction bits
+  const unsigned e = (unsigned)(b >> 52) - 1023 + 15, m = (unsigned)(b >> 42) & 1023u;
+  return (unsigned short)(sign | (e << 10) | m);
 }
 double host_f16_value(unsigned short h) {
   const int ex = (h >> 10) & 31, man = h & 1023;
@@ -426,125 +354,277 @@ double host_f16_value(unsigned short h) {
   return (h & 0x8000) ? -v : v;
 }
 
-double half_entry(const MfmaTables& t, int rb, int row16, int k) {
-  const bool isE = rb < t.RBe;
-  const int row = 16 * (isE ? rb : rb - t.RBe) + row16;
-  const int rows = isE ? t.rowsE : t.rowsO;
-  if (row >= rows || k >= t.hK) return 0.0;
-  return isE ? t.E[(size_t)row * t.hK + k] : t.O[(size_t)row * t.hK + k];
+// Kernels of a size class with what their launches need: the blocks of each
+// kernel that fit a CU (registers, LDS).
+struct WaveClass {
+  WaveKernels k{};
+  int regs[WK_COUNT] = {0};
+};
+
+template <int C = WC_COUNT - 1>
+void fill_wave_classes(WaveClass* out) {
+  out[C].k = wave_class<C>();
+  if constexpr (C > 0) fill_wave_classes<C - 1>(out);
 }
 
-int setup_mfma_axis(sfrde_plan_s* p, int axis) {
-  if (p->n[axis] < 2) return SFRDE_OK;  // padding axis of a 1D plan: dense kernels
-  MfmaTables t = mfma_tables(p->bc, p->n[axis]);
-  if (!t.ok) return SFRDE_OK;
-  const bool f32 = p->dtype == SFRDE_F32;
-  const int W = f32 ? (axis == 0 ? XfX<float>::W : XfZ<float>::W) : MfmaXfF64::W;
-  const int threads = f32 ? XfZ<float>::THREADS : MfmaXfF64::THREADS;
-  // geometry
-  Geom& g = p->geom_m[axis];
-  g = p->geom[axis];
-  g.W = W;
-  g.pitch = W + 1;
-  g.wshift = 0;
-  while ((1 << g.wshift) < g.W) ++g.wshift;
-  if (g.inner == 1) {
-    g.tpo = 1;
-    g.tposh = 0;
-    g.ntiles = (g.outer + W - 1) / W;
-  } else {
-    // Tiles along strided axes hold one species (the species index becomes
-    // part of the outer block index; the fields are [S][total]): always in
-    // FP32, whose vector paths assume it, and in FP64 when the launch (all
-    // members) split by species still has at most one block per CU, i.e.
-    // leaves CUs idle otherwise; FP64 tiles of every species are faster
-    // once the blocks outnumber the CUs.
-    const long long tiles_all = g.outer * ((g.inner + W - 1) / W) * p->B;
-    if (f32 || tiles_all * p->S <= (long long)p->n_cu) {
-      g.outer *= p->S;
-      g.spt = 1;
+// The class table (filled on first use) and, per class on first use by a
+// plan, its kernels' register counts.
+int wave_class_info(int c, const WaveClass** out) {
+  static std::mutex mu;
+  static WaveClass tab[WC_COUNT];
+  static bool filled = false, known[WC_COUNT] = {false};
+  std::lock_guard<std::mutex> lock(mu);
+  if (!filled) {
+    fill_wave_classes(tab);
+    filled = true;
+  }
+  if (!known[c]) {
+    for (int i = 0; i < WK_COUNT; ++i) {
+      if (!tab[c].k.fn[i]) continue;
+      hipFuncAttributes at{};
+      HIPCHECK(hipFuncGetAttributes(&at, tab[c].k.fn[i]));
+      tab[c].regs[i] = at.numRegs;
     }
-    g.tpo = (g.inner + W - 1) / W;
-    g.tposh = pow2_shift(g.tpo);
-    g.ntiles = g.outer * g.tpo;
+    known[c] = true;
   }
-  // vector tile paths of the FP32 engine (their thread layouts assume these)
-  if (f32 && g.inner == 1)
-    g.fast = (g.n == 64 || g.n == 128 || g.n == 256) && (long long)p->S * g.n <= 512 &&
-             (long long)p->S * g.n >= 64 && g.outer % W == 0;
-  else if (f32)
-    g.fast = g.inner % W == 0 && g.n % 64 == 0 && g.n <= 256;
-  else  // FP64: full tiles of at most two species move through registers (TileIOF64;
-        // its x-axis layout needs n = 64, 128 or 256, strided axes a multiple of 64)
-    g.fast = g.n % 64 == 0 && g.n <= 256 && g.spt <= 2 &&
-             (g.inner == 1 ? g.outer % W == 0 && (g.n & (g.n - 1)) == 0 : g.inner % W == 0);
-  MfmaAxisDev& ax = p->mfax[axis];
-  ax.hK = t.hK;
-  ax.RBe = t.RBe;
-  ax.RB = t.RB;
-  ax.fb_pitch = p->dtype == SFRDE_F32 ? F32_FBP : t.hK + 2;
-  ax.r_pitch = W + 1;
-  ax.direct = p->bc != SFRDE_BC_PERIODIC;
-  size_t tile_bytes = (size_t)g.spt * g.n * g.pitch * p->w;
-  tile_bytes = (tile_bytes + 15) / 16 * 16;
-  // fold area: FP32 plans keep two binary16 terms of s and d and the column
-  // scales; FP64 plans s and d.
-  const size_t fold_bytes = p->dtype == SFRDE_F32 ? (size_t)f32_fold_bytes(W)
-                                                   : (size_t)2 * W * ax.fb_pitch * 8;
-  const size_t res_bytes = (size_t)16 * t.RB * ax.r_pitch * p->w;
-  ax.fb_off = (int)tile_bytes;
-  // FP32 x tiles: a second fold buffer where it fits (the unfold's result
-  // rows fit one buffer)
-  ax.nfb = p->dtype == SFRDE_F32 && axis == 0 &&
-                   tile_bytes + std::max(2 * fold_bytes, res_bytes) <= 160 * 1024
-               ? 2
-               : 1;
-  size_t lds = tile_bytes + std::max(ax.nfb * fold_bytes, res_bytes);
-  lds = std::max<size_t>(lds, (size_t)threads * sizeof(double));
-  if (lds > 160 * 1024) return SFRDE_OK;  // does not fit: FFT or dense kernels
-  // the engine's tile indices are 32-bit, with room for one stride of the grid
-  if (g.ntiles > 0x7fff0000LL) return SFRDE_OK;
-  p->lds_m[axis] = lds;
-  // persistent grid: as many blocks as fit on the CUs at once
-  const long long per_cu = 1;
-  // ensembles launch B times these blocks (blockIdx.y = member)
-  const long long slots = std::max<long long>(1, ((long long)p->n_cu * per_cu + p->B - 1) / p->B);
-  p->grid_m[axis] = (unsigned)std::min<long long>(g.ntiles, slots);
-  // fragment-ordered split matrices
-  if (p->dtype == SFRDE_F32) {
-    std::vector<unsigned short> frag((size_t)MF_WAVES * MF_KSMAX_F32 * 2 * 64 * 8, 0);
-    for (int rb = 0; rb < t.RB; ++rb)
-      for (int ks = 0; ks < MF_KSMAX_F32; ++ks)
-        for (int lane = 0; lane < 64; ++lane)
-          for (int e = 0; e < 8; ++e) {
-            // folded entries 64 and up sit rotated by four within each group
-            // of eight in the engine's fold buffer: the same order here
-            const int k = 32 * ks + 8 * (lane / 16) + e;
-            const double v = half_entry(t, rb, lane % 16, k >= 64 ? k ^ 4 : k);
-            const unsigned short h0 = host_f16(v);
-            const unsigned short h1 = host_f16(v - host_f16_value(h0));
-            frag[((((size_t)rb * MF_KSMAX_F32 + ks) * 2 + 0) * 64 + lane) * 8 + e] = h0;
-            frag[((((size_t)rb * MF_KSMAX_F32 + ks) * 2 + 1) * 64 + lane) * 8 + e] = h1;
-          }
-    TRY(dev_alloc(p, &p->mf_A[axis], frag.size() * sizeof(unsigned short)));
-    HIPCHECK(hipMemcpy(p->mf_A[axis], frag.data(), frag.size() * sizeof(unsigned short),
-                       hipMemcpyHostToDevice));
+  *out = &tab[c];
+  return SFRDE_OK;
+}
+
+// Size class of an axis, -1 if the engine has none.
+int wave_class_of(int dtype, int bc, long long n, bool source) {
+  // (the one-point padding axis of a 1D plan is an odd axis on every boundary)
+  const bool per = bc == SFRDE_BC_PERIODIC && n > 1, f32 = dtype == SFRDE_F32;
+  const long long half = per ? n / 2 + 1 : (n + 1) / 2;  // positions of an even axis
+  const bool odd = !per && n % 2 == 1;
+  const int c2 = f32 ? WC_F32_2X : WC_F64_2X, c4 = f32 ? WC_F32_4X : WC_F64_4X;
+  const int lay = odd ? 2 : 1;
+  // exact classes (they have no kernel for manufactured sources)
+  if (!per && !source && n == 64) return c2;
+  if (!per && !source && n == 128) return c4;
+  if (!per && !source && n == 192 && f32) return WC_F32_6X;
+  if (!per && !source && n == 256) return f32 ? WC_F32_8X : WC_F64_8X;
+  if (half <= 32) return c2 + lay;
+  if (half <= 64) return c4 + lay;
+  if (f32) return half <= 128 ? WC_F32_8X + lay : -1;
+  if (odd) return half <= 128 ? WC_F64_8O : -1;
+  return half <= 144 ? WC_F64_9E : -1;
+}
+
+// The engine's view of an axis: segments of pair positions (wave.h).
+WaveAxis wave_axis(int bc, long long n) {
+  WaveAxis x{};
+  x.n = (int)n;
+  x.periodic = bc == SFRDE_BC_PERIODIC && n > 1;
+  auto blocks = [](int c) { return (c + 15) / 16; };
+  if (x.periodic) {
+    const int half = (int)(n / 2) + 1;  // p = 0 .. n/2
+    x.da = 1;
+    x.s0 = WaveSeg{half, 1, (int)((n + 1) / 2), 0, (int)n, 0};
+    if (n % 2 == 1) x.s0.ca = (int)((n + 1) / 2);
+    x.nb = blocks(x.s0.ca);
+  } else if (n % 2 == 0) {
+    const int half = (int)(n / 2);
+    x.da = 2;
+    x.s0 = WaveSeg{half, 0, half, 0, (int)n - 1, half - 1};
+    x.nb = blocks(half);
   } else {
-    std::vector<double> frag((size_t)MF_WAVES * MF_KSMAX_F64 * 64, 0.0);
-    for (int rb = 0; rb < t.RB; ++rb)
-      for (int ks = 0; ks < MF_KSMAX_F64; ++ks)
-        for (int lane = 0; lane < 64; ++lane)
-          frag[((size_t)rb * MF_KSMAX_F64 + ks) * 64 + lane] =
-              half_entry(t, rb, lane % 16, 4 * ks + lane / 16);
-    TRY(dev_alloc(p, &p->mf_A[axis], frag.size() * sizeof(double)));
-    HIPCHECK(hipMemcpy(p->mf_A[axis], frag.data(), frag.size() * sizeof(double),
-                       hipMemcpyHostToDevice));
+    const int mid = (int)((n - 1) / 2);  // pairs; the middle index
+    const int qe = (mid + 1) / 2, qo = mid / 2;
+    x.da = 2;
+    x.s0 = WaveSeg{qe + (mid % 2 == 0 ? 1 : 0), 0, qe, 0, (int)n - 1, mid};
+    x.s1 = WaveSeg{qo + (mid % 2 == 1 ? 1 : 0), 0, qo, 1, (int)n - 2, mid - 1};
+    x.nb = blocks(x.s0.ca);
+    x.nb1 = blocks(x.s1.ca);
   }
-  ax.Afrag = p->mf_A[axis];
-  ax.n = (int)p->n[axis];
-  ax.ns = t.ns;
-  ax.periodic = p->bc == SFRDE_BC_PERIODIC;
-  p->use_m[axis] = true;
+  return x;
+}
+
+// The half matrices E and O [row][position] in FP64. A point without a partner
+// stands on both sides: half the entry in E, none in O.
+struct WaveMatrix {
+  const WaveAxis& x;
+  int bc, seg_at;
+  std::vector<double> trig;  // cos / sin of the axis' angles
+  std::vector<double> trig2;
+  WaveMatrix(int bc_, const WaveAxis& x_, int layout, int nb)
+      : x(x_), bc(bc_), seg_at(layout == WL_ODD ? 16 * (nb / 2) : 16 * nb) {
+    const double pi = 3.14159265358979323846;
+    const long long n = x.n;
+    if (bc == SFRDE_BC_PERIODIC) {
+      trig.resize(n);
+      trig2.resize(n);
+      for (long long m = 0; m < n; ++m) {
+        trig[m] = cos(2.0 * pi * double(m) / double(n));
+        trig2[m] = 2 * m == n ? 0.0 : sin(2.0 * pi * double(m) / double(n));
+      }
+    } else if (bc == SFRDE_BC_DIRICHLET) {
+      trig.resize(2 * (n + 1));
+      for (long long m = 0; m < 2 * (n + 1); ++m) trig[m] = sin(pi * double(m) / double(n + 1));
+    } else if (n > 1) {
+      trig.resize(2 * (n - 1));
+      for (long long m = 0; m < 2 * (n - 1); ++m) trig[m] = cos(pi * double(m) / double(n - 1));
+    }
+  }
+  double operator()(int half, int row, int pos) const {
+    const long long n = x.n;
+    const WaveSeg& g = pos < seg_at ? x.s0 : x.s1;
+    const int q = pos < seg_at ? pos : pos - seg_at;
+    const int rows = x.periodic ? (int)(n / 2) + 1 : (int)(half ? n / 2 : (n + 1) / 2);
+    if (q >= g.ca || row >= rows) return 0.0;
+    const bool fixed = !(q >= g.blo && q < g.bhi);
+    if (half && fixed) return 0.0;
+    const double f = fixed ? 0.5 : 1.0;
+    if (n == 1) return f;  // padding axis of a 1D plan: the identity
+    const long long a = g.a0 + (long long)x.da * q;
+    if (x.periodic) return half ? trig2[(row * a) % n] : f * trig[(row * a) % n];
+    const long long k = 2LL * row + half;
+    if (bc == SFRDE_BC_DIRICHLET) return f * trig[((k + 1) * (a + 1)) % (2 * (n + 1))];
+    return f * (a == 0 || a == n - 1 ? 0.5 : 1.0) * trig[(k * a) % (2 * (n - 1))];
+  }
+};
+
+int setup_wave_axis(sfrde_plan_s* p, int axis) {
+  const long long n = p->n[axis];
+  const int c = wave_class_of(p->dtype, p->bc, n, p->rxn.kind >= RXN_HUXLEY_MMS);
+  if (c < 0) return SFRDE_OK;
+  long long inner = 1;
+  for (int a = 0; a < axis; ++a) inner *= p->n[a];
+  // 32-bit lane offsets within a tile of a strided axis, 32-bit line numbers
+  const long long reach = (inner % 16 ? 2 : 1) * (n + 32) * inner * (long long)p->w;
+  const long long lines = axis == 0 ? p->total / n : (long long)p->S * (p->total / n);
+  if (axis > 0 && reach >= (1LL << 32)) return SFRDE_OK;
+  if (lines >= (1LL << 31) - 64) return SFRDE_OK;
+  const WaveClass* wc = nullptr;
+  TRY(wave_class_info(c, &wc));
+  const int nb = wc->k.nb, layout = wc->k.layout;
+  WaveAxis& x = p->wax[axis];
+  x = wave_axis(p->bc, n);
+  WaveTiles& t = p->wtl[axis];
+  t.lines = lines;
+  t.inner = inner;
+  t.cpsh = p->S == 1 ? 4 : p->S == 2 ? 3 : 2;
+  const long long per = axis == 0 ? 1LL << t.cpsh : 16;
+  t.ntiles = (int)((lines + per - 1) / per);
+  t.priv = layout == WL_EXACT && (p->S == 1 || p->S == 2 || p->S == 4) && lines % per == 0;
+  const int RS = 16 * nb;
+  // axes of one length share a table
+  for (int b = 0; b < axis && !x.A; ++b)
+    if (p->wcls[b] >= 0 && p->n[b] == n) x.A = p->wax[b].A;
+  const WaveMatrix mat(p->bc, x, layout, nb);
+  if (x.A) {
+  } else if (p->dtype == SFRDE_F32) {
+    const int KS = nb / 2;
+    std::vector<unsigned short> tab(wc->k.tab_bytes / 2, 0);
+    for (int h = 0; h < 2; ++h)
+      for (int ks = 0; ks < KS; ++ks)
+        for (int g = 0; g < 4; ++g)
+          for (int row = 0; row < RS; ++row)
+            for (int e = 0; e < 8; ++e) {
+              const int pos = 32 * ks + 4 * g + (e < 4 ? e : 12 + e);
+              const double v = mat(h, row, pos);
+              const unsigned short h0 = host_f16(v);
+              const unsigned short h1 = host_f16(v - host_f16_value(h0));
+              const size_t u = ((size_t)((h * 2 * KS + ks) * 4 + g) * RS + row) * 8 + e;
+              tab[u] = h0;
+              tab[u + (size_t)KS * 4 * RS * 8] = h1;
+            }
+    TRY(dev_alloc(p, &p->wA[axis], wc->k.tab_bytes));
+    HIPCHECK(hipMemcpy(p->wA[axis], tab.data(), wc->k.tab_bytes, hipMemcpyHostToDevice));
+  } else {
+    const int KS = 4 * nb;
+    std::vector<double> tab(wc->k.tab_bytes / 8, 0.0);
+    for (int h = 0; h < 2; ++h)
+      for (int ks = 0; ks < KS; ++ks)
+        for (int g = 0; g < 4; ++g)
+          for (int row = 0; row < RS; ++row)
+            tab[((size_t)(h * KS + ks) * 4 + g) * RS + row] =
+                mat(h, row, 4 * ks + g);
+    TRY(dev_alloc(p, &p->wA[axis], wc->k.tab_bytes));
+    HIPCHECK(hipMemcpy(p->wA[axis], tab.data(), wc->k.tab_bytes, hipMemcpyHostToDevice));
+  }
+  if (!x.A) x.A = p->wA[axis];
+  // more LDS than the default limit where the table needs it
+  for (int i = 0; i < WK_COUNT; ++i)
+    for (const void* f : {wc->k.fn[i], wc->k.grp[i]})
+      if (f)
+        HIPCHECK(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+  p->wcls[axis] = c;
+  return SFRDE_OK;
+}
+
+// Launch of a wave kernel over an axis. Blocks: one tile per block while the
+// tiles do not outnumber the CUs (every CU gets work; the other waves help to
+// load the matrix), one tile per wave up to a full device, then runs of tiles.
+int wave_grid(const sfrde_plan_s* p, int axis, int kernel, size_t lds, const WaveClass** out,
+              unsigned* blocks) {
+  const WaveClass* wc = nullptr;
+  TRY(wave_class_info(p->wcls[axis], &wc));
+  const int waves = wc->k.threads / 64;
+  int regs = wc->regs[kernel];
+  // the kernels that add to one set of partials run on one grid
+  if (kernel >= WK_ZADJTH)
+    regs = std::max({wc->regs[WK_ZADJTH], wc->regs[WK_ZADJTH + 1], wc->regs[WK_ZADJTH + 2]});
+  const int per_simd = 512 / std::max(1, (regs + 7) / 8 * 8);
+  long long fit = std::max(1, std::min(per_simd * 4, 32) / waves);
+  if (lds > 0) fit = std::min<long long>(fit, std::max<long long>(1, (160 * 1024) / (long long)lds));
+  const long long tiles =
+      kernel == WK_SY2 ? (p->wtl[axis].lines + 31) / 32 : (long long)p->wtl[axis].ntiles;
+  const long long cus = std::max<long long>(1, (p->n_cu + p->B - 1) / p->B);
+  const long long most = std::max<long long>(1, ((long long)p->n_cu * fit + p->B - 1) / p->B);
+  long long g = tiles;
+  if (tiles > cus) g = std::min(most, std::max(cus, (tiles + waves - 1) / waves));
+  *out = wc;
+  *blocks = (unsigned)g;
+  return SFRDE_OK;
+}
+
+// LDS of a launch: the class' matrix copy, the eigenvalue tables of the
+// kernels that form L, the scratch of the block sums.
+size_t wave_lds(const sfrde_plan_s* p, int axis, int kernel, const WaveKernels& k) {
+  size_t lds = k.lds_a;
+  if ((kernel >= WK_ZFLY && kernel < WK_ZFLY + 4) || kernel >= WK_ZADJFLY)
+    lds += (size_t)(32 * k.nb + p->n[0] + (p->ndim == 3 ? p->n[1] : 0)) * sizeof(float);
+  if (kernel == WK_XADJ + 1 || kernel >= WK_ZADJTH)
+    lds = std::max<size_t>(lds, (size_t)RXN_NP_MAX * 16 * sizeof(double));
+  return lds;
+}
+
+// Whether an axis runs the group kernels (one tile per block, a wave per row
+// block): its tiles are at most one per CU.
+bool use_group(const sfrde_plan_s* p, int axis) {
+  return (long long)p->wtl[axis].ntiles * p->B <= (long long)p->n_cu;
+}
+
+// Blocks of a kernel's launch over an axis.
+int wave_blocks(const sfrde_plan_s* p, int axis, int kernel, unsigned* blocks) {
+  const WaveClass* wc = nullptr;
+  TRY(wave_class_info(p->wcls[axis], &wc));
+  if (use_group(p, axis)) {
+    *blocks = (unsigned)p->wtl[axis].ntiles;
+    return SFRDE_OK;
+  }
+  return wave_grid(p, axis, kernel, wave_lds(p, axis, kernel, wc->k), &wc, blocks);
+}
+
+template <class Args>
+int launch_wave(sfrde_plan_s* p, int axis, int kernel, Args& a) {
+  const WaveClass* wc = nullptr;
+  TRY(wave_class_info(p->wcls[axis], &wc));
+  if (kernel != WK_SY2 && use_group(p, axis)) {
+    void* args[] = {&a, &p->wax[axis], &p->wtl[axis]};
+    HIPCHECK(hipLaunchKernel(wc->k.grp[kernel],
+                             dim3((unsigned)p->wtl[axis].ntiles, (unsigned)p->B),
+                             dim3((unsigned)(64 * wc->k.nb)), args, wc->k.lds_g, p->stream));
+    return SFRDE_OK;
+  }
+  const size_t lds = wave_lds(p, axis, kernel, wc->k);
+  unsigned g = 1;
+  TRY(wave_grid(p, axis, kernel, lds, &wc, &g));
+  WaveTiles tl = p->wtl[axis];
+  if (kernel == WK_SY2) tl.ntiles = (int)((tl.lines + 31) / 32);
+  void* args[] = {&a, &p->wax[axis], &tl};
+  HIPCHECK(hipLaunchKernel(wc->k.fn[kernel], dim3(g, (unsigned)p->B), dim3((unsigned)wc->k.threads), args, lds, p->stream));
   return SFRDE_OK;
 }
 
@@ -554,7 +634,7 @@ int setup_mfma_axis(sfrde_plan_s* p, int axis) {
 template <typename T>
 int setup_fft_axis(sfrde_plan_s* p, int axis) {
   const long long n = p->n[axis];
-  if (p->use_m[axis] || p->bc != SFRDE_BC_PERIODIC ||
+  if (p->wcls[axis] >= 0 || p->bc != SFRDE_BC_PERIODIC ||
       !(n == 256 || n == 512 || n == 1024))
     return SFRDE_OK;
   Geom& g = p->geom_f[axis];
@@ -601,72 +681,11 @@ int setup_fft_axis(sfrde_plan_s* p, int axis) {
   return SFRDE_OK;
 }
 
-template <typename T>
-int set_lds_attrs(size_t bytes) {
-  std::vector<const void*> fns = {
-      reinterpret_cast<const void*>(&k_xstage_m<T, XfX<T>, false>),
-      reinterpret_cast<const void*>(&k_zstage_m<T, XfZ<T>, -1, false>),
-      reinterpret_cast<const void*>(&k_zstage_m<T, XfZ<T>, 0, false>),
-      reinterpret_cast<const void*>(&k_zstage_m<T, XfZ<T>, 1, false>),
-      reinterpret_cast<const void*>(&k_zstage_m<T, XfZ<T>, 2, false>),
-      reinterpret_cast<const void*>(&k_zstage_m<T, XfZ<T>, 3, false>),
-      reinterpret_cast<const void*>(&k_xadj_m<T, XfX<T>, false>),
-      reinterpret_cast<const void*>(&k_zadj_m<T, XfZ<T>, false>),
-      reinterpret_cast<const void*>(&k_single_m<T, XfX<T>, false>),
-      reinterpret_cast<const void*>(&k_single_m<T, XfZ<T>, false>)};
-  if constexpr (std::is_same<T, double>::value) {
-    const void* kinds[] = {
-        reinterpret_cast<const void*>(&k_xadj_m<T, XfX<T>, false, 2, false, RXN_LINEAR>),
-        reinterpret_cast<const void*>(&k_xadj_m<T, XfX<T>, false, 2, false, RXN_FHN>),
-        reinterpret_cast<const void*>(&k_xadj_m<T, XfX<T>, false, 2, false, RXN_GRAY_SCOTT>),
-        reinterpret_cast<const void*>(&k_xadj_m<T, XfX<T>, false, 2, false, RXN_SCHNAKENBERG>),
-        reinterpret_cast<const void*>(&k_xadj_m<T, XfX<T>, false, 2, false, RXN_GM>)};
-    for (const void* f : kinds) fns.push_back(f);
-  }
-  if constexpr (std::is_same<T, float>::value) {
-    const void* fast[] = {reinterpret_cast<const void*>(&k_xstage_m<T, XfX<T>, true>),
-                          reinterpret_cast<const void*>(&k_zstage_m<T, XfZ<T>, -1, true>),
-                          reinterpret_cast<const void*>(&k_zstage_m<T, XfZ<T>, 0, true>),
-                          reinterpret_cast<const void*>(&k_zstage_m<T, XfZ<T>, 1, true>),
-                          reinterpret_cast<const void*>(&k_zstage_m<T, XfZ<T>, 2, true>),
-                          reinterpret_cast<const void*>(&k_zstage_m<T, XfZ<T>, 3, true>),
-                          reinterpret_cast<const void*>(&k_xadj_m<T, XfX<T>, true>),
-                          reinterpret_cast<const void*>(&k_zadj_m<T, XfZ<T>, true>),
-                          reinterpret_cast<const void*>(&k_zadj_m<T, XfZ<T>, true, 0, 0>),
-                          reinterpret_cast<const void*>(&k_zadj_m<T, XfZ<T>, true, 1, 0>),
-                          reinterpret_cast<const void*>(&k_zadj_m<T, XfZ<T>, true, 2, 0>),
-                          reinterpret_cast<const void*>(&k_zadj_m<T, XfZ<T>, true, 3, 0>),
-                          reinterpret_cast<const void*>(&k_zadj_m<T, XfZ<T>, true, MODE_INIT, 0>),
-                          reinterpret_cast<const void*>(&k_zadj_m<T, XfZ<T>, true, 0, 1>),
-                          reinterpret_cast<const void*>(&k_zadj_m<T, XfZ<T>, true, 1, 1>),
-                          reinterpret_cast<const void*>(&k_zadj_m<T, XfZ<T>, true, 2, 1>),
-                          reinterpret_cast<const void*>(&k_zadj_m<T, XfZ<T>, true, 3, 1>),
-                          reinterpret_cast<const void*>(&k_zadj_m<T, XfZ<T>, true, MODE_INIT, 1>),
-                          reinterpret_cast<const void*>(&k_xadj_m<T, XfX<T>, true, 1>),
-                          reinterpret_cast<const void*>(&k_xadj_m<T, XfX<T>, true, 2>),
-                          reinterpret_cast<const void*>(&k_xadj_m<T, XfX<T>, true, 2, true>),
-                          reinterpret_cast<const void*>(&k_single_m<T, XfX<T>, true>),
-                          reinterpret_cast<const void*>(&k_single_m<T, XfZ<T>, true>),
-                          reinterpret_cast<const void*>(&k_single_m<T, XfZ<T>, true, 1>),
-                          reinterpret_cast<const void*>(&k_single_m<T, XfX<T>, true, 2>),
-                          reinterpret_cast<const void*>(&k_single_m<T, XfZ<T>, true, 2>),
-                          reinterpret_cast<const void*>(&k_xstage_m<T, XfX<T>, true, RXN_LINEAR>),
-                          reinterpret_cast<const void*>(&k_xstage_m<T, XfX<T>, true, RXN_FHN>),
-                          reinterpret_cast<const void*>(&k_xstage_m<T, XfX<T>, true, RXN_GRAY_SCOTT>),
-                          reinterpret_cast<const void*>(&k_xstage_m<T, XfX<T>, true, RXN_SCHNAKENBERG>),
-                          reinterpret_cast<const void*>(&k_xstage_m<T, XfX<T>, true, RXN_GM>)};
-    for (const void* f : fast) fns.push_back(f);
-  }
-  for (const void* f : fns)
-    HIPCHECK(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
-  return SFRDE_OK;
-}
-
 // --------------------------------------------------------------------------
 template <typename T>
 StageArgs<T> stage_args(sfrde_plan_s* p, int axis, void* P) {
   StageArgs<T> a{};
-  a.g = p->use_m[axis] ? p->geom_m[axis] : p->use_f[axis] ? p->geom_f[axis] : p->geom[axis];
+  a.g = p->use_f[axis] ? p->geom_f[axis] : p->geom[axis];
   a.Mt = (const T*)(p->use_f[axis] ? p->tw[axis] : p->Mt[axis]);
   a.P = (T*)P;
   a.coef = (const T*)p->coef;
@@ -678,8 +697,6 @@ StageArgs<T> stage_args(sfrde_plan_s* p, int axis, void* P) {
     a.kt[s] = T(p->kappa[s] * p->dt);
     a.ha[s] = T(0.5 * p->alpha[s]);
   }
-  a.lfly = p->lfly && axis == p->ndim - 1;
-  a.lam_off = (int)p->lam_off;
   a.uhat = (T*)p->uhat;
   a.ctil = (T*)p->ctil;
   a.acc = (T*)p->acc;
@@ -701,30 +718,10 @@ StageArgs<T> stage_args(sfrde_plan_s* p, int axis, void* P) {
   return a;
 }
 
-// The FP32 engine's vector tile paths: the axis geometry allows them and
-// every field pointer the kernel moves tiles of is 16-byte aligned.
-template <typename T>
-bool use_fast(const sfrde_plan_s* p, int axis, std::initializer_list<const void*> ptrs) {
-  if (!std::is_same<T, float>::value || !p->geom_m[axis].fast) return false;
-  for (const void* q : ptrs)
-    if (reinterpret_cast<uintptr_t>(q) & 15u) return false;
-  return true;
-}
-
-// FP64 matrix-core launches move tiles through registers only with 16-byte
-// aligned fields (the plan's own buffers always are).
-template <typename T>
-void align_check(Geom& g, std::initializer_list<const void*> ptrs) {
-  if (std::is_same<T, float>::value) return;
-  for (const void* q : ptrs)
-    if (reinterpret_cast<uintptr_t>(q) & 15u) g.fast = 0;
-}
-
 template <typename T>
 int launch_single(sfrde_plan_s* p, int axis, const void* src, void* dst, int pre_div, int post_mul) {
   SingleArgs<T> a{};
-  a.g = p->use_m[axis] ? p->geom_m[axis] : p->use_f[axis] ? p->geom_f[axis] : p->geom[axis];
-  align_check<T>(a.g, {src, dst});
+  a.g = p->use_f[axis] ? p->geom_f[axis] : p->geom[axis];
   a.Mt = (const T*)(p->use_f[axis] ? p->tw[axis] : p->Mt[axis]);
   a.src = (const T*)src;
   a.dst = (T*)dst;
@@ -737,55 +734,18 @@ int launch_single(sfrde_plan_s* p, int axis, const void* src, void* dst, int pre
   a.n1 = p->n[1];
   a.n2 = p->n[2];
   const long long pk = prof_start(p, KC_Y);
-  if (p->use_m[axis]) {
-    const dim3 grid(p->grid_m[axis], p->B);
-    const size_t lds = p->lds_m[axis];
-    const bool fast = use_fast<T>(p, axis, {src, dst});
-    // fast launches without point weights: the kernel holding only the
-    // tile path that runs
-    const bool plain = fast && !a.pre_divide_w && !a.post_multiply_w;
-    // results straight to global memory: DCT-I / DST-I on one-species
-    // strided tiles (rows inner apart, columns contiguous)
-    const bool to_glob = p->mfax[axis].direct != 0 && a.g.spt == 1 && a.g.inner > 1;
-    if (axis == 0) {
-      const dim3 block(XfX<T>::THREADS);
-      if constexpr (std::is_same<T, float>::value)
-        if (fast) {
-          if (plain)  // x tiles: through the tile
-            hipLaunchKernelGGL((k_single_m<T, XfX<T>, true, 2>), grid, block, lds, p->stream, a,
-                               p->mfax[axis]);
-          else
-            hipLaunchKernelGGL((k_single_m<T, XfX<T>, true>), grid, block, lds, p->stream, a,
-                               p->mfax[axis]);
-          goto launched;
-        }
-      hipLaunchKernelGGL((k_single_m<T, XfX<T>, false>), grid, block, lds, p->stream, a,
-                         p->mfax[axis]);
-    } else {
-      const dim3 block(XfZ<T>::THREADS);
-      if constexpr (std::is_same<T, float>::value)
-        if (fast) {
-          if (plain && to_glob)
-            hipLaunchKernelGGL((k_single_m<T, XfZ<T>, true, 1>), grid, block, lds, p->stream, a,
-                               p->mfax[axis]);
-          else if (plain)
-            hipLaunchKernelGGL((k_single_m<T, XfZ<T>, true, 2>), grid, block, lds, p->stream, a,
-                               p->mfax[axis]);
-          else
-            hipLaunchKernelGGL((k_single_m<T, XfZ<T>, true>), grid, block, lds, p->stream, a,
-                               p->mfax[axis]);
-          goto launched;
-        }
-      hipLaunchKernelGGL((k_single_m<T, XfZ<T>, false>), grid, block, lds, p->stream, a,
-                         p->mfax[axis]);
-    }
+  if (p->wcls[axis] >= 0) {
+    // two columns per lane where the tiles still give every CU four waves or
+    // more (below that the shorter chain of one column wins)
+    const bool two = p->dtype == SFRDE_F32 && p->wtl[axis].inner % 2 == 0 &&
+                     p->wtl[axis].lines / 32 * p->B >= 4LL * p->n_cu;
+    TRY(launch_wave(p, axis, axis == 0 ? WK_SX : two ? WK_SY2 : WK_SY, a));
   } else if (p->use_f[axis]) {
     hipLaunchKernelGGL((k_single<T, FftXf, true>), dim3((unsigned)a.g.ntiles, p->B),
                        dim3(p->thr_f[axis]), p->lds_f[axis], p->stream, a);
   } else
     hipLaunchKernelGGL(k_single<T>, dim3((unsigned)a.g.ntiles, p->B), dim3(NTHREADS),
                        p->lds[axis], p->stream, a);
-launched:
   prof_stop(p, pk);
   HIPCHECK(hipGetLastError());
   return SFRDE_OK;
@@ -820,35 +780,8 @@ int launch_x(sfrde_plan_s* p, int stage, double t, T* st_phys) {
   a.t = t;
   a.st_phys = st_phys;
   const long long pk = prof_start(p, KC_X);
-  if (p->use_m[0]) {
-    const dim3 grid(p->grid_m[0], p->B), block(XfX<T>::THREADS);
-    const bool fast = use_fast<T>(p, 0, {p->P, st_phys});
-    // FP32, two species, non-periodic x: the register-fed kernel of the
-    // plan's reaction kind
-    const int rk = std::is_same<T, float>::value && fast && p->S == 2 &&
-                           p->bc != SFRDE_BC_PERIODIC && p->rxn.kind <= RXN_GM
-                       ? p->rxn.kind
-                       : -1;
-    if constexpr (std::is_same<T, float>::value) {
-      if (rk >= 0) {
-        const size_t lds = p->lds_m[0];
-        switch (rk) {
-          case RXN_LINEAR: hipLaunchKernelGGL((k_xstage_m<T, XfX<T>, true, RXN_LINEAR>), grid, block, lds, p->stream, a, p->mfax[0]); break;
-          case RXN_FHN: hipLaunchKernelGGL((k_xstage_m<T, XfX<T>, true, RXN_FHN>), grid, block, lds, p->stream, a, p->mfax[0]); break;
-          case RXN_GRAY_SCOTT: hipLaunchKernelGGL((k_xstage_m<T, XfX<T>, true, RXN_GRAY_SCOTT>), grid, block, lds, p->stream, a, p->mfax[0]); break;
-          case RXN_SCHNAKENBERG: hipLaunchKernelGGL((k_xstage_m<T, XfX<T>, true, RXN_SCHNAKENBERG>), grid, block, lds, p->stream, a, p->mfax[0]); break;
-          default: hipLaunchKernelGGL((k_xstage_m<T, XfX<T>, true, RXN_GM>), grid, block, lds, p->stream, a, p->mfax[0]); break;
-        }
-        goto x_launched;
-      }
-    }
-    if (fast)
-      hipLaunchKernelGGL((k_xstage_m<T, XfX<T>, std::is_same<T, float>::value>), grid, block,
-                         p->lds_m[0], p->stream, a, p->mfax[0]);
-    else
-      hipLaunchKernelGGL((k_xstage_m<T, XfX<T>, false>), grid, block, p->lds_m[0], p->stream, a,
-                         p->mfax[0]);
-  x_launched:;
+  if (p->wcls[0] >= 0) {
+    TRY(launch_wave(p, 0, p->rxn.kind >= RXN_HUXLEY_MMS ? WK_XSRC : WK_X, a));
   } else if (p->use_f[0]) {
     hipLaunchKernelGGL((k_xstage<T, FftXf, true>), dim3((unsigned)a.g.ntiles, p->B), dim3(p->thr_f[0]),
                        p->lds_f[0], p->stream, a);
@@ -860,34 +793,6 @@ int launch_x(sfrde_plan_s* p, int stage, double t, T* st_phys) {
   return SFRDE_OK;
 }
 
-// The four forward stages of FP32 plans have their own Z kernels.
-template <typename T>
-void launch_zstage_m(bool fast, int mode, dim3 grid, size_t lds, hipStream_t st,
-                     const StageArgs<T>& a, const MfmaAxisDev& ax) {
-  const dim3 block(XfZ<T>::THREADS);
-  if constexpr (std::is_same<T, float>::value) {
-    if (fast) {
-      switch (mode) {
-        case 0: hipLaunchKernelGGL((k_zstage_m<T, XfZ<T>, 0, true>), grid, block, lds, st, a, ax); return;
-        case 1: hipLaunchKernelGGL((k_zstage_m<T, XfZ<T>, 1, true>), grid, block, lds, st, a, ax); return;
-        case 2: hipLaunchKernelGGL((k_zstage_m<T, XfZ<T>, 2, true>), grid, block, lds, st, a, ax); return;
-        case 3: hipLaunchKernelGGL((k_zstage_m<T, XfZ<T>, 3, true>), grid, block, lds, st, a, ax); return;
-        default: hipLaunchKernelGGL((k_zstage_m<T, XfZ<T>, -1, true>), grid, block, lds, st, a, ax); return;
-      }
-    }
-  }
-  if constexpr (!std::is_same<T, float>::value) {
-    switch (mode) {
-      case 0: hipLaunchKernelGGL((k_zstage_m<T, XfZ<T>, 0, false>), grid, block, lds, st, a, ax); return;
-      case 1: hipLaunchKernelGGL((k_zstage_m<T, XfZ<T>, 1, false>), grid, block, lds, st, a, ax); return;
-      case 2: hipLaunchKernelGGL((k_zstage_m<T, XfZ<T>, 2, false>), grid, block, lds, st, a, ax); return;
-      case 3: hipLaunchKernelGGL((k_zstage_m<T, XfZ<T>, 3, false>), grid, block, lds, st, a, ax); return;
-      default: break;
-    }
-  }
-  hipLaunchKernelGGL((k_zstage_m<T, XfZ<T>, -1, false>), grid, block, lds, st, a, ax);
-}
-
 // uhat: the spectral state this stage reads (stages 0, 1) or writes (stage
 // 3); NULL: the plan's own.
 template <typename T>
@@ -896,21 +801,12 @@ int launch_z(sfrde_plan_s* p, int mode, const void* src, T* st_fhat, T* uhat = n
   StageArgs<T> a = stage_args<T>(p, ax, p->P);
   a.mode = mode;
   a.src = (const T*)src;
-  align_check<T>(a.g, {src});
   a.st_fhat = st_fhat;
   if (uhat) a.uhat = uhat;
   const long long pk = prof_start(p, KC_Z);
-  if (p->use_m[ax])
-    {
-      const bool fast = use_fast<T>(p, ax, {p->P, src});
-      // the per-stage kernels: forward stages (the vector layout holds last
-      // axes of 64 to 256 points in steps of 64), L formed in the kernel or
-      // read from the table
-      const bool staged = fast && mode >= 0 && mode <= 3 && !src && (p->lfly || p->ltab);
-      launch_zstage_m<T>(fast, staged || (!fast && !src && mode >= 0 && mode <= 3) ? mode : -1,
-                         dim3(p->grid_m[ax], p->B), p->lds_m[ax], p->stream, a, p->mfax[ax]);
-    }
-  else if (p->use_f[ax]) {
+  if (p->wcls[ax] >= 0) {
+    TRY(launch_wave(p, ax, mode > 3 ? WK_ZINIT : (p->lfly ? WK_ZFLY : WK_Z) + mode, a));
+  } else if (p->use_f[ax]) {
     hipLaunchKernelGGL((k_zstage<T, FftXf, true>), dim3((unsigned)a.g.ntiles, p->B), dim3(p->thr_f[ax]),
                        p->lds_f[ax], p->stream, a);
   } else
@@ -1064,14 +960,6 @@ int resume_t(sfrde_plan_s* p, const void* ckpt, long long slot, void* state, lon
 }
 
 // --------------------------------------------------------------------------
-// The FP64 adjoint x kernel of reaction kind KIND (two species).
-template <int KIND>
-void launch_xadj64(sfrde_plan_s* p, dim3 grid, dim3 block, size_t lds,
-                   const StageArgs<double>& a) {
-  hipLaunchKernelGGL((k_xadj_m<double, XfX<double>, false, 2, false, KIND>), grid, block, lds,
-                     p->stream, a, p->mfax[0]);
-}
-
 template <typename T>
 int launch_xadj(sfrde_plan_s* p, int stage, const StepStore<T>& st) {
   StageArgs<T> a = stage_args<T>(p, 0, p->Pa);
@@ -1079,42 +967,8 @@ int launch_xadj(sfrde_plan_s* p, int stage, const StepStore<T>& st) {
   a.st_phys = st.phys;
   a.rp_acc = p->rp_acc;
   const long long pk = prof_start(p, KC_XADJ);
-  if (p->use_m[0]) {
-    const dim3 grid(p->grid_m[0], p->B), block(XfX<T>::THREADS);
-    const bool fast = use_fast<T>(p, 0, {p->Pa});
-    if constexpr (std::is_same<T, double>::value) {
-      // FP64, two species: the instance of the plan's reaction kind
-      if (p->S == 2 && p->rxn.kind <= RXN_GM) {
-        const size_t lds = p->lds_m[0];
-        switch (p->rxn.kind) {
-          case RXN_LINEAR: launch_xadj64<RXN_LINEAR>(p, grid, block, lds, a); break;
-          case RXN_FHN: launch_xadj64<RXN_FHN>(p, grid, block, lds, a); break;
-          case RXN_GRAY_SCOTT: launch_xadj64<RXN_GRAY_SCOTT>(p, grid, block, lds, a); break;
-          case RXN_SCHNAKENBERG: launch_xadj64<RXN_SCHNAKENBERG>(p, grid, block, lds, a); break;
-          default: launch_xadj64<RXN_GM>(p, grid, block, lds, a); break;
-        }
-        goto xadj_launched;
-      }
-    }
-    if (std::is_same<T, float>::value && fast && p->S == 1)
-      hipLaunchKernelGGL((k_xadj_m<T, XfX<T>, true, 1>), grid, block, p->lds_m[0], p->stream, a,
-                         p->mfax[0]);
-    else if (std::is_same<T, float>::value && fast && p->S == 2 && p->mfax[0].direct &&
-             !p->rp_acc)
-      // DCT-I / DST-I, no reaction-parameter partials: the input folded
-      // straight from registers
-      hipLaunchKernelGGL((k_xadj_m<T, XfX<T>, true, 2, true>), grid, block, p->lds_m[0], p->stream,
-                         a, p->mfax[0]);
-    else if (std::is_same<T, float>::value && fast && p->S == 2)
-      hipLaunchKernelGGL((k_xadj_m<T, XfX<T>, true, 2>), grid, block, p->lds_m[0], p->stream, a,
-                         p->mfax[0]);
-    else if (fast)
-      hipLaunchKernelGGL((k_xadj_m<T, XfX<T>, std::is_same<T, float>::value>), grid, block,
-                         p->lds_m[0], p->stream, a, p->mfax[0]);
-    else
-      hipLaunchKernelGGL((k_xadj_m<T, XfX<T>, false>), grid, block, p->lds_m[0], p->stream, a,
-                         p->mfax[0]);
-  xadj_launched:;
+  if (p->wcls[0] >= 0) {
+    TRY(launch_wave(p, 0, a.rp_acc ? WK_XADJ + 1 : WK_XADJ, a));
   } else if (p->use_f[0]) {
     hipLaunchKernelGGL((k_xadj<T, FftXf, true>), dim3((unsigned)a.g.ntiles, p->B), dim3(p->thr_f[0]),
                        p->lds_f[0], p->stream, a);
@@ -1140,50 +994,17 @@ int launch_zadj(sfrde_plan_s* p, int mode, const StepStore<T>* st, int last) {
   }
   if (!p->G) a.dcoef = nullptr;
   const long long pk = prof_start(p, KC_ZADJ);
-  if (p->use_m[ax]) {
-    const dim3 grid(p->grid_m[ax], p->B), block(XfZ<T>::THREADS);
-    const size_t lds = p->lds_m[ax];
-    const bool fast = use_fast<T>(p, ax, {p->Pa});
-    // per-stage kernels: L formed in the kernel, no per-point accumulator
-    const bool staged = fast && p->lfly && (p->thp_on || !p->G) && mode >= 0 && mode <= MODE_INIT;
-    if constexpr (std::is_same<T, float>::value) {
-      if (staged) {
-        // the instance with or without the kappa/alpha partials
-        const MfmaAxisDev& mx = p->mfax[ax];
-        hipStream_t sm = p->stream;
-        if (p->thp_on) {
-          switch (mode) {
-            case 0: hipLaunchKernelGGL((k_zadj_m<T, XfZ<T>, true, 0, 1>), grid, block, lds, sm, a, mx); break;
-            case 1: hipLaunchKernelGGL((k_zadj_m<T, XfZ<T>, true, 1, 1>), grid, block, lds, sm, a, mx); break;
-            case 2: hipLaunchKernelGGL((k_zadj_m<T, XfZ<T>, true, 2, 1>), grid, block, lds, sm, a, mx); break;
-            case 3: hipLaunchKernelGGL((k_zadj_m<T, XfZ<T>, true, 3, 1>), grid, block, lds, sm, a, mx); break;
-            default: hipLaunchKernelGGL((k_zadj_m<T, XfZ<T>, true, MODE_INIT, 1>), grid, block, lds, sm, a, mx); break;
-          }
-        } else {
-          switch (mode) {
-            case 0: hipLaunchKernelGGL((k_zadj_m<T, XfZ<T>, true, 0, 0>), grid, block, lds, sm, a, mx); break;
-            case 1: hipLaunchKernelGGL((k_zadj_m<T, XfZ<T>, true, 1, 0>), grid, block, lds, sm, a, mx); break;
-            case 2: hipLaunchKernelGGL((k_zadj_m<T, XfZ<T>, true, 2, 0>), grid, block, lds, sm, a, mx); break;
-            case 3: hipLaunchKernelGGL((k_zadj_m<T, XfZ<T>, true, 3, 0>), grid, block, lds, sm, a, mx); break;
-            default: hipLaunchKernelGGL((k_zadj_m<T, XfZ<T>, true, MODE_INIT, 0>), grid, block, lds, sm, a, mx); break;
-          }
-        }
-        goto zadj_launched;
-      }
-    }
-    if (fast)
-      hipLaunchKernelGGL((k_zadj_m<T, XfZ<T>, std::is_same<T, float>::value>), grid, block,
-                         p->lds_m[ax], p->stream, a, p->mfax[ax]);
-    else
-      hipLaunchKernelGGL((k_zadj_m<T, XfZ<T>, false>), grid, block, p->lds_m[ax], p->stream, a,
-                         p->mfax[ax]);
+  if (p->wcls[ax] >= 0) {
+    // L formed in the kernel (no per-point accumulator), else from tables
+    const bool fly = p->lfly && (p->thp_on || !p->G);
+    const int k = !fly ? WK_ZADJ : (p->thp_on && mode <= 2 ? WK_ZADJTH : WK_ZADJFLY) + mode;
+    TRY(launch_wave(p, ax, k, a));
   } else if (p->use_f[ax]) {
     hipLaunchKernelGGL((k_zadj<T, FftXf, true>), dim3((unsigned)a.g.ntiles, p->B), dim3(p->thr_f[ax]),
                        p->lds_f[ax], p->stream, a);
   } else
     hipLaunchKernelGGL(k_zadj<T>, dim3((unsigned)a.g.ntiles, p->B), dim3(NTHREADS),
                        p->lds[ax], p->stream, a);
-zadj_launched:
   prof_stop(p, pk);
   HIPCHECK(hipGetLastError());
   return SFRDE_OK;
@@ -1243,8 +1064,18 @@ int coef_tables(sfrde_plan_s* p, int deriv, void* out) {
 
 // Blocks of the adjoint X kernel (each owns one accumulator per parameter).
 long long rp_blocks(const sfrde_plan_s* p) {
-  return p->use_m[0] ? (long long)p->grid_m[0]
-                      : p->use_f[0] ? p->geom_f[0].ntiles : p->geom[0].ntiles;
+  if (p->wcls[0] < 0) return p->use_f[0] ? p->geom_f[0].ntiles : p->geom[0].ntiles;
+  unsigned g = 1;
+  (void)wave_blocks(p, 0, WK_XADJ + 1, &g);  // (the class is known since the plan was made)
+  return g;
+}
+
+// Row length of the kappa/alpha partials (the blocks of the adjoint Z kernels
+// that add to them).
+long long thp_blocks(const sfrde_plan_s* p) {
+  unsigned g = 1;
+  (void)wave_blocks(p, p->ndim - 1, WK_ZADJTH, &g);
+  return g;
 }
 
 // Bytes of the backward buffers (what ensure_backward_buffers allocates),
@@ -1276,7 +1107,7 @@ int carve_backward_buffers(sfrde_plan_s* p, long long seg_steps, bool want_theta
   p->rp_acc = nullptr;
   bool fill_dcoef = false;
   if (want_theta && p->thp_on) {
-    take((void**)&p->thp, (size_t)4 * p->grid_m[p->ndim - 1] * sizeof(double));
+    take((void**)&p->thp, (size_t)4 * thp_blocks(p) * sizeof(double));
   } else if (want_theta) {
     take((void**)&p->G, field_elems(p) * sizeof(double));
     // FP64 P13 plans form the coefficient derivatives from L in the combine
@@ -1317,7 +1148,7 @@ int ensure_backward_buffers(sfrde_plan_s* p, long long seg_steps, bool want_thet
   }
   p->seg_steps = seg_steps;
   if (want_theta && p->thp_on) {
-    TRY(dev_alloc(p, (void**)&p->thp, (size_t)4 * p->grid_m[p->ndim - 1] * sizeof(double)));
+    TRY(dev_alloc(p, (void**)&p->thp, (size_t)4 * thp_blocks(p) * sizeof(double)));
   } else if (want_theta) {
     TRY(dev_alloc(p, (void**)&p->G, field_elems(p) * sizeof(double)));
     // FP64 P13 plans form the coefficient derivatives from L in the combine
@@ -1350,7 +1181,7 @@ int backward_t(sfrde_plan_s* p, const void* ckpt, long long nsteps, long long K,
   p->seg_stride = want_theta ? 9 : 4;
   // kappa/alpha gradients formed inside the vector adjoint Z kernels (L
   // formed there too), else through the per-point accumulator G
-  p->thp_on = want_theta && p->lfly && p->B == 1 && p->S <= 2 && use_fast<T>(p, p->ndim - 1, {});
+  p->thp_on = want_theta && p->lfly && p->S <= 2;
   {
     const int rc0 = ensure_backward_buffers(p, seg_steps, want_theta, want_p);
     if (rc0 != SFRDE_OK) {
@@ -1362,7 +1193,7 @@ int backward_t(sfrde_plan_s* p, const void* ckpt, long long nsteps, long long K,
   double* G_saved = p->G;
   if (!want_theta || p->thp_on) p->G = nullptr;
   if (p->G) TRY(fill<double>(p, p->G, (long long)field_elems(p), 0.0));
-  const long long zgrid = p->grid_m[p->ndim - 1];
+  const long long zgrid = p->thp_on ? thp_blocks(p) : 0;
   if (p->thp_on) TRY(fill<double>(p, p->thp, 4 * zgrid, 0.0));
   double* rp_saved = p->rp_acc;
   if (!want_p) p->rp_acc = nullptr;
@@ -1469,8 +1300,8 @@ void destroy_plan(sfrde_plan_s* p) {
   void** ptrs[] = {&p->Mt[0], &p->Mt[1], &p->Mt[2], (void**)&p->lam[0], (void**)&p->lam[1],
                    (void**)&p->lam[2], &p->coef, &p->dcoef, &p->ltab, &p->P, &p->uhat, &p->ctil, &p->acc,
                    &p->Pa, &p->zh, &p->aacc, &p->ahat, &p->gu, (void**)&p->G, &p->seg,
-                   (void**)&p->rp_acc, (void**)&p->thp, (void**)&p->red, (void**)&p->flag, (void**)&p->rxm, &p->tw[0], &p->tw[1], &p->tw[2], &p->mf_A[0],
-                   &p->mf_A[1], &p->mf_A[2]};
+                   (void**)&p->rp_acc, (void**)&p->thp, (void**)&p->red, (void**)&p->flag, (void**)&p->rxm, &p->tw[0], &p->tw[1], &p->tw[2],
+                   &p->wA[0], &p->wA[1], &p->wA[2]};
   for (void** q : ptrs) {
     if (*q) (void)hipFree(*q);
     *q = nullptr;
@@ -1548,11 +1379,10 @@ int build_plan(sfrde_plan_s* p) {
     TRY(dev_alloc(p, (void**)&p->lam[a], lam.size() * sizeof(double)));
     HIPCHECK(hipMemcpy(p->lam[a], lam.data(), lam.size() * sizeof(double), hipMemcpyHostToDevice));
   }
-  size_t lds_max = 0;
   // dense tiles narrowed until the launch (all members) fills the device
   for (int a = 0; a < p->ndim; ++a)
     make_geom(p, a, std::max<long long>(1, (2LL * p->n_cu + p->B - 1) / p->B));
-  for (int a = 0; a < p->ndim; ++a) TRY(setup_mfma_axis(p, a));
+  for (int a = 0; a < p->ndim; ++a) TRY(setup_wave_axis(p, a));
   // Long periodic axes of 256, 512 or 1024 points: FFT kernels. Any other
   // axis the matrix-core engine does not take (n > 256, other periodic
   // n >= 256, the one-point padding axis of 1D plans) runs the dense LDS
@@ -1562,7 +1392,7 @@ int build_plan(sfrde_plan_s* p) {
       TRY(setup_fft_axis<float>(p, a));
     else
       TRY(setup_fft_axis<double>(p, a));
-    if (!p->use_m[a] && !p->use_f[a]) {
+    if (p->wcls[a] < 0 && !p->use_f[a]) {
       if (p->dtype == SFRDE_F32)
         TRY(upload_matrix<float>(p, a));
       else
@@ -1570,27 +1400,14 @@ int build_plan(sfrde_plan_s* p) {
     }
   }
   {
-    // FP32 P13 plans whose last axis runs the vector Z kernels form L there
-    // from the eigenvalue tables (kept in LDS as floats) instead of reading
-    // an L table.
+    // FP32 P13 plans form L in the Z kernels from the eigenvalue tables
+    // instead of reading an L table where the last axis has 64, 128, 192 or
+    // 256 points and its columns come in whole tiles of 32; other grids read
+    // the table (rounded from FP64 L, and no slower on the sizes they have).
     const int za = p->ndim - 1;
-    long long nsum = 0;
-    for (int a = 0; a < p->ndim; ++a) nsum += p->n[a];
-    const size_t extra = (size_t)nsum * sizeof(float);
-    if (p->dtype == SFRDE_F32 && p->scheme == SFRDE_SCHEME_P13 && p->B == 1 &&
-        p->use_m[za] &&
-        p->geom_m[za].fast && p->n[0] % 4 == 0 && p->lds_m[za] + extra <= 160 * 1024) {
-      p->lfly = true;
-      p->lam_off = (p->lds_m[za] + 15) / 16 * 16;
-      p->lds_m[za] = p->lam_off + extra;
-    }
-  }
-  for (int a = 0; a < p->ndim; ++a) lds_max = std::max(lds_max, p->lds_m[a]);
-  if (lds_max > 0) {
-    if (p->dtype == SFRDE_F32)
-      TRY(set_lds_attrs<float>(lds_max));
-    else
-      TRY(set_lds_attrs<double>(lds_max));
+    const long long inner = za == 2 ? p->n[0] * p->n[1] : p->n[0];
+    p->lfly = p->dtype == SFRDE_F32 && p->scheme == SFRDE_SCHEME_P13 && p->B == 1 &&
+              p->wcls[za] >= 0 && p->n[za] % 64 == 0 && inner % 32 == 0 && p->n[0] % 4 == 0;
   }
   const size_t f = field_bytes(p);
   TRY(dev_alloc(p, &p->coef, NCOEF * f));
