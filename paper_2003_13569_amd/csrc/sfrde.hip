@@ -406,9 +406,16 @@ int wave_class_of(int dtype, int bc, long long n, bool source) {
   if (!per && !source && n == 256) return f32 ? WC_F32_8X : WC_F64_8X;
   if (half <= 32) return c2 + lay;
   if (half <= 64) return c4 + lay;
-  if (f32) return half <= 128 ? WC_F32_8X + lay : -1;
-  if (odd) return half <= 128 ? WC_F64_8O : -1;
-  return half <= 144 ? WC_F64_9E : -1;
+  if (f32 && half <= 128) return WC_F32_8X + lay;
+  // periodic axes of 256 and 512 points run as FFTs: 256^2 FP64 102 us per step
+  // against 196 (FP32 equal), 512^2 FP32 153 against 152 for the products
+  if (per && (n == 256 || n == 512)) return -1;
+  if (!f32 && half <= (odd ? 128 : 144)) return odd ? WC_F64_8O : WC_F64_9E;
+  // to 512 points on the group kernels (the dense kernels / these, per step:
+  // 300 x 333 FP32 6280 / 117 us, 390 x 280 FP64 7257 / 313, 512^2 Dirichlet
+  // FP32 10983 / 152); beyond, the matrix of an axis leaves the caches
+  if (half > 256) return -1;
+  return (f32 ? WC_F32_16E : WC_F64_16E) + (odd ? 1 : 0);
 }
 
 // The engine's view of an axis: segments of pair positions (wave.h).
@@ -591,16 +598,24 @@ size_t wave_lds(const sfrde_plan_s* p, int axis, int kernel, const WaveKernels& 
 }
 
 // Whether an axis runs the group kernels (one tile per block, a wave per row
-// block): its tiles are at most one per CU.
-bool use_group(const sfrde_plan_s* p, int axis) {
-  return (long long)p->wtl[axis].ntiles * p->B <= (long long)p->n_cu;
+// block): at most GROUP_WAVES waves per CU in all, or no wave kernels. A group
+// kernel spends nb waves on the chain of one, and moves its operands through LDS:
+// it wins while the device is not full of chains. Step times, wave kernels /
+// groups up to 8 waves per CU: 64^2 FP64, 16 members 127 / 46 us, 64 157 / 70;
+// 256^2 FP64 257 / 134; 64^3 FP32 149 / 98. Limits of 4 / 8 / 16 waves: 256
+// members of 64^2 FP64 127 / 127 / 143, FP32 70 / 70 / 96; 48 x 80 FP32, 64
+// members 69 / 62 / 62; periodic 64^3 FP32 128 / 108 / 108.
+constexpr long long GROUP_WAVES = 8;
+bool use_group(const sfrde_plan_s* p, int axis, const WaveKernels& k) {
+  return !k.fn[WK_X] ||
+         (long long)p->wtl[axis].ntiles * p->B * k.nb <= GROUP_WAVES * p->n_cu;
 }
 
 // Blocks of a kernel's launch over an axis.
 int wave_blocks(const sfrde_plan_s* p, int axis, int kernel, unsigned* blocks) {
   const WaveClass* wc = nullptr;
   TRY(wave_class_info(p->wcls[axis], &wc));
-  if (use_group(p, axis)) {
+  if (use_group(p, axis, wc->k)) {
     *blocks = (unsigned)p->wtl[axis].ntiles;
     return SFRDE_OK;
   }
@@ -611,7 +626,7 @@ template <class Args>
 int launch_wave(sfrde_plan_s* p, int axis, int kernel, Args& a) {
   const WaveClass* wc = nullptr;
   TRY(wave_class_info(p->wcls[axis], &wc));
-  if (kernel != WK_SY2 && use_group(p, axis)) {
+  if (kernel != WK_SY2 && use_group(p, axis, wc->k)) {
     void* args[] = {&a, &p->wax[axis], &p->wtl[axis]};
     HIPCHECK(hipLaunchKernel(wc->k.grp[kernel],
                              dim3((unsigned)p->wtl[axis].ntiles, (unsigned)p->B),
@@ -738,7 +753,8 @@ int launch_single(sfrde_plan_s* p, int axis, const void* src, void* dst, int pre
     // two columns per lane where the tiles still give every CU four waves or
     // more (below that the shorter chain of one column wins)
     const bool two = p->dtype == SFRDE_F32 && p->wtl[axis].inner % 2 == 0 &&
-                     p->wtl[axis].lines / 32 * p->B >= 4LL * p->n_cu;
+                     p->wtl[axis].lines / 32 * p->B >= 4LL * p->n_cu &&
+                     p->n[axis] <= 256;
     TRY(launch_wave(p, axis, axis == 0 ? WK_SX : two ? WK_SY2 : WK_SY, a));
   } else if (p->use_f[axis]) {
     hipLaunchKernelGGL((k_single<T, FftXf, true>), dim3((unsigned)a.g.ntiles, p->B),
@@ -1407,7 +1423,7 @@ int build_plan(sfrde_plan_s* p) {
     const int za = p->ndim - 1;
     const long long inner = za == 2 ? p->n[0] * p->n[1] : p->n[0];
     p->lfly = p->dtype == SFRDE_F32 && p->scheme == SFRDE_SCHEME_P13 && p->B == 1 &&
-              p->wcls[za] >= 0 && p->n[za] % 64 == 0 && inner % 32 == 0 && p->n[0] % 4 == 0;
+              p->wcls[za] >= 0 && p->n[za] % 64 == 0 && p->n[za] <= 256 && inner % 32 == 0 && p->n[0] % 4 == 0;
   }
   const size_t f = field_bytes(p);
   TRY(dev_alloc(p, &p->coef, NCOEF * f));

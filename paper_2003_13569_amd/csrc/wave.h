@@ -1894,15 +1894,15 @@ struct GroupXf : WaveXf<T, NB, LAY> {
   struct Rows64 {
     T a[KS];
   };
-  // FP64 axes past 128 points: read during the product (the four sides' rows
-  // do not fit; three waves per SIMD cover the reads)
-  static constexpr bool STREAM = !F32 && NB > 4;
+  // FP64 axes past 128 points, FP32 past 256: read during the product (the
+  // rows of four sides do not fit; three or four waves per SIMD cover the reads)
+  static constexpr bool STREAM = F32 ? NB > 8 : NB > 4;
   struct RowsAt {
     int half;
     unsigned lo;
   };
   using Rows = typename std::conditional<
-      F32, Rows32, typename std::conditional<STREAM, RowsAt, Rows64>::type>::type;
+      STREAM, RowsAt, typename std::conditional<F32, Rows32, Rows64>::type>::type;
   int rb;
   bool on;
   int lane;
@@ -1916,16 +1916,16 @@ struct GroupXf : WaveXf<T, NB, LAY> {
   }
   __device__ __forceinline__ void rows_of(int half, unsigned lo, Rows& m) const {
     const char* p = this->tab + lo;
-    if constexpr (F32) {
+    if constexpr (STREAM) {
+      m.half = half;
+      m.lo = lo;
+    } else if constexpr (F32) {
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
         for (int t = 0; t < 2; ++t)
           m.a[ks][t] = *reinterpret_cast<const f16x8*>(
               p + (size_t)((half * 2 + t) * KS + ks) * 4 * RS * UB);
-    } else if constexpr (STREAM) {
-      m.half = half;
-      m.lo = lo;
     } else {
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks)
@@ -2004,6 +2004,13 @@ struct GroupXf : WaveXf<T, NB, LAY> {
       return 1.f;
     }
   }
+  __device__ __forceinline__ f16x8 row32(const Rows& m, int ks, int t) const {
+    if constexpr (STREAM)
+      return *reinterpret_cast<const f16x8*>(
+          this->tab + m.lo + (size_t)((m.half * 2 + t) * KS + ks) * 4 * RS * UB);
+    else
+      return m.a[ks][t];
+  }
   // One row block times the shared columns of half `half`.
   template <bool SWAP>
   __device__ __forceinline__ void mul_shared(const char* smem, int b, int half, const Rows& m,
@@ -2016,14 +2023,15 @@ struct GroupXf : WaveXf<T, NB, LAY> {
       for (int ks = 0; ks < KS; ++ks) {
         const f16x8 b0 = *reinterpret_cast<const f16x8*>(p + (size_t)ks * 2048);
         const f16x8 b1 = *reinterpret_cast<const f16x8*>(p + (size_t)ks * 2048 + 1024);
+        const f16x8 a0 = row32(m, ks, 0), a1 = row32(m, ks, 1);
         if constexpr (SWAP) {
-          hi = __builtin_amdgcn_mfma_f32_16x16x32_f16(b0, m.a[ks][0], hi, 0, 0, 0);
-          lo4 = __builtin_amdgcn_mfma_f32_16x16x32_f16(b0, m.a[ks][1], lo4, 0, 0, 0);
-          lo4 = __builtin_amdgcn_mfma_f32_16x16x32_f16(b1, m.a[ks][0], lo4, 0, 0, 0);
+          hi = __builtin_amdgcn_mfma_f32_16x16x32_f16(b0, a0, hi, 0, 0, 0);
+          lo4 = __builtin_amdgcn_mfma_f32_16x16x32_f16(b0, a1, lo4, 0, 0, 0);
+          lo4 = __builtin_amdgcn_mfma_f32_16x16x32_f16(b1, a0, lo4, 0, 0, 0);
         } else {
-          hi = __builtin_amdgcn_mfma_f32_16x16x32_f16(m.a[ks][0], b0, hi, 0, 0, 0);
-          lo4 = __builtin_amdgcn_mfma_f32_16x16x32_f16(m.a[ks][1], b0, lo4, 0, 0, 0);
-          lo4 = __builtin_amdgcn_mfma_f32_16x16x32_f16(m.a[ks][0], b1, lo4, 0, 0, 0);
+          hi = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, b0, hi, 0, 0, 0);
+          lo4 = __builtin_amdgcn_mfma_f32_16x16x32_f16(a1, b0, lo4, 0, 0, 0);
+          lo4 = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, b1, lo4, 0, 0, 0);
         }
       }
 #pragma unroll
@@ -2425,29 +2433,30 @@ struct WaveKernels {
   size_t lds_g;             // LDS of the group kernels
 };
 
-template <typename T, int NB, int LAY, int MODE = 3>
+template <typename T, int NB, int LAY, bool FN, int MODE = 3>
 void wave_z_kernels(WaveKernels& k) {
-  k.fn[WK_Z + MODE] = reinterpret_cast<const void*>(&k_wz<T, NB, LAY, MODE, false>);
-  if constexpr (LAY != WL_ODD && sizeof(T) == 4)
-    k.fn[WK_ZFLY + MODE] = reinterpret_cast<const void*>(&k_wz<T, NB, LAY, MODE, true>);
+  constexpr bool FLY = LAY != WL_ODD && sizeof(T) == 4 && FN;
   k.grp[WK_Z + MODE] = reinterpret_cast<const void*>(&k_gz<T, NB, LAY, MODE, false>);
-  if constexpr (LAY != WL_ODD && sizeof(T) == 4)
-    k.grp[WK_ZFLY + MODE] = reinterpret_cast<const void*>(&k_gz<T, NB, LAY, MODE, true>);
-  if constexpr (MODE > 0) wave_z_kernels<T, NB, LAY, MODE - 1>(k);
+  if constexpr (FLY) k.grp[WK_ZFLY + MODE] = reinterpret_cast<const void*>(&k_gz<T, NB, LAY, MODE, true>);
+  if constexpr (FN) k.fn[WK_Z + MODE] = reinterpret_cast<const void*>(&k_wz<T, NB, LAY, MODE, false>);
+  if constexpr (FLY) k.fn[WK_ZFLY + MODE] = reinterpret_cast<const void*>(&k_wz<T, NB, LAY, MODE, true>);
+  if constexpr (MODE > 0) wave_z_kernels<T, NB, LAY, FN, MODE - 1>(k);
 }
 
 template <typename T, int NB, int LAY, int MODE = MODE_INIT>
 void wave_zadj_kernels(WaveKernels& k) {
   k.fn[WK_ZADJFLY + MODE] = reinterpret_cast<const void*>(&k_wzadj<T, NB, LAY, MODE, false>);
-  if constexpr (MODE <= 2)
-    k.fn[WK_ZADJTH + MODE] = reinterpret_cast<const void*>(&k_wzadj<T, NB, LAY, MODE, true>);
   k.grp[WK_ZADJFLY + MODE] = reinterpret_cast<const void*>(&k_gzadj<T, NB, LAY, MODE, false>);
-  if constexpr (MODE <= 2)
+  if constexpr (MODE <= 2) {
+    k.fn[WK_ZADJTH + MODE] = reinterpret_cast<const void*>(&k_wzadj<T, NB, LAY, MODE, true>);
     k.grp[WK_ZADJTH + MODE] = reinterpret_cast<const void*>(&k_gzadj<T, NB, LAY, MODE, true>);
+  }
   if constexpr (MODE > 0) wave_zadj_kernels<T, NB, LAY, MODE - 1>(k);
 }
 
-template <typename T, int NB, int LAY>
+// FN: with the wave kernels; classes past 288 points have the group kernels
+// only (a wave cannot hold 16 of their lines).
+template <typename T, int NB, int LAY, bool FN = (NB <= 9)>
 WaveKernels wave_kernels() {
   WaveKernels k{};
   k.nb = NB;
@@ -2455,14 +2464,6 @@ WaveKernels wave_kernels() {
   k.threads = wave_threads<T, NB>();
   k.tab_bytes = WaveTab<T, NB>::bytes;
   k.lds_a = wave_lds_a<T, NB>() ? WaveTab<T, NB>::bytes : 0;
-  k.fn[WK_X] = reinterpret_cast<const void*>(&k_wx<T, NB, LAY, false>);
-  if constexpr (LAY != WL_EXACT)
-    k.fn[WK_XSRC] = reinterpret_cast<const void*>(&k_wx<T, NB, LAY, true>);
-  k.fn[WK_SX] = reinterpret_cast<const void*>(&k_wsx<T, NB, LAY>);
-  k.fn[WK_SY] = reinterpret_cast<const void*>(&k_wsy<T, NB, LAY>);
-  if constexpr (sizeof(T) == 4)
-    k.fn[WK_SY2] = reinterpret_cast<const void*>(&k_wsy2<NB, LAY>);
-  k.fn[WK_ZINIT] = reinterpret_cast<const void*>(&k_wz<T, NB, LAY, -1, false>);
   k.lds_g = GroupXf<T, NB, LAY>::lds_bytes();
   k.grp[WK_X] = reinterpret_cast<const void*>(&k_gx<T, NB, LAY, false>);
   if constexpr (LAY != WL_EXACT)
@@ -2473,11 +2474,20 @@ WaveKernels wave_kernels() {
   k.grp[WK_XADJ] = reinterpret_cast<const void*>(&k_gxadj<T, NB, LAY, false>);
   k.grp[WK_XADJ + 1] = reinterpret_cast<const void*>(&k_gxadj<T, NB, LAY, true>);
   k.grp[WK_ZADJ] = reinterpret_cast<const void*>(&k_gzadj<T, NB, LAY, -1, false>);
-  wave_z_kernels<T, NB, LAY>(k);
-  k.fn[WK_XADJ] = reinterpret_cast<const void*>(&k_wxadj<T, NB, LAY, false>);
-  k.fn[WK_XADJ + 1] = reinterpret_cast<const void*>(&k_wxadj<T, NB, LAY, true>);
-  k.fn[WK_ZADJ] = reinterpret_cast<const void*>(&k_wzadj<T, NB, LAY, -1, false>);
-  if constexpr (LAY != WL_ODD && sizeof(T) == 4) wave_zadj_kernels<T, NB, LAY>(k);
+  wave_z_kernels<T, NB, LAY, FN>(k);
+  if constexpr (FN) {
+    k.fn[WK_X] = reinterpret_cast<const void*>(&k_wx<T, NB, LAY, false>);
+    if constexpr (LAY != WL_EXACT)
+      k.fn[WK_XSRC] = reinterpret_cast<const void*>(&k_wx<T, NB, LAY, true>);
+    k.fn[WK_SX] = reinterpret_cast<const void*>(&k_wsx<T, NB, LAY>);
+    k.fn[WK_SY] = reinterpret_cast<const void*>(&k_wsy<T, NB, LAY>);
+    if constexpr (sizeof(T) == 4) k.fn[WK_SY2] = reinterpret_cast<const void*>(&k_wsy2<NB, LAY>);
+    k.fn[WK_ZINIT] = reinterpret_cast<const void*>(&k_wz<T, NB, LAY, -1, false>);
+    k.fn[WK_XADJ] = reinterpret_cast<const void*>(&k_wxadj<T, NB, LAY, false>);
+    k.fn[WK_XADJ + 1] = reinterpret_cast<const void*>(&k_wxadj<T, NB, LAY, true>);
+    k.fn[WK_ZADJ] = reinterpret_cast<const void*>(&k_wzadj<T, NB, LAY, -1, false>);
+    if constexpr (LAY != WL_ODD && sizeof(T) == 4) wave_zadj_kernels<T, NB, LAY>(k);
+  }
   return k;
 }
 

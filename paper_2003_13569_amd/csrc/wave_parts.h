@@ -12,7 +12,7 @@ enum {
   WC_F32_2X, WC_F32_2E, WC_F32_2O, WC_F32_4X, WC_F32_4E, WC_F32_4O,
   WC_F32_8X, WC_F32_8E, WC_F32_8O, WC_F64_2X, WC_F64_2E, WC_F64_2O,
   WC_F64_4X, WC_F64_4E, WC_F64_4O, WC_F64_8X, WC_F64_8O, WC_F64_9E,
-  WC_F32_6X,
+  WC_F32_6X, WC_F32_16E, WC_F32_16O, WC_F64_16E, WC_F64_16O,
   WC_COUNT
 };
 
@@ -87,6 +87,18 @@ SFRDE_WAVE_CLASS(WC_F64_9E, double, 9, WL_EVEN)
 #endif
 #if SFRDE_HAS(18)
 SFRDE_WAVE_CLASS(WC_F32_6X, float, 6, WL_EXACT)
+#endif
+#if SFRDE_HAS(19)
+SFRDE_WAVE_CLASS(WC_F32_16E, float, 16, WL_EVEN)
+#endif
+#if SFRDE_HAS(20)
+SFRDE_WAVE_CLASS(WC_F32_16O, float, 16, WL_ODD)
+#endif
+#if SFRDE_HAS(21)
+SFRDE_WAVE_CLASS(WC_F64_16E, double, 16, WL_EVEN)
+#endif
+#if SFRDE_HAS(22)
+SFRDE_WAVE_CLASS(WC_F64_16O, double, 16, WL_ODD)
 #endif
 #undef SFRDE_HAS
 #undef SFRDE_WAVE_CLASS
