@@ -1,11 +1,11 @@
-// Hartley transforms of long periodic axes (N = 256, 512, 1024 points) as
-// radix-8/4 complex FFTs in LDS.
+// Hartley transforms of periodic axes of N = 256, 512 and 1024 points as
+// radix-8/4 complex FFTs, one pair of lines per wavefront.
 //
 // The periodic operator's eigenvalues satisfy lambda_k = lambda_{N-k}
 // (Section 3.1), so the real Hartley basis cas(2 pi jk/N) = cos + sin
 // diagonalises it like the complex Fourier basis of Alg. 1's fftn. Two real
-// lines a, b of a tile are transformed together as one complex sequence
-// z = a + i b: with Z = DFT(z) and Z'_k = Z_{(N-k) mod N},
+// lines a, b are transformed together as one complex sequence z = a + i b:
+// with Z = DFT(z) and Z'_k = Z_{(N-k) mod N},
 //   H(a)_k = (Re Z_k + Re Z'_k - Im Z_k + Im Z'_k) / 2
 //   H(b)_k = (Re Z_k - Re Z'_k + Im Z_k + Im Z'_k) / 2
 // (Re and Im of the DFT of a real line are its cosine sum and minus its sine
@@ -16,21 +16,32 @@
 // The complex DFT is a Stockham autosort FFT (no bit reversal): stage by
 // stage, butterfly j of span Ns reads x[j + r N/R], r < R, multiplies input r
 // by e^{-2 pi i r k / (Ns R)} with k = j mod Ns, takes the radix-R DFT, and
-// writes x[(j - k) R + k + r Ns]. One wavefront runs one pair of lines; its
-// 64 lanes take butterflies lane, lane + 64, ... of every stage. Each stage
-// reads all of its inputs before any output is written, so a single buffer of
-// N complex values per wavefront suffices. Twiddles (cos, sin of 2 pi m / N)
-// come from a table built in FP64 on the host.
+// writes x[(j - k) R + k + r Ns]. Lane l of the wavefront holds the points
+// l + 64 e of its two lines in registers. That is exactly what its butterflies
+// l, l + 64, ... of any stage read, so a stage is register work and one
+// exchange through the wavefront's own LDS (written in the stage's output
+// order, read back at l + 64 e). Nothing is shared between wavefronts: there
+// is no barrier, and the launch can be cut into blocks of any size.
+//
+// On the x axis of two-species plans the two lines are the two species of one
+// row, so the reaction is lane-local between the inverse and the forward
+// transform; on strided axes they are adjacent columns. Twiddles (cos, sin of
+// 2 pi m / N) come from a table built in FP64 on the host.
+//
+// A launch of 512^2 points is bound by the length of one wavefront's chain
+// (512 wavefronts on 256 CUs). 512^2 Gray-Scott, FP32, per launch, against
+// blocks of 256 threads with the tile in LDS, two of four wavefronts in the FFT
+// and block barriers between stages: X 14.4 -> 6.1 us, Z 22.4 -> 12.6 us; a step
+// 155 -> 76 us (FP64 168 -> 94); 1024^2 363 -> 256 (FP64 416 -> 283); 256^3
+// 6.99 -> 4.02 ms (FP64 8.80 -> 4.84).
 #pragma once
 
 #include <hip/hip_runtime.h>
 
 #include "kernels.h"
+#include "wave.h"
 
 namespace sfrde {
-
-constexpr int FFT_MIN_N = 256;
-constexpr int FFT_MAX_N = 1024;
 
 // Radix-R DFT (e^{-2 pi i rk/R}) of v in place, R = 4 or 8.
 template <typename T>
@@ -79,130 +90,597 @@ __device__ __forceinline__ void dft_r(T (&vr)[R], T (&vi)[R]) {
   }
 }
 
-// One Stockham stage of radix R and span NS on the wavefront's buffer
-// (xr, xi) of N points. Block-wide barriers: every wavefront of the block
-// runs the same stages; wavefronts without a line pair (`on` false) only
-// take part in the barriers.
-template <typename T, int N, int R, int NS>
-__device__ __forceinline__ void fft_stage(T* xr, T* xi, const T* __restrict__ tw, int lane,
-                                          bool on) {
-  constexpr int NB = N / R;  // butterflies
-  constexpr int B = NB / 64;  // per lane
-  static_assert(B >= 1 && NB % 64 == 0, "at least one butterfly per lane");
-  T vr[B][R], vi[B][R];
-  if (on) {
-#pragma unroll
-    for (int b = 0; b < B; ++b) {
-      const int j = lane + 64 * b;
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        vr[b][r] = xr[j + r * NB];
-        vi[b][r] = xi[j + r * NB];
-      }
+// One pair of lines in registers: lane l holds points l + 64 e.
+template <typename T, int N>
+struct WaveFft {
+  static constexpr int E = N / 64;
+  using Vals = T[E];
+  // LDS of one wavefront: real and imaginary parts, one spare word after every
+  // eight (the strides of a stage's writes then spread over the banks)
+  static constexpr int PART = N + N / 8;
+  static constexpr size_t lds_bytes() { return (size_t)2 * PART * sizeof(T); }
+  T *xr, *xi;
+  int lane;
+  // this lane's twiddles, read once for both transforms of a launch
+  static constexpr int NTW = N == 256 ? 9 : N == 512 ? 14 : 22;
+  T wc[NTW], ws[NTW];
+  // tw: [N][2] cos, sin of 2 pi m / N
+  __device__ __forceinline__ WaveFft(char* smem, const T* tw) {
+    lane = threadIdx.x & 63;
+    xr = reinterpret_cast<T*>(smem + (size_t)(threadIdx.x >> 6) * lds_bytes());
+    xi = xr + PART;
+    if constexpr (N == 256) {
+      twiddles<4, 4, 0>(tw);
+      twiddles<4, 16, 3>(tw);
+      twiddles<4, 64, 6>(tw);
+    } else if constexpr (N == 512) {
+      twiddles<8, 8, 0>(tw);
+      twiddles<8, 64, 7>(tw);
+    } else {
+      static_assert(N == 1024, "N = 256, 512 or 1024");
+      twiddles<8, 8, 0>(tw);
+      twiddles<4, 64, 7>(tw);
+      twiddles<4, 256, 10>(tw);
     }
   }
-  __syncthreads();
-  if (on) {
+  // Distinct twiddle sets of a lane's butterflies lane + 64 b in a stage of
+  // span NS (k = butterfly mod NS).
+  template <int NS>
+  static constexpr int sets() { return NS > 64 ? NS / 64 : 1; }
+  template <int R, int NS, int W0>
+  __device__ __forceinline__ void twiddles(const T* tw) {
+#pragma unroll
+    for (int b = 0; b < sets<NS>(); ++b)
+#pragma unroll
+      for (int r = 1; r < R; ++r) {
+        const int m = r * ((lane + 64 * b) & (NS - 1)) * (N / (NS * R));  // < N
+        wc[W0 + b * (R - 1) + r - 1] = tw[2 * m];
+        ws[W0 + b * (R - 1) + r - 1] = tw[2 * m + 1];
+      }
+  }
+  __device__ __forceinline__ static int at(int i) { return i + (i >> 3); }
+  // The wavefront's LDS accesses complete in order; this keeps the compiler's
+  // order, too.
+  __device__ __forceinline__ static void sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+  template <int R, int NS, int W0 = 0>
+  __device__ __forceinline__ void stage(Vals& vr, Vals& vi) const {
+    constexpr int NB = N / R, B = NB / 64;
 #pragma unroll
     for (int b = 0; b < B; ++b) {
-      const int j = lane + 64 * b;
-      const int k = j & (NS - 1);
+      const int j = lane + 64 * b, k = j & (NS - 1);
+      T br[R], bi[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        br[r] = vr[b + B * r];
+        bi[r] = vi[b + B * r];
+      }
       if constexpr (NS > 1) {
 #pragma unroll
         for (int r = 1; r < R; ++r) {
-          const int m = r * k * (N / (NS * R));  // < N
-          const T c = tw[2 * m], s = tw[2 * m + 1];
-          const T ar = vr[b][r], ai = vi[b][r];
-          vr[b][r] = ar * c + ai * s;  // times e^{-i theta}
-          vi[b][r] = ai * c - ar * s;
+          const int w = W0 + (b % sets<NS>()) * (R - 1) + r - 1;
+          const T c = wc[w], s = ws[w];
+          const T ar = br[r], ai = bi[r];
+          br[r] = ar * c + ai * s;  // times e^{-i theta}
+          bi[r] = ai * c - ar * s;
         }
       }
-      dft_r<T, R>(vr[b], vi[b]);
+      dft_r<T, R>(br, bi);
       const int base = (j - k) * R + k;
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        xr[base + r * NS] = vr[b][r];
-        xi[base + r * NS] = vi[b][r];
+        xr[at(base + r * NS)] = br[r];
+        xi[at(base + r * NS)] = bi[r];
       }
     }
+    sync();
   }
-  __syncthreads();
-}
-
-// Complex DFT of the wavefront's buffer, natural order in and out.
-template <typename T, int N>
-__device__ __forceinline__ void fft_wave(T* xr, T* xi, const T* __restrict__ tw, int lane,
-                                         bool on) {
-  if constexpr (N == 256) {
-    fft_stage<T, N, 4, 1>(xr, xi, tw, lane, on);
-    fft_stage<T, N, 4, 4>(xr, xi, tw, lane, on);
-    fft_stage<T, N, 4, 16>(xr, xi, tw, lane, on);
-    fft_stage<T, N, 4, 64>(xr, xi, tw, lane, on);
-  } else if constexpr (N == 512) {
-    fft_stage<T, N, 8, 1>(xr, xi, tw, lane, on);
-    fft_stage<T, N, 8, 8>(xr, xi, tw, lane, on);
-    fft_stage<T, N, 8, 64>(xr, xi, tw, lane, on);
-  } else {
-    static_assert(N == 1024, "N = 256, 512 or 1024");
-    fft_stage<T, N, 8, 1>(xr, xi, tw, lane, on);
-    fft_stage<T, N, 8, 8>(xr, xi, tw, lane, on);
-    fft_stage<T, N, 4, 64>(xr, xi, tw, lane, on);
-    fft_stage<T, N, 4, 256>(xr, xi, tw, lane, on);
+  __device__ __forceinline__ void read(Vals& vr, Vals& vi) const {
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      vr[e] = xr[at(lane + 64 * e)];
+      vi[e] = xi[at(lane + 64 * e)];
+    }
+    sync();
   }
-}
-
-// Lines per tile of an FFT axis and the LDS the kernels need: tiles hold W
-// lines of spt species (x axis: spt = S, W = 2 for S <= 2 else 1; strided
-// axes: spt = 1, W = 4), one wavefront per pair of the tile's spt * W lines;
-// the block has FFT_THREADS threads (at least one wavefront per pair), all of
-// which take part in the tile's loads, stores and pointwise stages.
-constexpr int FFT_THREADS = 256;
-__host__ __device__ constexpr int fft_pairs(int spt, int W) { return (spt * W + 1) / 2; }
-template <typename T>
-constexpr size_t fft_lds_bytes(int spt, int n, int W, int pitch) {
-  return ((size_t)spt * n * pitch + (size_t)fft_pairs(spt, W) * 2 * n) * sizeof(T);
-}
-
-// The transform functor of the tile kernels (kernels.h): Hartley transform of
-// every line of the tile buf[s][j][w], in place. Wavefront q < pairs runs the
-// pair of lines 2q, 2q + 1; the pair buffers follow the tile in LDS.
-template <typename T>
-struct FftXf {
-  const Geom* g;
-  const T* tw;  // [N][2] cos, sin of 2 pi m / N
-  __device__ __forceinline__ void operator()(T* buf, int S) {
-    const int n = g->n, W = g->W, pitch = g->pitch;
-    const int L = S * W;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const bool on = wave < fft_pairs(S, W);
-    const int l0 = 2 * wave, l1 = 2 * wave + 1;
-    const bool has1 = l1 < L;
-    T* xr = buf + (size_t)S * n * pitch + (size_t)(on ? wave : 0) * 2 * n;
-    T* xi = xr + n;
-    T* a = buf + (size_t)(l0 / W) * n * pitch + (l0 % W);
-    T* b = buf + (size_t)(l1 / W) * n * pitch + (l1 % W);
-    if (on) {
-      for (int j = lane; j < n; j += 64) {
-        xr[j] = a[j * pitch];
-        xi[j] = has1 ? b[j * pitch] : T(0);
-      }
+  // Hartley transforms of the lines in a and b, in place.
+  __device__ __forceinline__ void hartley(Vals& a, Vals& b) const {
+    if constexpr (N == 256) {
+      stage<4, 1>(a, b);
+      read(a, b);
+      stage<4, 4>(a, b);
+      read(a, b);
+      stage<4, 16, 3>(a, b);
+      read(a, b);
+      stage<4, 64, 6>(a, b);
+    } else if constexpr (N == 512) {
+      stage<8, 1>(a, b);
+      read(a, b);
+      stage<8, 8>(a, b);
+      read(a, b);
+      stage<8, 64, 7>(a, b);
+    } else {
+      stage<8, 1>(a, b);
+      read(a, b);
+      stage<8, 8>(a, b);
+      read(a, b);
+      stage<4, 64, 7>(a, b);
+      read(a, b);
+      stage<4, 256, 10>(a, b);
     }
-    __syncthreads();
-    switch (n) {
-      case 256: fft_wave<T, 256>(xr, xi, tw, lane, on); break;
-      case 512: fft_wave<T, 512>(xr, xi, tw, lane, on); break;
-      default: fft_wave<T, 1024>(xr, xi, tw, lane, on); break;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int k = lane + 64 * e, kk = (N - k) & (N - 1);
+      const T zr = xr[at(k)], zi = xi[at(k)], wr = xr[at(kk)], wi = xi[at(kk)];
+      a[e] = T(0.5) * ((zr + wr) - (zi - wi));
+      b[e] = T(0.5) * ((zr - wr) + (zi + wi));
     }
-    if (on) {
-      for (int k = lane; k < n; k += 64) {
-        const int kk = (n - k) & (n - 1);
-        const T zr = xr[k], zi = xi[k], wr = xr[kk], wi = xi[kk];
-        a[k * pitch] = T(0.5) * ((zr + wr) - (zi - wi));
-        if (has1) b[k * pitch] = T(0.5) * ((zr - wr) + (zi + wi));
-      }
-    }
-    __syncthreads();
+    sync();
   }
 };
+
+// Pairs of an axis: x axis: S = 1: lines 2q, 2q + 1; S >= 2: species 2h, 2h + 1
+// of line q / ((S + 1) / 2). Strided: columns 2q, 2q + 1 counted over every
+// outer block (species included). A last pair without a partner repeats its
+// line (and stores it twice).
+struct FftPairs {
+  long long lines;   // x: per species; strided: of every outer block
+  long long inner;   // strided
+  int npairs;
+};
+
+// The wavefront's pair, -1 past the last. Blocks are dealt to the XCDs in turn;
+// neighbouring pairs (which share cache lines on strided axes) go to one XCD.
+__device__ __forceinline__ int fft_pair(int npairs) {
+  const int nb = (int)gridDim.x, per = nb / 8;
+  const int b = (int)blockIdx.x;
+  const int g = b < 8 * per ? (b & 7) * per + (b >> 3) : b;
+  const int q = g * (int)(blockDim.x >> 6) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  return q < npairs ? q : -1;
+}
+
+struct FftXPair {
+  long long la, lb;  // lines
+  int sa, sb;        // species
+  __device__ __forceinline__ FftXPair(const FftPairs& fp, int S, int q) {
+    if (S == 1) {
+      la = 2LL * q;
+      lb = la + 1 < fp.lines ? la + 1 : la;
+      sa = sb = 0;
+    } else {
+      const int h = (S + 1) / 2;
+      la = lb = q / h;
+      sa = 2 * (q % h);
+      sb = sa + 1 < S ? sa + 1 : sa;
+    }
+  }
+};
+
+// Column pair of a strided axis, with the interface of RowIO (wave.h): "side"
+// a / b are the two columns, row block rb the points lane + 64 (4 rb + r).
+template <typename T>
+struct FftCols {
+  static constexpr bool EXACT = true;  // every point counts once
+  long long oa, ob, step;              // elements; step: 64 rows
+  bool adj;                            // b follows a in memory
+  __device__ __forceinline__ FftCols(const FftPairs& fp, int n, int q, int lane) {
+    const long long c0 = 2LL * q, c1 = c0 + 1 < fp.lines ? c0 + 1 : c0;
+    const unsigned inner = (unsigned)fp.inner;
+    const unsigned o0 = (unsigned)c0 / inner, o1 = (unsigned)c1 / inner;
+    oa = (long long)o0 * n * fp.inner + ((unsigned)c0 - o0 * inner);
+    ob = (long long)o1 * n * fp.inner + ((unsigned)c1 - o1 * inner);
+    adj = ob == oa + 1;
+    oa += lane * fp.inner;
+    ob += lane * fp.inner;
+    step = 64 * fp.inner;
+  }
+  struct Off {
+    long long a[4], b[4];
+    bool adj;
+  };
+  __device__ __forceinline__ Off offs(int rb) const {
+    Off o;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      o.a[r] = oa + (4 * rb + r) * step;
+      o.b[r] = ob + (4 * rb + r) * step;
+    }
+    o.adj = adj;
+    return o;
+  }
+  template <typename U>
+  struct alignas(sizeof(U)) Two {
+    U x, y;
+  };
+  template <typename U>
+  __device__ __forceinline__ void load(const U* f, const Off& o, U (&va)[4], U (&vb)[4]) const {
+    if (o.adj) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const Two<U> t = *reinterpret_cast<const Two<U>*>(f + o.a[r]);
+        va[r] = t.x;
+        vb[r] = t.y;
+      }
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        va[r] = f[o.a[r]];
+        vb[r] = f[o.b[r]];
+      }
+    }
+  }
+  template <typename U>
+  __device__ __forceinline__ void store(U* f, const Off& o, const U (&va)[4], const U (&vb)[4]) const {
+    if (o.adj) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) *reinterpret_cast<Two<U>*>(f + o.a[r]) = Two<U>{va[r], vb[r]};
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        f[o.a[r]] = va[r];
+        f[o.b[r]] = vb[r];
+      }
+    }
+  }
+  template <typename U>
+  __device__ __forceinline__ void load1(const U* f, const long long (&o)[4], U (&v)[4]) const {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = f[o[r]];
+  }
+  template <typename U>
+  __device__ __forceinline__ void store1(U* f, const long long (&o)[4], const U (&v)[4]) const {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) f[o[r]] = v[r];
+  }
+  // an array that this pass also read: a repeated last column (b on a) is
+  // written from side a only
+  template <int SIDE, typename U>
+  __device__ __forceinline__ void store_rmw(U* f, const long long (&o)[4], const U (&v)[4], int) const {
+    if (SIDE == 0 || ob != oa) store1(f, o, v);
+  }
+  template <int E>
+  __device__ __forceinline__ void load_all(const T* f, T (&a)[E], T (&b)[E]) const {
+#pragma unroll
+    for (int q = 0; q < E / 4; ++q) {
+      T va[4], vb[4];
+      load(f, offs(q), va, vb);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        a[4 * q + r] = va[r];
+        b[4 * q + r] = vb[r];
+      }
+    }
+  }
+  template <int E>
+  __device__ __forceinline__ void store_all(T* f, const T (&a)[E], const T (&b)[E]) const {
+#pragma unroll
+    for (int q = 0; q < E / 4; ++q) {
+      T va[4], vb[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        va[r] = a[4 * q + r];
+        vb[r] = b[4 * q + r];
+      }
+      store(f, offs(q), va, vb);
+    }
+  }
+};
+
+template <int E, typename T>
+__device__ __forceinline__ void fft_load_line(const T* p, int lane, T (&v)[E]) {
+#pragma unroll
+  for (int e = 0; e < E; ++e) v[e] = p[lane + 64 * e];
+}
+template <int E, typename T>
+__device__ __forceinline__ void fft_store_line(T* p, int lane, const T (&v)[E]) {
+#pragma unroll
+  for (int e = 0; e < E; ++e) p[lane + 64 * e] = v[e];
+}
+
+// f of the pair's stage values; true if a value was not finite.
+template <int KIND, int E, typename T>
+__device__ __forceinline__ bool fft_react(const StageArgs<T>& a, const FftXPair& pr, int n, int lane,
+                                          T (&va)[E], T (&vb)[E]) {
+  const RxnT<T> rx(a.rxn);
+  T chk = T(0);
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const T u[2] = {va[e], vb[e]};
+    T f[2];
+    if constexpr (KIND == RXN_LINEAR) {
+      auto lin = [&](int s) { return s == 0 ? rx.lin[0] : s == 1 ? rx.lin[1] : s == 2 ? rx.lin[2] : rx.lin[3]; };
+      f[0] = lin(pr.sa) * u[0];
+      f[1] = lin(pr.sb) * u[1];
+    } else if constexpr (KIND >= RXN_HUXLEY_MMS) {
+      rxn_eval_k<T, 1, KIND>(rx, &u[0], &f[0]);
+      rxn_eval_k<T, 1, KIND>(rx, &u[1], &f[1]);
+      f[0] += T(mms_source_call(a.rxn, a.t, pr.la * n + lane + 64 * e, a.n0, a.n1));
+      f[1] += T(mms_source_call(a.rxn, a.t, pr.lb * n + lane + 64 * e, a.n0, a.n1));
+    } else {
+      rxn_eval_k<T, 2, KIND>(rx, u, f);
+    }
+    chk = fma(u[0], T(0), chk);
+    chk = fma(u[1], T(0), chk);
+    chk = fma(f[0], T(0), chk);
+    chk = fma(f[1], T(0), chk);
+    va[e] = f[0];
+    vb[e] = f[1];
+  }
+  return !(chk == T(0));
+}
+
+// X: inverse-x, reaction, forward-x (in place on P). SRC: manufactured sources
+// (a call, whose stack the other plans' kernel does without).
+template <typename T, int N, bool SRC>
+__global__ __launch_bounds__(256) void k_fx(StageArgs<T> a, FftPairs fp) {
+  to_member(a);
+  extern __shared__ __align__(16) char smem[];
+  const WaveFft<T, N> ft(smem, a.Mt);
+  const int q = fft_pair(fp.npairs);
+  if (q < 0) return;
+  const FftXPair pr(fp, a.S, q);
+  const long long oa = pr.sa * a.g.total + pr.la * N, ob = pr.sb * a.g.total + pr.lb * N;
+  typename WaveFft<T, N>::Vals va, vb;
+  fft_load_line(a.P + oa, ft.lane, va);
+  fft_load_line(a.P + ob, ft.lane, vb);
+  ft.hartley(va, vb);
+  if (a.st_phys) {
+    T* st = a.st_phys + (long long)a.mode * a.S * a.g.total;
+    fft_store_line(st + oa, ft.lane, va);
+    fft_store_line(st + ob, ft.lane, vb);
+  }
+  bool bad;
+  if constexpr (SRC) {
+    bad = a.rxn.kind == RXN_HUXLEY_MMS ? fft_react<RXN_HUXLEY_MMS>(a, pr, N, ft.lane, va, vb)
+                                       : fft_react<RXN_FISHER_MMS>(a, pr, N, ft.lane, va, vb);
+  } else {
+    switch (a.rxn.kind) {  // uniform
+      case RXN_LINEAR: bad = fft_react<RXN_LINEAR>(a, pr, N, ft.lane, va, vb); break;
+      case RXN_FHN: bad = fft_react<RXN_FHN>(a, pr, N, ft.lane, va, vb); break;
+      case RXN_GRAY_SCOTT: bad = fft_react<RXN_GRAY_SCOTT>(a, pr, N, ft.lane, va, vb); break;
+      case RXN_SCHNAKENBERG: bad = fft_react<RXN_SCHNAKENBERG>(a, pr, N, ft.lane, va, vb); break;
+      default: bad = fft_react<RXN_GM>(a, pr, N, ft.lane, va, vb); break;
+    }
+  }
+  if (bad) a.flag[0] = 1;
+  ft.hartley(va, vb);
+  fft_store_line(a.P + oa, ft.lane, va);
+  fft_store_line(a.P + ob, ft.lane, vb);
+}
+
+// One transform along the x axis, src -> dst (may alias). (Neumann point
+// weights never apply: the axis is periodic.)
+template <typename T, int N>
+__global__ __launch_bounds__(256) void k_fsx(SingleArgs<T> a, FftPairs fp) {
+  to_member(a);
+  extern __shared__ __align__(16) char smem[];
+  const WaveFft<T, N> ft(smem, a.Mt);
+  const int q = fft_pair(fp.npairs);
+  if (q < 0) return;
+  const FftXPair pr(fp, a.S, q);
+  const long long oa = pr.sa * a.g.total + pr.la * N, ob = pr.sb * a.g.total + pr.lb * N;
+  typename WaveFft<T, N>::Vals va, vb;
+  fft_load_line(a.src + oa, ft.lane, va);
+  fft_load_line(a.src + ob, ft.lane, vb);
+  ft.hartley(va, vb);
+  fft_store_line(a.dst + oa, ft.lane, va);
+  fft_store_line(a.dst + ob, ft.lane, vb);
+}
+
+// One transform along a strided axis, src -> dst (may alias).
+template <typename T, int N>
+__global__ __launch_bounds__(256) void k_fsy(SingleArgs<T> a, FftPairs fp) {
+  to_member(a);
+  extern __shared__ __align__(16) char smem[];
+  const WaveFft<T, N> ft(smem, a.Mt);
+  const int q = fft_pair(fp.npairs);
+  if (q < 0) return;
+  const FftCols<T> io(fp, N, q, ft.lane);
+  typename WaveFft<T, N>::Vals va, vb;
+  io.load_all(a.src, va, vb);
+  ft.hartley(va, vb);
+  io.store_all(a.dst, va, vb);
+}
+
+// Z: forward transform along the last axis, stage combine, inverse transform
+// (in place on P). MODE 0..3; MODE < 0: MODE_INIT or MODE_RESTORE (a.mode).
+template <typename T, int N, int MODE>
+__global__ __launch_bounds__(256) void k_fz(StageArgs<T> a, FftPairs fp) {
+  to_member(a);
+  extern __shared__ __align__(16) char smem[];
+  using FT = WaveFft<T, N>;
+  const FT ft(smem, a.Mt);
+  const int q = fft_pair(fp.npairs);
+  if (q < 0) return;
+  const FftCols<T> io(fp, N, q, ft.lane);
+  typename FT::Vals va, vb;
+  io.load_all(a.src ? a.src : a.P, va, vb);
+  if constexpr (MODE >= 0) {
+    auto run = [&](auto tab) {
+      constexpr int TAB = decltype(tab)::value;
+      // the retained arrays in flight over the transform, where they fit
+      constexpr bool AHEAD = FT::E * sizeof(T) <= 64;
+      CombineIn<T> in[FT::E / 4];
+      auto read = [&](auto rbc) {
+        constexpr int rb = decltype(rbc)::value;
+        io.load(MODE <= 1 ? a.uhat : a.acc, io.offs(rb), in[rb].x1[0], in[rb].x1[1]);
+        wave_combine_in<MODE, false, TAB>(io, a, rb, in[rb]);
+      };
+      if constexpr (AHEAD) static_for<FT::E / 4>(read);
+      ft.hartley(va, vb);
+      const float lz[2][4] = {};
+      static_for<FT::E / 4>([&](auto rbc) {
+        constexpr int rb = decltype(rbc)::value;
+        if constexpr (!AHEAD) read(rbc);
+        T ya[4], yb[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          ya[r] = va[4 * rb + r];
+          yb[r] = vb[4 * rb + r];
+        }
+        wave_combine_out<MODE, false, TAB>(io, a, rb, 0.f, T(0), T(0), lz, in[rb], ya, yb);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          va[4 * rb + r] = ya[r];
+          vb[4 * rb + r] = yb[r];
+        }
+      });
+    };
+    if (a.ltab)
+      run(std::integral_constant<int, 1>{});
+    else
+      run(std::integral_constant<int, 0>{});
+  } else {
+    if (!a.src) ft.hartley(va, vb);
+    if (a.mode == MODE_INIT) io.store_all(a.uhat, va, vb);
+#pragma unroll
+    for (int e = 0; e < FT::E; ++e) {
+      va[e] *= a.cs;
+      vb[e] *= a.cs;
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < FT::E; ++e) {
+    keep(va[e]);
+    keep(vb[e]);
+  }
+  ft.hartley(va, vb);
+  io.store_all(a.P, va, vb);
+}
+
+// Adjoint reaction of the pair (species 0, 1 of two-species plans).
+template <int KIND, int E, typename T>
+__device__ __forceinline__ void fft_adj_react(const StageArgs<T>& a, const FftXPair& pr,
+                                              T (&ga)[E], T (&gb)[E], const T (&ua)[E],
+                                              const T (&ub)[E], double* pacc) {
+  const bool wp = a.rp_acc != nullptr;
+  // a repeated line or species counts once
+  const bool two = pr.la != pr.lb || pr.sa != pr.sb;
+  auto lin = [&](int s) { return T(s == 0 ? a.rxn.p[0] : s == 1 ? a.rxn.p[1] : s == 2 ? a.rxn.p[2] : a.rxn.p[3]); };
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const T g[2] = {ga[e], gb[e]}, u[2] = {ua[e], ub[e]};
+    T o[2];
+    if constexpr (KIND == RXN_LINEAR) {
+      o[0] = lin(pr.sa) * g[0];
+      o[1] = lin(pr.sb) * g[1];
+      if (wp) {
+        const double ca = double(g[0] * u[0]), cb = two ? double(g[1] * u[1]) : 0.0;
+#pragma unroll
+        for (int s = 0; s < MAX_SPECIES; ++s) {
+          pacc[s] += pr.sa == s ? ca : 0.0;
+          pacc[s] += pr.sb == s ? cb : 0.0;
+        }
+      }
+    } else if constexpr (KIND >= RXN_HUXLEY_MMS) {
+      rxn_adjoint_k<T, 1, KIND>(a.rxn, &u[0], &g[0], &o[0], 1.0, pacc, false);
+      rxn_adjoint_k<T, 1, KIND>(a.rxn, &u[1], &g[1], &o[1], 1.0, pacc, false);
+    } else {
+      rxn_adjoint_k<T, 2, KIND>(a.rxn, u, g, o, 1.0, pacc, wp);
+    }
+    ga[e] = o[0];
+    gb[e] = o[1];
+  }
+}
+
+// X, adjoint. (Every wavefront of a block reaches the block sums.)
+template <typename T, int N>
+__global__ __launch_bounds__(256) void k_fxadj(StageArgs<T> a, FftPairs fp) {
+  to_member(a);
+  extern __shared__ __align__(16) char smem[];
+  using FT = WaveFft<T, N>;
+  const FT ft(smem, a.Mt);
+  double pacc[RXN_NP_MAX];
+#pragma unroll
+  for (int k = 0; k < RXN_NP_MAX; ++k) pacc[k] = 0.0;
+  const int q = fft_pair(fp.npairs);
+  if (q >= 0) {
+    const FftXPair pr(fp, a.S, q);
+    const long long oa = pr.sa * a.g.total + pr.la * N, ob = pr.sb * a.g.total + pr.lb * N;
+    typename FT::Vals va, vb, ua, ub;
+    fft_load_line(a.P + oa, ft.lane, va);
+    fft_load_line(a.P + ob, ft.lane, vb);
+    const T* st = a.st_phys + (long long)a.mode * a.S * a.g.total;
+    fft_load_line(st + oa, ft.lane, ua);
+    fft_load_line(st + ob, ft.lane, ub);
+    ft.hartley(va, vb);
+    switch (a.rxn.kind) {  // uniform
+      case RXN_LINEAR: fft_adj_react<RXN_LINEAR>(a, pr, va, vb, ua, ub, pacc); break;
+      case RXN_FHN: fft_adj_react<RXN_FHN>(a, pr, va, vb, ua, ub, pacc); break;
+      case RXN_GRAY_SCOTT: fft_adj_react<RXN_GRAY_SCOTT>(a, pr, va, vb, ua, ub, pacc); break;
+      case RXN_SCHNAKENBERG: fft_adj_react<RXN_SCHNAKENBERG>(a, pr, va, vb, ua, ub, pacc); break;
+      case RXN_GM: fft_adj_react<RXN_GM>(a, pr, va, vb, ua, ub, pacc); break;
+      case RXN_HUXLEY_MMS: fft_adj_react<RXN_HUXLEY_MMS>(a, pr, va, vb, ua, ub, pacc); break;
+      default: fft_adj_react<RXN_FISHER_MMS>(a, pr, va, vb, ua, ub, pacc); break;
+    }
+    ft.hartley(va, vb);
+    fft_store_line(a.P + oa, ft.lane, va);
+    fft_store_line(a.P + ob, ft.lane, vb);
+  }
+  if (a.rp_acc) block_add_partials(reinterpret_cast<double*>(smem), pacc, a.rxn.np, a.rp_acc);
+}
+
+// Z, adjoint (a.mode at run time).
+template <typename T, int N>
+__global__ __launch_bounds__(256) void k_fzadj(StageArgs<T> a, FftPairs fp) {
+  to_member(a);
+  extern __shared__ __align__(16) char smem[];
+  using FT = WaveFft<T, N>;
+  const FT ft(smem, a.Mt);
+  const int q = fft_pair(fp.npairs);
+  if (q < 0) return;
+  const FftCols<T> io(fp, N, q, ft.lane);
+  typename FT::Vals va, vb;
+  io.load_all(a.P, va, vb);
+  ft.hartley(va, vb);
+  static_for<FT::E / 4>([&](auto rbc) {
+    constexpr int rb = decltype(rbc)::value;
+    T ya[4], yb[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      ya[r] = va[4 * rb + r];
+      yb[r] = vb[4 * rb + r];
+    }
+    wave_adj_tab<0>(io, a, rb, ya);
+    wave_adj_tab<1>(io, a, rb, yb);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      va[4 * rb + r] = ya[r];
+      // (a repeated column: side b has read what side a wrote)
+      vb[4 * rb + r] = io.ob != io.oa ? yb[r] : ya[r];
+    }
+  });
+  ft.hartley(va, vb);
+  io.store_all(a.P, va, vb);
+}
+
+// Kernels of one N, by the kernel numbers of the wave engine.
+struct FftKernels {
+  const void* fn[WK_COUNT];
+  size_t lds;  // per wavefront
+};
+template <typename T, int N>
+FftKernels fft_kernels() {
+  FftKernels k{};
+  k.fn[WK_X] = reinterpret_cast<const void*>(&k_fx<T, N, false>);
+  k.fn[WK_XSRC] = reinterpret_cast<const void*>(&k_fx<T, N, true>);
+  k.fn[WK_SX] = reinterpret_cast<const void*>(&k_fsx<T, N>);
+  k.fn[WK_SY] = reinterpret_cast<const void*>(&k_fsy<T, N>);
+  k.fn[WK_ZINIT] = reinterpret_cast<const void*>(&k_fz<T, N, -1>);
+  k.fn[WK_Z] = reinterpret_cast<const void*>(&k_fz<T, N, 0>);
+  k.fn[WK_Z + 1] = reinterpret_cast<const void*>(&k_fz<T, N, 1>);
+  k.fn[WK_Z + 2] = reinterpret_cast<const void*>(&k_fz<T, N, 2>);
+  k.fn[WK_Z + 3] = reinterpret_cast<const void*>(&k_fz<T, N, 3>);
+  k.fn[WK_XADJ] = k.fn[WK_XADJ + 1] = reinterpret_cast<const void*>(&k_fxadj<T, N>);
+  k.fn[WK_ZADJ] = reinterpret_cast<const void*>(&k_fzadj<T, N>);
+  k.lds = WaveFft<T, N>::lds_bytes();
+  return k;
+}
+template <typename T>
+FftKernels fft_kernels(long long n) {
+  return n == 256 ? fft_kernels<T, 256>() : n == 512 ? fft_kernels<T, 512>() : fft_kernels<T, 1024>();
+}
 
 }  // namespace sfrde

@@ -1,9 +1,10 @@
 // Device kernels of the ETDRK4 step.
 //
 // Every field is [S][total] with x fastest (ensembles: [member][S][total], the
-// member taken from blockIdx.y). A kernel works on "line tiles":
-// W lines along one axis (length n, stride `inner`), staged in LDS as
-// buf[s][j][w] (j along the axis, w the line within the tile). Per-axis
+// member taken from blockIdx.y). The dense kernels of this file, for axes that
+// neither the matrix-core engine (wave.h) nor the FFTs (fft.h) take, work on
+// "line tiles": W lines along one axis (length n, stride `inner`), staged in LDS
+// as buf[s][j][w] (j along the axis, w the line within the tile). Per-axis
 // transforms are products with the axis matrix M (forward, unnormalised):
 //   periodic  M[k][j] = cos(2 pi kj/N) + sin(2 pi kj/N)   (discrete Hartley)
 //   Dirichlet M[k][j] = sin(pi (k+1)(j+1)/N)                (DST-I)
@@ -38,9 +39,7 @@ constexpr int KMAX = 32;  // outputs per thread in the dense transform: n*W <= K
 
 struct Geom {
   int n;            // length of the transformed axis
-  int spt;          // species per tile: all, or 1 (strided axes may split tiles by species,
-                    // with the species index folded into the outer blocks)
-  int fast;         // full tiles may use the 32-bit-offset vector paths of the FP32 engine
+  int spt;          // species per tile (all of them)
   int W;            // lines per tile (a power of two)
   int pitch;        // LDS row pitch (>= W)
   int wshift;       // log2(W)
@@ -159,134 +158,6 @@ __device__ __forceinline__ void store_tile(const Geom& g, long long tile, const 
       long long idx;
       if (elem(g, tr, j, w, idx)) dp[idx] = b[j * g.pitch + w];
     }
-  }
-}
-
-// 16-byte vectors of the field type.
-template <typename T>
-struct Vec16;
-template <>
-struct Vec16<float> {
-  using type = float4;
-  static constexpr int N = 4;
-};
-template <>
-struct Vec16<double> {
-  using type = double2;
-  static constexpr int N = 2;
-};
-template <typename T>
-__device__ __forceinline__ T vget(const typename Vec16<T>::type& v, int e);
-template <>
-__device__ __forceinline__ float vget<float>(const float4& v, int e) {
-  return e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w;
-}
-template <>
-__device__ __forceinline__ double vget<double>(const double2& v, int e) {
-  return e == 0 ? v.x : v.y;
-}
-template <typename T>
-__device__ __forceinline__ void vset(typename Vec16<T>::type& v, int e, T x);
-template <>
-__device__ __forceinline__ void vset<float>(float4& v, int e, float x) {
-  if (e == 0) v.x = x; else if (e == 1) v.y = x; else if (e == 2) v.z = x; else v.w = x;
-}
-template <>
-__device__ __forceinline__ void vset<double>(double2& v, int e, double x) {
-  if (e == 0) v.x = x; else v.y = x;
-}
-
-// Whether a tile can move in 16-byte vectors: full tile, vector-aligned rows.
-template <typename T>
-__device__ __forceinline__ bool tile_vectorizable(const Geom& g, const TileRef& t, const void* p) {
-  constexpr int VW = Vec16<T>::N;
-  if (reinterpret_cast<unsigned long long>(p) & 15ull) return false;
-  if (g.total % VW) return false;
-  if (t.wvalid != g.W) return false;
-  if (g.inner == 1) return (g.n % VW) == 0;
-  return (g.inner % VW) == 0 && (g.W % VW) == 0;
-}
-
-// Vector v of one species' tile -> (global element, LDS row j, lane w): VW
-// consecutive rows of one line (x axis) or VW consecutive lanes of one row.
-template <typename T>
-__device__ __forceinline__ void vec_coords(const Geom& g, const TileRef& t, int v, long long& gidx,
-                                           int& j, int& w) {
-  constexpr int VW = Vec16<T>::N;
-  const int e = v * VW;
-  unpack(g, e, j, w);
-  gidx = t.base + (long long)j * t.rs + (long long)w * t.cs;
-}
-
-// Tile load with every vector load of a thread issued before any use.
-template <typename T>
-__device__ __forceinline__ void load_tile_fast(const Geom& g, long long tile,
-                                               const T* __restrict__ src, T* buf, int S) {
-  const TileRef tr = tile_ref(g, tile);
-  if (!tile_vectorizable<T>(g, tr, src)) {
-    load_tile(g, tile, src, buf, S);
-    return;
-  }
-  using V = typename Vec16<T>::type;
-  constexpr int VW = Vec16<T>::N;
-  constexpr int CH = 4;
-  const int per_s = g.n * g.W / VW;
-  const int total_v = S * per_s;
-  for (int base = 0; base < total_v; base += CH * blockDim.x) {
-    V r[CH];
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-      const int v = base + c * blockDim.x + threadIdx.x;
-      if (v < total_v) {
-        const int s = v >= per_s ? (v >= 2 * per_s ? (v >= 3 * per_s ? 3 : 2) : 1) : 0;
-        long long gi;
-        int j, w;
-        vec_coords<T>(g, tr, v - s * per_s, gi, j, w);
-        r[c] = *reinterpret_cast<const V*>(src + s * g.total + gi);
-      }
-    }
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-      const int v = base + c * blockDim.x + threadIdx.x;
-      if (v < total_v) {
-        const int s = v >= per_s ? (v >= 2 * per_s ? (v >= 3 * per_s ? 3 : 2) : 1) : 0;
-        long long gi;
-        int j, w;
-        vec_coords<T>(g, tr, v - s * per_s, gi, j, w);
-        T* b = buf + s * g.n * g.pitch;
-        for (int e = 0; e < VW; ++e) {
-          if (g.inner == 1)
-            b[(j + e) * g.pitch + w] = vget<T>(r[c], e);
-          else
-            b[j * g.pitch + w + e] = vget<T>(r[c], e);
-        }
-      }
-    }
-  }
-}
-
-template <typename T>
-__device__ __forceinline__ void store_tile_fast(const Geom& g, long long tile, const T* buf,
-                                                T* __restrict__ dst, int S) {
-  const TileRef tr = tile_ref(g, tile);
-  if (!tile_vectorizable<T>(g, tr, dst)) {
-    store_tile(g, tile, buf, dst, S);
-    return;
-  }
-  using V = typename Vec16<T>::type;
-  constexpr int VW = Vec16<T>::N;
-  const int per_s = g.n * g.W / VW;
-  const int total_v = S * per_s;
-  for (int v = threadIdx.x; v < total_v; v += blockDim.x) {
-    const int s = v >= per_s ? (v >= 2 * per_s ? (v >= 3 * per_s ? 3 : 2) : 1) : 0;
-    long long gi;
-    int j, w;
-    vec_coords<T>(g, tr, v - s * per_s, gi, j, w);
-    const T* b = buf + s * g.n * g.pitch;
-    V r;
-    for (int e = 0; e < VW; ++e)
-      vset<T>(r, e, g.inner == 1 ? b[(j + e) * g.pitch + w] : b[j * g.pitch + w + e]);
-    *reinterpret_cast<V*>(dst + s * g.total + gi) = r;
   }
 }
 
@@ -673,110 +544,6 @@ __device__ __forceinline__ void pw_combine(const StageArgs<T>& a, T* buf, long l
   }
 }
 
-// Vectorised forward combine for full tiles along a strided axis: each work
-// item is VW consecutive lanes of one row of one species, with all of its
-// global loads issued before the arithmetic. One instance per stage.
-template <typename T, int MODE, bool LT>
-__device__ __forceinline__ void combine_vec(const StageArgs<T>& a, T* buf, const TileRef& tr) {
-  using V = typename Vec16<T>::type;
-  constexpr int VW = Vec16<T>::N;
-  const Geom& g = a.g;
-  const int S = a.S;
-  const long long tot = g.total;
-  const long long cst = (long long)S * tot;
-  const int ngroups = g.n * g.W / VW;
-  const T cs = a.cs;
-#pragma clang loop unroll(disable)
-  for (int it = threadIdx.x; it < g.spt * ngroups; it += blockDim.x) {
-    const int s = it >= ngroups ? (it >= 2 * ngroups ? (it >= 3 * ngroups ? 3 : 2) : 1) : 0;
-    long long gi;
-    int j, w;
-    vec_coords<T>(g, tr, it - s * ngroups, gi, j, w);
-    const long long i = s * tot + gi;
-    T* cell = buf + (s * g.n + j) * g.pitch + w;
-    // global loads first
-    V Lv, t0, t1, t2, t3, uh, ac, ct;
-    if (LT) {
-      Lv = *reinterpret_cast<const V*>(a.ltab + i);
-    } else {
-      const T* cf = a.coef + i;
-      if (MODE <= 1) t0 = *reinterpret_cast<const V*>(cf + C_Q * cst);
-      if (MODE <= 2) t1 = *reinterpret_cast<const V*>(cf + C_PHI * cst);
-      t2 = *reinterpret_cast<const V*>(cf + (MODE == 0 ? C_R : MODE == 3 ? C_PHI3 : C_PHI2) * cst);
-      if (MODE == 0) t3 = *reinterpret_cast<const V*>(cf + C_PHI1 * cst);
-    }
-    if (MODE <= 1) uh = *reinterpret_cast<const V*>(a.uhat + i);
-    if (MODE >= 1) ac = *reinterpret_cast<const V*>(a.acc + i);
-    if (MODE == 2) ct = *reinterpret_cast<const V*>(a.ctil + i);
-    V fh, o0, o1, out;
-    for (int e = 0; e < VW; ++e) vset<T>(fh, e, cell[e]);
-#pragma unroll
-    for (int e = 0; e < VW; ++e) {
-      T c0 = T(0), c1 = T(0), c2 = T(0), c3 = T(0);
-      if (LT) {
-        stage_coefs_L<T>(MODE, vget<T>(Lv, e), a.tau, c0, c1, c2, c3);
-      } else {
-        if (MODE <= 1) c0 = vget<T>(t0, e);
-        if (MODE <= 2) c1 = vget<T>(t1, e);
-        c2 = vget<T>(t2, e);
-        if (MODE == 0) c3 = vget<T>(t3, e);
-      }
-      const T f = vget<T>(fh, e);
-      if (MODE == 0) {
-        const T u = vget<T>(uh, e);
-        const T av = dec_mul(c0, u) + c1 * f;
-        vset<T>(o0, e, dec_mul(c0, av) - c1 * f);
-        vset<T>(o1, e, dec_mul(c2, u) + c3 * f);
-        vset<T>(out, e, cs * av);
-      } else if (MODE == 1) {
-        vset<T>(out, e, cs * (dec_mul(c0, vget<T>(uh, e)) + c1 * f));
-        vset<T>(o1, e, vget<T>(ac, e) + c2 * f);
-      } else if (MODE == 2) {
-        vset<T>(out, e, cs * (vget<T>(ct, e) + T(2) * c1 * f));
-        vset<T>(o1, e, vget<T>(ac, e) + c2 * f);
-      } else {
-        const T un = vget<T>(ac, e) + c2 * f;
-        vset<T>(o0, e, un);
-        vset<T>(out, e, cs * un);
-      }
-    }
-    if (MODE == 0) {
-      if (a.st_uhat) *reinterpret_cast<V*>(a.st_uhat + i) = uh;
-      *reinterpret_cast<V*>(a.ctil + i) = o0;
-    }
-    if (a.st_fhat) *reinterpret_cast<V*>(a.st_fhat + MODE * cst + i) = fh;
-    if (MODE <= 2) *reinterpret_cast<V*>(a.acc + i) = o1;
-    if (MODE == 3) *reinterpret_cast<V*>(a.uhat + i) = o0;
-    for (int e = 0; e < VW; ++e) cell[e] = vget<T>(out, e);
-  }
-}
-
-// Forward combine of a tile; full tiles along strided axes move in vectors.
-template <typename T>
-__device__ __forceinline__ void pw_combine_fast(const StageArgs<T>& a, T* buf, long long tile) {
-  const Geom& g = a.g;
-  const TileRef tr = tile_ref(g, tile);
-  if (g.inner == 1 || a.mode > 3 || !tile_vectorizable<T>(g, tr, a.uhat)) {
-    pw_combine(a, buf, tile);
-    return;
-  }
-  const bool lt = a.ltab != nullptr;
-  switch (a.mode) {
-    case 0:
-      lt ? combine_vec<T, 0, true>(a, buf, tr) : combine_vec<T, 0, false>(a, buf, tr);
-      break;
-    case 1:
-      lt ? combine_vec<T, 1, true>(a, buf, tr) : combine_vec<T, 1, false>(a, buf, tr);
-      break;
-    case 2:
-      lt ? combine_vec<T, 2, true>(a, buf, tr) : combine_vec<T, 2, false>(a, buf, tr);
-      break;
-    default:
-      lt ? combine_vec<T, 3, true>(a, buf, tr) : combine_vec<T, 3, false>(a, buf, tr);
-      break;
-  }
-}
-
 // Adjoint reaction: buf holds the cotangent of f(stage value) (physical);
 // replaced by J^T of it at the stored stage value. Reaction-parameter
 // partials are added to pacc (weighted by the Neumann point weights).
@@ -991,112 +758,59 @@ __device__ __forceinline__ void block_add_partials(double* red, const double (&p
   block_sums(red, pacc, np, rp_acc, true);
 }
 
-// ---------------------------------------------------------------- tile bodies
-// XF is the per-axis transform applied in place to every species' tile. FAST:
-// full tiles move in 16-byte vectors with every load of a thread issued
-// before its first use, and the combine runs on vectors of strided tiles.
-template <bool FAST, typename T>
-__device__ __forceinline__ void tile_in(const Geom& g, long long tile, const T* src, T* buf, int S) {
-  if (FAST)
-    load_tile_fast(g, tile, src, buf, S);
-  else
-    load_tile(g, tile, src, buf, S);
-}
-
-template <bool FAST, typename T>
-__device__ __forceinline__ void tile_out(const Geom& g, long long tile, const T* buf, T* dst, int S) {
-  if (FAST)
-    store_tile_fast(g, tile, buf, dst, S);
-  else
-    store_tile(g, tile, buf, dst, S);
-}
-
-template <bool FAST, typename T, class XF>
-__device__ __forceinline__ void body_x(const StageArgs<T>& a, T* buf, long long tile, XF& xf) {
-  tile_in<FAST>(a.g, tile, a.P, buf, a.g.spt);
-  __syncthreads();
-  xf(buf, a.g.spt);
-  const bool bad = pw_reaction(a, buf, tile);
-  if (bad) a.flag[0] = 1;
-  __syncthreads();
-  xf(buf, a.g.spt);
-  tile_out<FAST>(a.g, tile, buf, a.P, a.g.spt);
-}
-
-template <bool FAST, typename T, class XF>
-__device__ __forceinline__ void body_z(const StageArgs<T>& a, T* buf, long long tile, XF& xf) {
-  tile_in<FAST>(a.g, tile, a.src ? a.src : a.P, buf, a.g.spt);
-  __syncthreads();
-  if (!a.src) xf(buf, a.g.spt);
-  if (FAST)
-    pw_combine_fast(a, buf, tile);
-  else
-    pw_combine(a, buf, tile);
-  __syncthreads();
-  xf(buf, a.g.spt);
-  tile_out<FAST>(a.g, tile, buf, a.P, a.g.spt);
-}
-
-template <bool FAST, typename T, class XF>
-__device__ __forceinline__ void body_xadj(const StageArgs<T>& a, T* buf, long long tile, XF& xf,
-                                          double* pacc) {
-  tile_in<FAST>(a.g, tile, a.P, buf, a.g.spt);
-  __syncthreads();
-  xf(buf, a.g.spt);
-  pw_adj_reaction(a, buf, tile, pacc);
-  __syncthreads();
-  xf(buf, a.g.spt);
-  tile_out<FAST>(a.g, tile, buf, a.P, a.g.spt);
-}
-
-template <bool FAST, typename T, class XF>
-__device__ __forceinline__ void body_zadj(const StageArgs<T>& a, T* buf, long long tile, XF& xf) {
-  tile_in<FAST>(a.g, tile, a.P, buf, a.g.spt);
-  __syncthreads();
-  xf(buf, a.g.spt);
-  pw_adj_combine(a, buf, tile);
-  __syncthreads();
-  xf(buf, a.g.spt);
-  tile_out<FAST>(a.g, tile, buf, a.P, a.g.spt);
-}
-
-// Dense transform as a functor (one tile per block).
-template <typename T>
-struct DenseXf {
-  const Geom* g;
-  const T* Mt;
-  __device__ __forceinline__ void operator()(T* buf, int S) { dense_transform(buf, S, *g, Mt); }
-};
-
+// ----------------------------------------------------------- dense kernels
+// One tile per block.
 // X kernel, forward: inverse-x, reaction, forward-x (in place on P).
-template <typename T, template <typename> class XFT = DenseXf, bool FAST = false>
+template <typename T>
 __global__ __launch_bounds__(NTHREADS) void k_xstage(StageArgs<T> a) {
   to_member(a);
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  XFT<T> xf{&a.g, a.Mt};
-  body_x<FAST>(a, reinterpret_cast<T*>(smem_raw), blockIdx.x, xf);
+  T* buf = reinterpret_cast<T*>(smem_raw);
+  const long long tile = blockIdx.x;
+  load_tile(a.g, tile, a.P, buf, a.g.spt);
+  __syncthreads();
+  dense_transform(buf, a.g.spt, a.g, a.Mt);
+  const bool bad = pw_reaction(a, buf, tile);
+  if (bad) a.flag[0] = 1;
+  __syncthreads();
+  dense_transform(buf, a.g.spt, a.g, a.Mt);
+  store_tile(a.g, tile, buf, a.P, a.g.spt);
 }
 
 // Z kernel, forward: forward transform along the last axis, stage combine,
 // inverse transform (in place on P).
-template <typename T, template <typename> class XFT = DenseXf, bool FAST = false>
+template <typename T>
 __global__ __launch_bounds__(NTHREADS) void k_zstage(StageArgs<T> a) {
   to_member(a);
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  XFT<T> xf{&a.g, a.Mt};
-  body_z<FAST>(a, reinterpret_cast<T*>(smem_raw), blockIdx.x, xf);
+  T* buf = reinterpret_cast<T*>(smem_raw);
+  const long long tile = blockIdx.x;
+  load_tile(a.g, tile, a.src ? a.src : a.P, buf, a.g.spt);
+  __syncthreads();
+  if (!a.src) dense_transform(buf, a.g.spt, a.g, a.Mt);
+  pw_combine(a, buf, tile);
+  __syncthreads();
+  dense_transform(buf, a.g.spt, a.g, a.Mt);
+  store_tile(a.g, tile, buf, a.P, a.g.spt);
 }
 
 // X kernel, adjoint: inverse-x of the spectral cotangent of f(stage value),
 // transposed reaction Jacobian at the stored stage value, forward-x.
-template <typename T, template <typename> class XFT = DenseXf, bool FAST = false>
+template <typename T>
 __global__ __launch_bounds__(NTHREADS) void k_xadj(StageArgs<T> a) {
   to_member(a);
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  XFT<T> xf{&a.g, a.Mt};
+  T* buf = reinterpret_cast<T*>(smem_raw);
+  const long long tile = blockIdx.x;
   double pacc[RXN_NP_MAX];
   for (int k = 0; k < RXN_NP_MAX; ++k) pacc[k] = 0.0;
-  body_xadj<FAST>(a, reinterpret_cast<T*>(smem_raw), blockIdx.x, xf, pacc);
+  load_tile(a.g, tile, a.P, buf, a.g.spt);
+  __syncthreads();
+  dense_transform(buf, a.g.spt, a.g, a.Mt);
+  pw_adj_reaction(a, buf, tile, pacc);
+  __syncthreads();
+  dense_transform(buf, a.g.spt, a.g, a.Mt);
+  store_tile(a.g, tile, buf, a.P, a.g.spt);
   if (a.rp_acc) {
     __syncthreads();
     block_add_partials(reinterpret_cast<double*>(smem_raw), pacc, a.rxn.np, a.rp_acc);
@@ -1104,12 +818,19 @@ __global__ __launch_bounds__(NTHREADS) void k_xadj(StageArgs<T> a) {
 }
 
 // Z kernel, adjoint: forward-z, adjoint combine, inverse-z.
-template <typename T, template <typename> class XFT = DenseXf, bool FAST = false>
+template <typename T>
 __global__ __launch_bounds__(NTHREADS) void k_zadj(StageArgs<T> a) {
   to_member(a);
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  XFT<T> xf{&a.g, a.Mt};
-  body_zadj<FAST>(a, reinterpret_cast<T*>(smem_raw), blockIdx.x, xf);
+  T* buf = reinterpret_cast<T*>(smem_raw);
+  const long long tile = blockIdx.x;
+  load_tile(a.g, tile, a.P, buf, a.g.spt);
+  __syncthreads();
+  dense_transform(buf, a.g.spt, a.g, a.Mt);
+  pw_adj_combine(a, buf, tile);
+  __syncthreads();
+  dense_transform(buf, a.g.spt, a.g, a.Mt);
+  store_tile(a.g, tile, buf, a.P, a.g.spt);
 }
 
 // One transform along one axis, src -> dst (may alias), with optional
@@ -1137,7 +858,7 @@ __device__ __forceinline__ void to_member(SingleArgs<T>& a) {
   a.dst += f;
 }
 
-template <typename T, template <typename> class XFT = DenseXf, bool FAST = false>
+template <typename T>
 __global__ __launch_bounds__(NTHREADS) void k_single(SingleArgs<T> a) {
   to_member(a);
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -1148,7 +869,7 @@ __global__ __launch_bounds__(NTHREADS) void k_single(SingleArgs<T> a) {
   // tiles hold g.spt species (strided axes may hold one, with the species
   // index in the outer block)
   const int S = g.spt;
-  tile_in<FAST>(g, tile, a.src, buf, S);
+  load_tile(g, tile, a.src, buf, S);
   __syncthreads();
   const int ne = g.n * g.W;
   if (a.pre_divide_w) {
@@ -1162,7 +883,7 @@ __global__ __launch_bounds__(NTHREADS) void k_single(SingleArgs<T> a) {
     }
     __syncthreads();
   }
-  XFT<T>{&g, a.Mt}(buf, S);
+  dense_transform(buf, S, g, a.Mt);
   if (a.post_multiply_w) {
     for (int e = threadIdx.x; e < ne; e += blockDim.x) {
       int j, w;
@@ -1174,7 +895,7 @@ __global__ __launch_bounds__(NTHREADS) void k_single(SingleArgs<T> a) {
     }
     __syncthreads();
   }
-  tile_out<FAST>(g, tile, buf, a.dst, S);
+  store_tile(g, tile, buf, a.dst, S);
 }
 
 // --------------------------------------------------------------------------

@@ -132,9 +132,8 @@ struct sfrde_plan_s {
   bool lfly = false;     // Z kernels of the wave engine form L from the eigenvalues
   // long periodic axes of 256, 512 or 1024 points: FFT tile kernels (fft.h)
   bool use_f[3] = {false, false, false};
-  Geom geom_f[3]{};
-  size_t lds_f[3] = {0, 0, 0};
-  unsigned thr_f[3] = {0, 0, 0};
+  FftPairs fft[3]{};
+  unsigned wpb_f[3] = {0, 0, 0};  // wavefronts per block
   void* tw[3] = {nullptr, nullptr, nullptr};  // [N][2] cos, sin of 2 pi m / N
   int n_cu = 256;
   int device = 0;
@@ -298,7 +297,6 @@ void make_geom(sfrde_plan_s* p, int axis, long long min_tiles = 0) {
   for (int a = 0; a < axis; ++a) inner *= p->n[a];
   g.n = (int)n;
   g.spt = p->S;
-  g.fast = 0;
   g.inner = inner;
   g.total = p->total;
   // Tile width: a power of two with n*W <= KMAX*NTHREADS, the tile of all
@@ -643,38 +641,27 @@ int launch_wave(sfrde_plan_s* p, int axis, int kernel, Args& a) {
   return SFRDE_OK;
 }
 
-// Long periodic axes of N = 256, 512 or 1024 points run the FFT tile kernels
-// (fft.h): x tiles hold 2 lines of every species (1 line for S > 2), strided
-// tiles 4 lines of one species, one wavefront per pair of lines.
+// Periodic axes of N = 256, 512 or 1024 points run the FFT kernels (fft.h): a
+// wavefront per pair of lines, every CU its share of the wavefronts before a
+// block gets a second one (wavefronts of a block share the cache lines of
+// strided axes).
 template <typename T>
 int setup_fft_axis(sfrde_plan_s* p, int axis) {
   const long long n = p->n[axis];
   if (p->wcls[axis] >= 0 || p->bc != SFRDE_BC_PERIODIC ||
       !(n == 256 || n == 512 || n == 1024))
     return SFRDE_OK;
-  Geom& g = p->geom_f[axis];
-  g = p->geom[axis];
-  if (g.inner == 1) {
-    g.spt = p->S;
-    g.W = p->S <= 2 ? 2 : 1;
-    g.tpo = 1;
-    g.tposh = 0;
-    g.ntiles = (g.outer + g.W - 1) / g.W;
-  } else {
-    g.outer *= p->S;  // one species per tile: the species joins the outer index
-    g.spt = 1;
-    g.W = 4;
-    g.tpo = (g.inner + g.W - 1) / g.W;
-    g.tposh = pow2_shift(g.tpo);
-    g.ntiles = g.outer * g.tpo;
-  }
-  g.pitch = g.W | 1;  // odd: a line's elements fall in distinct LDS banks
-  g.wshift = 0;
-  while ((1 << g.wshift) < g.W) ++g.wshift;
-  g.fast = 0;
-  p->thr_f[axis] = FFT_THREADS;  // >= 64 per line pair (at most 2 here)
-  p->lds_f[axis] = fft_lds_bytes<T>(g.spt, g.n, g.W, g.pitch);
-  if (p->lds_f[axis] > 160 * 1024) return SFRDE_OK;  // dense kernels
+  FftPairs& f = p->fft[axis];
+  f.inner = 1;
+  for (int a = 0; a < axis; ++a) f.inner *= p->n[a];
+  const long long lines = p->total / n;  // per species
+  f.lines = axis == 0 ? lines : lines * p->S;
+  const long long pairs =
+      axis == 0 ? (p->S == 1 ? (lines + 1) / 2 : lines * ((p->S + 1) / 2)) : (f.lines + 1) / 2;
+  // 32-bit pair and column numbers
+  if (f.lines >= (1LL << 31) || pairs >= (1LL << 31) - 64) return SFRDE_OK;
+  f.npairs = (int)pairs;
+  p->wpb_f[axis] = pairs * p->B >= 4LL * p->n_cu ? 4 : pairs * p->B >= 2LL * p->n_cu ? 2 : 1;
   const double pi = 3.14159265358979323846;
   std::vector<T> tw((size_t)2 * n);
   for (long long m = 0; m < n; ++m) {
@@ -683,16 +670,26 @@ int setup_fft_axis(sfrde_plan_s* p, int axis) {
   }
   TRY(dev_alloc(p, &p->tw[axis], tw.size() * sizeof(T)));
   HIPCHECK(hipMemcpy(p->tw[axis], tw.data(), tw.size() * sizeof(T), hipMemcpyHostToDevice));
-  std::vector<const void*> fns = {
-      reinterpret_cast<const void*>(&k_xstage<T, FftXf, true>),
-      reinterpret_cast<const void*>(&k_zstage<T, FftXf, true>),
-      reinterpret_cast<const void*>(&k_xadj<T, FftXf, true>),
-      reinterpret_cast<const void*>(&k_zadj<T, FftXf, true>),
-      reinterpret_cast<const void*>(&k_single<T, FftXf, true>)};
-  for (const void* f : fns)
-    HIPCHECK(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 (int)p->lds_f[axis]));
+  const FftKernels k = fft_kernels<T>(n);
+  for (const void* fn : k.fn)
+    if (fn)
+      HIPCHECK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   (int)(p->wpb_f[axis] * k.lds)));
   p->use_f[axis] = true;
+  return SFRDE_OK;
+}
+
+// Blocks of an FFT launch over an axis.
+unsigned fft_blocks(const sfrde_plan_s* p, int axis) {
+  return (unsigned)((p->fft[axis].npairs + p->wpb_f[axis] - 1) / p->wpb_f[axis]);
+}
+
+template <typename T, class Args>
+int launch_fft(sfrde_plan_s* p, int axis, int kernel, Args& a) {
+  const FftKernels k = fft_kernels<T>(p->n[axis]);
+  void* args[] = {&a, &p->fft[axis]};
+  HIPCHECK(hipLaunchKernel(k.fn[kernel], dim3(fft_blocks(p, axis), (unsigned)p->B),
+                           dim3(64 * p->wpb_f[axis]), args, p->wpb_f[axis] * k.lds, p->stream));
   return SFRDE_OK;
 }
 
@@ -700,7 +697,7 @@ int setup_fft_axis(sfrde_plan_s* p, int axis) {
 template <typename T>
 StageArgs<T> stage_args(sfrde_plan_s* p, int axis, void* P) {
   StageArgs<T> a{};
-  a.g = p->use_f[axis] ? p->geom_f[axis] : p->geom[axis];
+  a.g = p->geom[axis];
   a.Mt = (const T*)(p->use_f[axis] ? p->tw[axis] : p->Mt[axis]);
   a.P = (T*)P;
   a.coef = (const T*)p->coef;
@@ -736,7 +733,7 @@ StageArgs<T> stage_args(sfrde_plan_s* p, int axis, void* P) {
 template <typename T>
 int launch_single(sfrde_plan_s* p, int axis, const void* src, void* dst, int pre_div, int post_mul) {
   SingleArgs<T> a{};
-  a.g = p->use_f[axis] ? p->geom_f[axis] : p->geom[axis];
+  a.g = p->geom[axis];
   a.Mt = (const T*)(p->use_f[axis] ? p->tw[axis] : p->Mt[axis]);
   a.src = (const T*)src;
   a.dst = (T*)dst;
@@ -757,8 +754,7 @@ int launch_single(sfrde_plan_s* p, int axis, const void* src, void* dst, int pre
                      p->n[axis] <= 256;
     TRY(launch_wave(p, axis, axis == 0 ? WK_SX : two ? WK_SY2 : WK_SY, a));
   } else if (p->use_f[axis]) {
-    hipLaunchKernelGGL((k_single<T, FftXf, true>), dim3((unsigned)a.g.ntiles, p->B),
-                       dim3(p->thr_f[axis]), p->lds_f[axis], p->stream, a);
+    TRY(launch_fft<T>(p, axis, axis == 0 ? WK_SX : WK_SY, a));
   } else
     hipLaunchKernelGGL(k_single<T>, dim3((unsigned)a.g.ntiles, p->B), dim3(NTHREADS),
                        p->lds[axis], p->stream, a);
@@ -799,8 +795,7 @@ int launch_x(sfrde_plan_s* p, int stage, double t, T* st_phys) {
   if (p->wcls[0] >= 0) {
     TRY(launch_wave(p, 0, p->rxn.kind >= RXN_HUXLEY_MMS ? WK_XSRC : WK_X, a));
   } else if (p->use_f[0]) {
-    hipLaunchKernelGGL((k_xstage<T, FftXf, true>), dim3((unsigned)a.g.ntiles, p->B), dim3(p->thr_f[0]),
-                       p->lds_f[0], p->stream, a);
+    TRY(launch_fft<T>(p, 0, p->rxn.kind >= RXN_HUXLEY_MMS ? WK_XSRC : WK_X, a));
   } else
     hipLaunchKernelGGL(k_xstage<T>, dim3((unsigned)a.g.ntiles, p->B), dim3(NTHREADS),
                        p->lds[0], p->stream, a);
@@ -823,8 +818,7 @@ int launch_z(sfrde_plan_s* p, int mode, const void* src, T* st_fhat, T* uhat = n
   if (p->wcls[ax] >= 0) {
     TRY(launch_wave(p, ax, mode > 3 ? WK_ZINIT : (p->lfly ? WK_ZFLY : WK_Z) + mode, a));
   } else if (p->use_f[ax]) {
-    hipLaunchKernelGGL((k_zstage<T, FftXf, true>), dim3((unsigned)a.g.ntiles, p->B), dim3(p->thr_f[ax]),
-                       p->lds_f[ax], p->stream, a);
+    TRY(launch_fft<T>(p, ax, mode > 3 ? WK_ZINIT : WK_Z + mode, a));
   } else
     hipLaunchKernelGGL(k_zstage<T>, dim3((unsigned)a.g.ntiles, p->B), dim3(NTHREADS),
                        p->lds[ax], p->stream, a);
@@ -986,8 +980,7 @@ int launch_xadj(sfrde_plan_s* p, int stage, const StepStore<T>& st) {
   if (p->wcls[0] >= 0) {
     TRY(launch_wave(p, 0, a.rp_acc ? WK_XADJ + 1 : WK_XADJ, a));
   } else if (p->use_f[0]) {
-    hipLaunchKernelGGL((k_xadj<T, FftXf, true>), dim3((unsigned)a.g.ntiles, p->B), dim3(p->thr_f[0]),
-                       p->lds_f[0], p->stream, a);
+    TRY(launch_fft<T>(p, 0, WK_XADJ, a));
   } else
     hipLaunchKernelGGL(k_xadj<T>, dim3((unsigned)a.g.ntiles, p->B), dim3(NTHREADS),
                        p->lds[0], p->stream, a);
@@ -1016,8 +1009,7 @@ int launch_zadj(sfrde_plan_s* p, int mode, const StepStore<T>* st, int last) {
     const int k = !fly ? WK_ZADJ : (p->thp_on && mode <= 2 ? WK_ZADJTH : WK_ZADJFLY) + mode;
     TRY(launch_wave(p, ax, k, a));
   } else if (p->use_f[ax]) {
-    hipLaunchKernelGGL((k_zadj<T, FftXf, true>), dim3((unsigned)a.g.ntiles, p->B), dim3(p->thr_f[ax]),
-                       p->lds_f[ax], p->stream, a);
+    TRY(launch_fft<T>(p, ax, WK_ZADJ, a));
   } else
     hipLaunchKernelGGL(k_zadj<T>, dim3((unsigned)a.g.ntiles, p->B), dim3(NTHREADS),
                        p->lds[ax], p->stream, a);
@@ -1080,7 +1072,7 @@ int coef_tables(sfrde_plan_s* p, int deriv, void* out) {
 
 // Blocks of the adjoint X kernel (each owns one accumulator per parameter).
 long long rp_blocks(const sfrde_plan_s* p) {
-  if (p->wcls[0] < 0) return p->use_f[0] ? p->geom_f[0].ntiles : p->geom[0].ntiles;
+  if (p->wcls[0] < 0) return p->use_f[0] ? (long long)fft_blocks(p, 0) : p->geom[0].ntiles;
   unsigned g = 1;
   (void)wave_blocks(p, 0, WK_XADJ + 1, &g);  // (the class is known since the plan was made)
   return g;
@@ -1399,9 +1391,8 @@ int build_plan(sfrde_plan_s* p) {
   for (int a = 0; a < p->ndim; ++a)
     make_geom(p, a, std::max<long long>(1, (2LL * p->n_cu + p->B - 1) / p->B));
   for (int a = 0; a < p->ndim; ++a) TRY(setup_wave_axis(p, a));
-  // Long periodic axes of 256, 512 or 1024 points: FFT kernels. Any other
-  // axis the matrix-core engine does not take (n > 256, other periodic
-  // n >= 256, the one-point padding axis of 1D plans) runs the dense LDS
+  // Periodic axes of 256, 512 or 1024 points: FFT kernels. Any other axis the
+  // matrix-core engine does not take (past 512 points) runs the dense LDS
   // kernels with the axis matrix.
   for (int a = 0; a < p->ndim; ++a) {
     if (p->dtype == SFRDE_F32)

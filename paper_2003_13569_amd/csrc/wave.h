@@ -1222,29 +1222,39 @@ __device__ __forceinline__ void lam_z(const XF& xf, const float* lam, int side, 
   v[3] = q.w;
 }
 
-// Stage combine (MODE 0..3) of a row block, both sides. x1a, x1b: the first
-// retained array (stages 0, 1: u_hat; 2, 3: acc), loaded ahead.
-template <int MODE, bool FLY, typename T, class XF>
-__device__ __forceinline__ void wave_combine(const XF& xf, const RowIO<T, XF>& io,
-                                             const StageArgs<T>& a, int rb, float lxy, T kt, T ha,
-                                             const float (&lz)[2][4], const T (&x1a)[4],
-                                             const T (&x1b)[4],
-                                             T (&va)[4], T (&vb)[4]) {
+// What the stage combine of a row block reads, both sides (TAB: whether the plan
+// has the table of L, -1 asked at run time): the retained arrays
+// x1 (stages 0, 1: u_hat; 2, 3: acc; loaded by the caller) and x2 (stage 1:
+// acc; 2: c_tilde), L (in t0) or the coefficients.
+template <typename T>
+struct CombineIn {
+  T x1[2][4], x2[2][4], t0[2][4], t1[2][4], t2[2][4], t3[2][4];
+};
+template <int MODE, bool FLY, int TAB = -1, typename T, class IO>
+__device__ __forceinline__ void wave_combine_in(const IO& io, const StageArgs<T>& a, int rb,
+                                                CombineIn<T>& in) {
   const long long cst = (long long)a.S * a.g.total;
   const auto of = io.offs(rb);
-  T Lv[2][4], t0[2][4], t1[2][4], t2[2][4], t3[2][4], x2[2][4];
   if constexpr (!FLY) {
-    if (a.ltab) {
-      io.load(a.ltab, of, Lv[0], Lv[1]);
+    if (TAB < 0 ? a.ltab != nullptr : TAB) {
+      io.load(a.ltab, of, in.t0[0], in.t0[1]);
     } else {
-      if (MODE <= 1) io.load(a.coef + C_Q * cst, of, t0[0], t0[1]);
-      if (MODE <= 2) io.load(a.coef + C_PHI * cst, of, t1[0], t1[1]);
-      io.load(a.coef + (MODE == 0 ? C_R : MODE == 3 ? C_PHI3 : C_PHI2) * cst, of, t2[0], t2[1]);
-      if (MODE == 0) io.load(a.coef + C_PHI1 * cst, of, t3[0], t3[1]);
+      if (MODE <= 1) io.load(a.coef + C_Q * cst, of, in.t0[0], in.t0[1]);
+      if (MODE <= 2) io.load(a.coef + C_PHI * cst, of, in.t1[0], in.t1[1]);
+      io.load(a.coef + (MODE == 0 ? C_R : MODE == 3 ? C_PHI3 : C_PHI2) * cst, of, in.t2[0], in.t2[1]);
+      if (MODE == 0) io.load(a.coef + C_PHI1 * cst, of, in.t3[0], in.t3[1]);
     }
   }
-  // second array, stage 1: acc;  2: c_tilde
-  if (MODE == 1 || MODE == 2) io.load(MODE == 1 ? a.acc : a.ctil, of, x2[0], x2[1]);
+  if (MODE == 1 || MODE == 2) io.load(MODE == 1 ? a.acc : a.ctil, of, in.x2[0], in.x2[1]);
+}
+
+// Stage combine (MODE 0..3) of a row block, both sides.
+template <int MODE, bool FLY, int TAB = -1, typename T, class IO>
+__device__ __forceinline__ void wave_combine_out(const IO& io, const StageArgs<T>& a, int rb,
+                                                 float lxy, T kt, T ha, const float (&lz)[2][4],
+                                                 const CombineIn<T>& in, T (&va)[4], T (&vb)[4]) {
+  const long long cst = (long long)a.S * a.g.total;
+  const auto of = io.offs(rb);
   T o0[2][4], o1[2][4], fh[2][4];
 #pragma unroll
   for (int side = 0; side < 2; ++side) {
@@ -1258,16 +1268,16 @@ __device__ __forceinline__ void wave_combine(const XF& xf, const RowIO<T, XF>& i
         const float L =
             kt * __builtin_amdgcn_exp2f(ha * __builtin_amdgcn_logf(lxy + lz[side][r]));
         stage_coefs_L<T>(MODE, L, a.tau, c0, c1, c2, c3);
-      } else if (a.ltab) {
-        stage_coefs_L<T>(MODE, Lv[side][r], a.tau, c0, c1, c2, c3);
+      } else if (TAB < 0 ? a.ltab != nullptr : TAB) {
+        stage_coefs_L<T>(MODE, in.t0[side][r], a.tau, c0, c1, c2, c3);
       } else {
-        if (MODE <= 1) c0 = t0[side][r];
-        if (MODE <= 2) c1 = t1[side][r];
-        c2 = t2[side][r];
-        if (MODE == 0) c3 = t3[side][r];
+        if (MODE <= 1) c0 = in.t0[side][r];
+        if (MODE <= 2) c1 = in.t1[side][r];
+        c2 = in.t2[side][r];
+        if (MODE == 0) c3 = in.t3[side][r];
       }
       T& v = side ? vb[r] : va[r];
-      const T x1 = side ? x1b[r] : x1a[r];
+      const T x1 = in.x1[side][r];
       const T f = v;
       fh[side][r] = f;
       T out;
@@ -1278,9 +1288,9 @@ __device__ __forceinline__ void wave_combine(const XF& xf, const RowIO<T, XF>& i
         out = av;
       } else if (MODE == 1) {
         out = dec_mul(c0, x1) + c1 * f;
-        o1[side][r] = x2[side][r] + c2 * f;
+        o1[side][r] = in.x2[side][r] + c2 * f;
       } else if (MODE == 2) {
-        out = x2[side][r] + T(2) * c1 * f;
+        out = in.x2[side][r] + T(2) * c1 * f;
         o1[side][r] = x1 + c2 * f;
       } else {
         out = x1 + c2 * f;
@@ -1290,7 +1300,7 @@ __device__ __forceinline__ void wave_combine(const XF& xf, const RowIO<T, XF>& i
     }
   }
   if (MODE == 0) {
-    if (a.st_uhat) io.store(a.st_uhat, of, x1a, x1b);
+    if (a.st_uhat) io.store(a.st_uhat, of, in.x1[0], in.x1[1]);
     io.store(a.ctil, of, o0[0], o0[1]);
   }
   if (a.st_fhat) io.store(a.st_fhat + MODE * cst, of, fh[0], fh[1]);
@@ -1345,7 +1355,14 @@ __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wz(StageArgs<T> a, 
           lam_z(xf, lam, 0, rb, lz[0]);
           lam_z(xf, lam, 1, rb, lz[1]);
         }
-        wave_combine<MODE, FLY>(xf, io, a, rb, lxy, kt, ha, lz, xa[rb], xb[rb], ya[rb], yb[rb]);
+        CombineIn<T> in;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          in.x1[0][r] = xa[rb][r];
+          in.x1[1][r] = xb[rb][r];
+        }
+        wave_combine_in<MODE, FLY>(io, a, rb, in);
+        wave_combine_out<MODE, FLY>(io, a, rb, lxy, kt, ha, lz, in, ya[rb], yb[rb]);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           keep(ya[rb][r]);
@@ -1666,9 +1683,9 @@ __device__ __forceinline__ void wave_adj_fly(const XF& xf, const RowIO<float, XF
 // The same from tables, any precision and scheme (formulas and terms of
 // pw_adj_combine; the per-point accumulator G when the gradients of kappa and
 // alpha are asked).
-template <int SIDE, typename T, class XF>
-__device__ __forceinline__ void wave_adj_tab(const XF& xf, const RowIO<T, XF>& io,
-                                             const StageArgs<T>& a, int rb, T (&v4)[4]) {
+template <int SIDE, typename T, class IO>
+__device__ __forceinline__ void wave_adj_tab(const IO& io, const StageArgs<T>& a, int rb,
+                                             T (&v4)[4]) {
   const long long cst = (long long)a.S * a.g.total;
   const auto ofs = io.offs(rb);
   const auto& of = SIDE ? ofs.b : ofs.a;
@@ -1848,9 +1865,9 @@ __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wzadj(StageArgs<T> 
       static_for<NB>([&](auto rbc) {
         constexpr int rb = decltype(rbc)::value;
         if (!xf.used(rb)) return;
-        wave_adj_tab<0>(xf, io, a, rb, ya[rb]);
+        wave_adj_tab<0>(io, a, rb, ya[rb]);
         __builtin_amdgcn_sched_barrier(0);
-        wave_adj_tab<1>(xf, io, a, rb, yb[rb]);
+        wave_adj_tab<1>(io, a, rb, yb[rb]);
         __builtin_amdgcn_sched_barrier(0);
       });
     }
@@ -2287,8 +2304,11 @@ __global__ __launch_bounds__(64 * NB) void k_gz(StageArgs<T> a, WaveAxis ax, Wav
   T va[4] = {}, vb[4] = {};
   typename XF::Rows ma, mb;
   if (xf.on) io.load(a.src ? a.src : a.P, of, va, vb);
-  T xa[4] = {}, xb[4] = {};
-  if (MODE >= 0 && xf.on) io.load(MODE <= 1 ? a.uhat : a.acc, of, xa, xb);
+  CombineIn<T> in = {};
+  if (MODE >= 0 && xf.on) {
+    io.load(MODE <= 1 ? a.uhat : a.acc, of, in.x1[0], in.x1[1]);
+    wave_combine_in<MODE, FLY>(io, a, xf.rb, in);
+  }
   xf.pair_rows(ma, mb);
   float lz[2][4] = {}, lxy = 0.f;
   T kt = T(0), ha = T(0);
@@ -2300,7 +2320,7 @@ __global__ __launch_bounds__(64 * NB) void k_gz(StageArgs<T> a, WaveAxis ax, Wav
   }
   if (MODE >= 0 || !a.src) xf.pair_shared(smem, 0, ma, mb, va, vb);
   if constexpr (MODE >= 0) {
-    if (xf.on) wave_combine<MODE, FLY>(w, io, a, xf.rb, lxy, kt, ha, lz, xa, xb, va, vb);
+    if (xf.on) wave_combine_out<MODE, FLY>(io, a, xf.rb, lxy, kt, ha, lz, in, va, vb);
   } else {
     if (a.mode == MODE_INIT && xf.on) io.store(a.uhat, of, va, vb);
 #pragma unroll
@@ -2398,8 +2418,8 @@ __global__ __launch_bounds__(64 * NB) void k_gzadj(StageArgs<T> a, WaveAxis ax, 
         acc[3] += ln.o == 0 ? 0.0 : sa;
       }
     } else {
-      wave_adj_tab<0>(w, io, a, xf.rb, va);
-      wave_adj_tab<1>(w, io, a, xf.rb, vb);
+      wave_adj_tab<0>(io, a, xf.rb, va);
+      wave_adj_tab<1>(io, a, xf.rb, vb);
     }
   }
   xf.pair_shared(smem, 1, ma, mb, va, vb);
