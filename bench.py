@@ -430,9 +430,9 @@ def main() -> int:
     t_dom, n_dom = prof[dom]
     avg_ms = t_dom / n_dom
     achieved = algorithmic_bytes(dom, S, n, w32) / (avg_ms * 1e-3) / 1e9
-    kernel_names = {"X": "k_xstage_m<float> (inverse-x, reaction, forward-x)",
-                    "Y": "k_single_m<float> (y transform)",
-                    "Z": "k_zstage_m<float> (forward-z, stage combine, inverse-z; four stage "
+    kernel_names = {"X": "k_wx<float> (inverse-x, reaction, forward-x)",
+                    "Y": "k_wsy2 (y transform)",
+                    "Z": "k_wz<float> (forward-z, stage combine, inverse-z; four stage "
                          "kernels)"}
     traffic = None
     tfile = os.path.join(ROOT, "profiles", f"traffic_{wl.name}_f32.json")

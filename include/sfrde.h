@@ -25,10 +25,10 @@
  *   of the plan's dtype, x contiguous; ensemble plans (sfrde_plan_batch) put
  *   the member first, [B][S][...]. Sizes are *unknowns* per axis: N = n
  *   (periodic), n + 1 (Dirichlet), n - 1 (Neumann) intervals with spacing h.
- * - Every transform runs in hand-written kernels: axes of up to 256 points
- *   (255 periodic) on the matrix cores, periodic axes of 256, 512 and 1024
- *   points as radix-8/4 FFTs in LDS, any other axis (up to 1024 points) as a
- *   dense product in LDS; each fused with the same pointwise stages.
+ * - Every transform runs in hand-written kernels: axes of up to 512 points on
+ *   the matrix cores, periodic axes of 256, 512 and 1024 points as radix-8/4
+ *   FFTs in registers, any other axis (up to 1024 points) as a dense product in
+ *   LDS; each fused with the same pointwise stages.
  * - n[0] is the x (fastest) extent, n[1] y, n[2] z; h[] in the same order.
  * - The caller owns every buffer passed in (state, checkpoints, gradients)
  *   and the stream; the library never frees caller memory. The plan owns its

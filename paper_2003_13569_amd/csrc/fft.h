@@ -334,6 +334,27 @@ struct FftCols {
 #pragma unroll
     for (int r = 0; r < 4; ++r) f[o[r]] = v[r];
   }
+  // (private arrays of the stage combines have the fields' order here)
+  template <typename U>
+  __device__ __forceinline__ void load_priv(const U* f, int, const Off& o, U (&va)[4], U (&vb)[4]) const {
+    load(f, o, va, vb);
+  }
+  template <typename U>
+  __device__ __forceinline__ void store_priv(U* f, int, const Off& o, const U (&va)[4], const U (&vb)[4]) const {
+    store(f, o, va, vb);
+  }
+  template <int SIDE, typename U>
+  __device__ __forceinline__ void load_priv1(const U* f, int, const long long (&o)[4], U (&v)[4]) const {
+    load1(f, o, v);
+  }
+  template <int SIDE, typename U>
+  __device__ __forceinline__ void store_priv1(U* f, int, const long long (&o)[4], const U (&v)[4]) const {
+    store1(f, o, v);
+  }
+  template <int SIDE, typename U>
+  __device__ __forceinline__ void store_priv_rmw(U* f, int rb, const long long (&o)[4], const U (&v)[4]) const {
+    store_rmw<SIDE>(f, o, v, rb);
+  }
   // an array that this pass also read: a repeated last column (b on a) is
   // written from side a only
   template <int SIDE, typename U>

@@ -1,7 +1,7 @@
 // libsfrde: host plan, step drivers and the C ABI declared in include/sfrde.h.
 //
-// A plan holds, on the device: per-axis transform data (matrix-core
-// fragments, FFT twiddles or dense matrices, built in FP64 on the host from
+// A plan holds, on the device: per-axis transform data (half matrices of
+// the matrix-core engine, FFT twiddles or dense matrices, built in FP64 on the host from
 // the closed forms of Section 3.1), per-axis FP64
 // eigenvalue tables, the six coefficient tables of the Alg. 1 precompute
 // (computed in FP64 on the device, stored in dtype), and the workspace of the
@@ -130,7 +130,7 @@ struct sfrde_plan_s {
   WaveTiles wtl[3]{};
   void* wA[3] = {nullptr, nullptr, nullptr};
   bool lfly = false;     // Z kernels of the wave engine form L from the eigenvalues
-  // long periodic axes of 256, 512 or 1024 points: FFT tile kernels (fft.h)
+  // periodic axes of 256, 512 or 1024 points: FFT kernels (fft.h)
   bool use_f[3] = {false, false, false};
   FftPairs fft[3]{};
   unsigned wpb_f[3] = {0, 0, 0};  // wavefronts per block
@@ -376,6 +376,7 @@ int wave_class_info(int c, const WaveClass** out) {
     fill_wave_classes(tab);
     filled = true;
   }
+  if (!tab[c].k.nb) return fail(SFRDE_EDEVICE, "this build holds no matrix-core kernels");
   if (!known[c]) {
     for (int i = 0; i < WK_COUNT; ++i) {
       if (!tab[c].k.fn[i]) continue;
@@ -511,7 +512,13 @@ int setup_wave_axis(sfrde_plan_s* p, int axis) {
   t.cpsh = p->S == 1 ? 4 : p->S == 2 ? 3 : 2;
   const long long per = axis == 0 ? 1LL << t.cpsh : 16;
   t.ntiles = (int)((lines + per - 1) / per);
-  t.priv = layout == WL_EXACT && (p->S == 1 || p->S == 2 || p->S == 4) && lines % per == 0;
+  // (x tiles of three species have a column to spare)
+  t.priv = layout == WL_EXACT && (axis > 0 || p->S != 3) && lines % per == 0;
+  // FP32 fields past 96 MB (the caches keep nothing from pass to pass): a step of
+  // 256^3 1.31 ms by the sweep, 1.40 by runs; 256 x 256 x 128 (67 MB) 683 / 678 us,
+  // 192^3 (57 MB) 671 / 587; FP64 rows are twice as long, 256^3 7.23 / 7.12 ms
+  t.sweep = p->dtype == SFRDE_F32 &&
+            (long long)p->S * p->total * p->B * (long long)sizeof(float) > (96LL << 20);
   const int RS = 16 * nb;
   // axes of one length share a table
   for (int b = 0; b < axis && !x.A; ++b)

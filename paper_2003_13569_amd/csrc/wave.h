@@ -122,20 +122,52 @@ struct WaveTiles {
   long long inner;
   int ntiles;
   int cpsh;
-  int priv;       // x axis: stage values are stored in register order (every column in use)
+  // Register order (exact axes, every column in use): a tile is contiguous, row
+  // block after row block, of each side a and side b, of each the lanes' four
+  // values. x axis: stored stage values; last axis: the spectral arrays that live
+  // within a step (private), all but u_hat.
+  int priv;
+  int sweep;  // WaveRun
 };
 
-// The tiles of a block: a contiguous run, balanced over the grid, which its
-// waves take in turn. With fewer tiles than blocks x waves the blocks (and so
-// the CUs) fill first.
+// The tiles of a wave. Fields that the caches hold: a contiguous run of tiles per
+// block, which its waves take in turn (the passes along x and y meet the same
+// rows on the same XCD); with fewer tiles than waves the blocks (and so the CUs)
+// fill first. Larger fields (sweep): the grid goes through the tiles front to
+// back, so that what is in flight at a time is contiguous in memory, and the
+// waves of a block start a tile together where a kernel asks for it by sync()
+// (strided axes: together they touch 512 bytes to 1 KB of a row, each alone 64
+// to 128).
 struct WaveRun {
-  int t, t1;
-  __device__ __forceinline__ explicit WaveRun(int ntiles) {
-    const int t0 = (int)((long long)blockIdx.x * ntiles / gridDim.x);
-    t1 = (int)(((long long)blockIdx.x + 1) * ntiles / gridDim.x);
-    t = t0 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  int t, t1, rounds, stride;
+  __device__ __forceinline__ explicit WaveRun(const WaveTiles& tl) : WaveRun(tl, tl.ntiles) {}
+  __device__ __forceinline__ WaveRun(const WaveTiles& tl, int ntiles) {
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int waves = (int)(blockDim.x >> 6), all = (int)gridDim.x * waves;
+    if (tl.sweep && ntiles > all) {
+      t = (int)blockIdx.x * waves + w;
+      t1 = ntiles;
+      stride = all;
+      rounds = (ntiles - (int)blockIdx.x * waves + all - 1) / all;
+    } else {
+      t = (int)((long long)blockIdx.x * ntiles / gridDim.x) + w;
+      t1 = (int)(((long long)blockIdx.x + 1) * ntiles / gridDim.x);
+      stride = waves;
+      rounds = 0;
+    }
   }
-  __device__ __forceinline__ static int step() { return (int)(blockDim.x >> 6); }
+  __device__ __forceinline__ int step() const { return stride; }
+  __device__ __forceinline__ void sync() const {
+    if (rounds > 0) __builtin_amdgcn_s_barrier();
+  }
+  // a round of N sync() calls done
+  __device__ __forceinline__ void done() { --rounds; }
+  // the barriers of the rounds that this wave has no tile in
+  template <int N>
+  __device__ __forceinline__ void drain() {
+    for (; rounds > 0; --rounds)
+      for (int k = 0; k < N; ++k) __builtin_amdgcn_s_barrier();
+  }
 };
 
 // Maximum over the four lanes of a column (l, l ^ 16, l ^ 32, l ^ 48).
@@ -631,72 +663,138 @@ struct PosOff {
 };
 
 // Row access of a strided column: both sides of row block rb, va[r] and vb[r].
+// A row's address is a scalar base and a 32-bit offset per lane. Exact axes: the
+// row block is part of the scalar base, and a lane's eight offsets are the same
+// in every row block and array (formed once per tile, no vector arithmetic per
+// access); others form them per row block, clamped to the last position.
 template <typename T, class XF>
 struct RowIO {
   const XF& xf;
   long long base;
   PosOff<XF> po;
-  __device__ __forceinline__ RowIO(const XF& xf_, const WaveTiles& tl, const StridedLane<T>& ln)
-      : xf(xf_), base(ln.base), po(xf_, (unsigned)tl.inner * (unsigned)sizeof(T), ln.off) {}
-  // byte offsets of a row block's rows
-  struct Off {
-    unsigned a[4], b[4];
+  struct Side {
+    unsigned v[4];          // bytes, per lane
+    unsigned long long rb;  // bytes of the row block (uniform)
   };
+  struct Off {
+    Side a, b;
+  };
+  unsigned la, lb;  // exact axes: row block 0 of side a, the last of side b
+  bool priv;        // private arrays in register order
+  long long pbase;  // element offset of the tile there (uniform)
+  __device__ __forceinline__ RowIO(const XF& xf_, const WaveTiles& tl, const StridedLane<T>& ln,
+                                   int tile = 0, bool priv_ = false)
+      : xf(xf_), base(ln.base), po(xf_, (unsigned)tl.inner * (unsigned)sizeof(T), ln.off),
+        priv(XF::EXACT && priv_), pbase((long long)tile * (16 * 32 * XF::NBLK)) {
+    la = po.a0 + po.lane;
+    lb = po.b0 - (unsigned)(16 * (XF::NBLK - 1)) * po.step - po.lane;
+  }
   __device__ __forceinline__ Off offs(int rb) const {
     Off o;
-    const unsigned l = po.opaque();
+    if constexpr (XF::EXACT) {
+      // (opaque copies: offsets are formed where they are used; kept, they would
+      // fill the register file)
+      unsigned xa = la, xb = lb;
+      asm volatile("" : "+v"(xa), "+v"(xb));
 #pragma unroll
-    for (int r = 0; r < 4; ++r) po.at(l, rb, r, o.a[r], o.b[r]);
+      for (int r = 0; r < 4; ++r) {
+        o.a.v[r] = xa + (unsigned)(XF::PR * r) * po.step;
+        o.b.v[r] = xb - (unsigned)(XF::PR * r) * po.step;
+      }
+      o.a.rb = (unsigned long long)(16 * rb) * po.step;
+      o.b.rb = (unsigned long long)(16 * (XF::NBLK - 1 - rb)) * po.step;
+    } else {
+      const unsigned l = po.opaque();
+#pragma unroll
+      for (int r = 0; r < 4; ++r) po.at(l, rb, r, o.a.v[r], o.b.v[r]);
+      o.a.rb = o.b.rb = 0;
+    }
     return o;
   }
-  // (base is uniform: a scalar base and a 32-bit offset per lane)
+  template <typename U>
+  __device__ __forceinline__ const char* at(const U* f, const Side& o) const {
+    return reinterpret_cast<const char*>(f + base) + o.rb * (sizeof(U) / sizeof(T));
+  }
+  template <typename U>
+  __device__ __forceinline__ char* at(U* f, const Side& o) const {
+    return reinterpret_cast<char*>(f + base) + o.rb * (sizeof(U) / sizeof(T));
+  }
   template <typename U>
   __device__ __forceinline__ void load(const U* f, const Off& o, U (&va)[4], U (&vb)[4]) const {
-    const char* p = reinterpret_cast<const char*>(f + base);
-    constexpr unsigned k = sizeof(U) / sizeof(T);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) va[r] = *reinterpret_cast<const U*>(p + o.a[r] * k);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) vb[r] = *reinterpret_cast<const U*>(p + o.b[r] * k);
+    load1(f, o.a, va);
+    load1(f, o.b, vb);
   }
   // (columns past the last line repeat it and store the same values again)
   template <typename U>
   __device__ __forceinline__ void store(U* f, const Off& o, const U (&va)[4], const U (&vb)[4]) const {
-    char* p = reinterpret_cast<char*>(f + base);
-    constexpr unsigned k = sizeof(U) / sizeof(T);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) *reinterpret_cast<U*>(p + o.a[r] * k) = va[r];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) *reinterpret_cast<U*>(p + o.b[r] * k) = vb[r];
+    store1(f, o.a, va);
+    store1(f, o.b, vb);
   }
   template <typename U>
-  __device__ __forceinline__ void load1(const U* f, const unsigned (&o)[4], U (&v)[4]) const {
-    const char* p = reinterpret_cast<const char*>(f + base);
+  __device__ __forceinline__ void load1(const U* f, const Side& o, U (&v)[4]) const {
+    const char* p = at(f, o);
     constexpr unsigned k = sizeof(U) / sizeof(T);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) v[r] = *reinterpret_cast<const U*>(p + o[r] * k);
+    for (int r = 0; r < 4; ++r) v[r] = *reinterpret_cast<const U*>(p + o.v[r] * k);
   }
   template <typename U>
-  __device__ __forceinline__ void store1(U* f, const unsigned (&o)[4], const U (&v)[4]) const {
-    char* p = reinterpret_cast<char*>(f + base);
+  __device__ __forceinline__ void store1(U* f, const Side& o, const U (&v)[4]) const {
+    char* p = at(f, o);
     constexpr unsigned k = sizeof(U) / sizeof(T);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) *reinterpret_cast<U*>(p + o[r] * k) = v[r];
+    for (int r = 0; r < 4; ++r) *reinterpret_cast<U*>(p + o.v[r] * k) = v[r];
   }
   // store of an array that this pass also read: side b of a row block is
   // loaded after side a is stored, so a point that stands on both sides is
   // written from side a only
   template <int SIDE, typename U>
-  __device__ __forceinline__ void store_rmw(U* f, const unsigned (&o)[4], const U (&v)[4], int rb) const {
+  __device__ __forceinline__ void store_rmw(U* f, const Side& o, const U (&v)[4], int rb) const {
     if (XF::EXACT || SIDE == 0) {
       store1(f, o, v);
       return;
     }
-    char* p = reinterpret_cast<char*>(f + base);
+    char* p = at(f, o);
     constexpr unsigned k = sizeof(U) / sizeof(T);
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-      if (xf.vb(rb, r)) *reinterpret_cast<U*>(p + o[r] * k) = v[r];
+      if (xf.vb(rb, r)) *reinterpret_cast<U*>(p + o.v[r] * k) = v[r];
+  }
+  // ---- private arrays
+  struct alignas(sizeof(T) * 2) Vec { T v[4]; };
+  __device__ __forceinline__ long long at_priv(int rb, int side) const {
+    return pbase + 512 * rb + 256 * side + 4 * (long long)(threadIdx.x & 63);
+  }
+  template <int SIDE>
+  __device__ __forceinline__ void load_priv1(const T* f, int rb, const Side& o, T (&v)[4]) const {
+    if (priv) {
+      const Vec u = *reinterpret_cast<const Vec*>(f + at_priv(rb, SIDE));
+#pragma unroll
+      for (int r = 0; r < 4; ++r) v[r] = u.v[r];
+    } else {
+      load1(f, o, v);
+    }
+  }
+  template <int SIDE>
+  __device__ __forceinline__ void store_priv1(T* f, int rb, const Side& o, const T (&v)[4]) const {
+    if (priv)
+      *reinterpret_cast<Vec*>(f + at_priv(rb, SIDE)) = Vec{{v[0], v[1], v[2], v[3]}};
+    else
+      store1(f, o, v);
+  }
+  template <int SIDE>
+  __device__ __forceinline__ void store_priv_rmw(T* f, int rb, const Side& o, const T (&v)[4]) const {
+    if (priv)
+      store_priv1<SIDE>(f, rb, o, v);
+    else
+      store_rmw<SIDE>(f, o, v, rb);
+  }
+  __device__ __forceinline__ void load_priv(const T* f, int rb, const Off& o, T (&va)[4], T (&vb)[4]) const {
+    load_priv1<0>(f, rb, o.a, va);
+    load_priv1<1>(f, rb, o.b, vb);
+  }
+  __device__ __forceinline__ void store_priv(T* f, int rb, const Off& o, const T (&va)[4], const T (&vb)[4]) const {
+    store_priv1<0>(f, rb, o.a, va);
+    store_priv1<1>(f, rb, o.b, vb);
   }
   __device__ __forceinline__ void load_all(const T* f, typename XF::Vals& ya,
                                            typename XF::Vals& yb) const {
@@ -1004,6 +1102,8 @@ struct StageIn {
 
 // X: inverse-x, reaction, forward-x (in place on P). SRC: the reactions with a
 // manufactured source (a kernel of their own: the source is a long function).
+// Bound at 256^3 FP32 by its chain at two waves per SIMD (244 registers): 86 us
+// (3.1 TB/s), 99 in the phases of an 8-wave block; 128^3 FP32 33 -> 15.5 us.
 template <typename T, int NB, int LAY, bool SRC>
 __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wx(StageArgs<T> a, WaveAxis ax, WaveTiles tl) {
   to_member(a);
@@ -1012,7 +1112,7 @@ __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wx(StageArgs<T> a, 
   const XF xf(ax, smem);
   const long long total = a.g.total;
   bool bad = false;
-  WaveRun run(tl.ntiles);
+  WaveRun run(tl);
   typename XF::Vals ya, yb;
   auto load = [&](int tile) {
     const XLane<T> ln(tl, a.S, tile, xf.i);
@@ -1045,7 +1145,7 @@ __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wsx(SingleArgs<T> a
   using XF = WaveXf<T, NB, LAY>;
   const XF xf(ax, smem);
   const long long total = a.g.total;
-  WaveRun run(tl.ntiles);
+  WaveRun run(tl);
   typename XF::Vals ya, yb;
   auto load = [&](int tile) {
     const XLane<T> ln(tl, a.S, tile, xf.i);
@@ -1089,7 +1189,7 @@ __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wsy(SingleArgs<T> a
   extern __shared__ __align__(16) char smem[];
   using XF = WaveXf<T, NB, LAY>;
   const XF xf(ax, smem);
-  WaveRun run(tl.ntiles);
+  WaveRun run(tl);
   typename XF::Vals ya, yb;
   auto load = [&](int tile) {
     const StridedLane<T> ln(tl, xf.n(), tile, xf.i);
@@ -1099,6 +1199,7 @@ __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wsy(SingleArgs<T> a
   xf.copy_table(smem);
   __syncthreads();
   for (int tile = run.t; tile < run.t1;) {
+    run.sync();
     const StridedLane<T> ln(tl, xf.n(), tile, xf.i);
     const RowIO<T, XF> io(xf, tl, ln);
     const int next = tile + run.step();
@@ -1108,38 +1209,43 @@ __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wsy(SingleArgs<T> a
           io.store(a.dst, io.offs(decltype(rbc)::value), va, vb);
         });
     tile = next;
+    run.done();
   }
+  run.drain<1>();
 }
 
 // The same for FP32 with two columns per lane (32 lines per wave; inner even:
 // both lie in one outer block): every matrix fragment read from LDS serves two
 // products, and rows move in 128-byte pieces, 8 bytes per lane. One transform
-// needs no registers beside the operands, so the second column fits.
+// needs no registers beside the operands, so the second column fits. Memory
+// bound: 256^3 54 us (4.9 TB/s; one column per lane 66), 128^3 9.7 us.
 template <int NB, int LAY>
 __global__ __launch_bounds__(512) void k_wsy2(SingleArgs<float> a, WaveAxis ax, WaveTiles tl) {
   to_member(a);
   extern __shared__ __align__(16) char smem[];
   using XF = WaveXf<float, NB, LAY>;
   const XF xf(ax, smem);
-  WaveRun run(tl.ntiles);
+  WaveRun run(tl);
   xf.copy_table(smem);
   __syncthreads();
   for (int tile = run.t; tile < run.t1; tile += run.step()) {
+    run.sync();
     const StridedLane<float> ln(tl, xf.n(), tile, xf.i, 2u);
     const RowIO<float, XF> io(xf, tl, ln);
     typename XF::Ops o[2];
     {
       typename XF::Vals ya[2], yb[2];
-      const char* p = reinterpret_cast<const char*>(a.src + io.base);
 #pragma unroll
       for (int rb = 0; rb < NB; ++rb) {
         f32x2 va[4] = {}, vb[4] = {};
         if (xf.used(rb)) {
           const auto of = io.offs(rb);
 #pragma unroll
-          for (int r = 0; r < 4; ++r) va[r] = *reinterpret_cast<const f32x2u*>(p + of.a[r]);
+          for (int r = 0; r < 4; ++r)
+            va[r] = *reinterpret_cast<const f32x2u*>(io.at(a.src, of.a) + of.a.v[r]);
 #pragma unroll
-          for (int r = 0; r < 4; ++r) vb[r] = *reinterpret_cast<const f32x2u*>(p + of.b[r]);
+          for (int r = 0; r < 4; ++r)
+            vb[r] = *reinterpret_cast<const f32x2u*>(io.at(a.src, of.b) + of.b.v[r]);
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r)
@@ -1156,7 +1262,6 @@ __global__ __launch_bounds__(512) void k_wsy2(SingleArgs<float> a, WaveAxis ax, 
     unsigned lnat = xf.lnat, lrev = xf.lrev;
     asm volatile("" : "+v"(lnat), "+v"(lrev));
     __builtin_amdgcn_sched_barrier(0);
-    char* q = reinterpret_cast<char*>(a.dst + io.base);
     static_for<NB>([&](auto rbc) {
       constexpr int rb = decltype(rbc)::value;
       if (!xf.used(rb)) return;
@@ -1170,11 +1275,13 @@ __global__ __launch_bounds__(512) void k_wsy2(SingleArgs<float> a, WaveAxis ax, 
       const auto of = io.offs(rb);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        *reinterpret_cast<f32x2u*>(q + of.a[r]) = f32x2u{va[0][r], va[1][r]};
-        *reinterpret_cast<f32x2u*>(q + of.b[r]) = f32x2u{vb[0][r], vb[1][r]};
+        *reinterpret_cast<f32x2u*>(io.at(a.dst, of.a) + of.a.v[r]) = f32x2u{va[0][r], va[1][r]};
+        *reinterpret_cast<f32x2u*>(io.at(a.dst, of.b) + of.b.v[r]) = f32x2u{vb[0][r], vb[1][r]};
       }
     });
+    run.done();
   }
+  run.drain<1>();
 }
 
 // Last-axis eigenvalues in position order for L formed in the kernel:
@@ -1245,7 +1352,7 @@ __device__ __forceinline__ void wave_combine_in(const IO& io, const StageArgs<T>
       if (MODE == 0) io.load(a.coef + C_PHI1 * cst, of, in.t3[0], in.t3[1]);
     }
   }
-  if (MODE == 1 || MODE == 2) io.load(MODE == 1 ? a.acc : a.ctil, of, in.x2[0], in.x2[1]);
+  if (MODE == 1 || MODE == 2) io.load_priv(MODE == 1 ? a.acc : a.ctil, rb, of, in.x2[0], in.x2[1]);
 }
 
 // Stage combine (MODE 0..3) of a row block, both sides.
@@ -1299,25 +1406,26 @@ __device__ __forceinline__ void wave_combine_out(const IO& io, const StageArgs<T
       v = a.cs * out;
     }
   }
-  if (MODE == 0) {
-    if (a.st_uhat) io.store(a.st_uhat, of, in.x1[0], in.x1[1]);
-    io.store(a.ctil, of, o0[0], o0[1]);
-  }
-  if (a.st_fhat) io.store(a.st_fhat + MODE * cst, of, fh[0], fh[1]);
-  if (MODE <= 2) io.store(a.acc, of, o1[0], o1[1]);
+  if (MODE == 0) io.store_priv(a.ctil, rb, of, o0[0], o0[1]);
+  if (a.st_fhat) io.store_priv(a.st_fhat + MODE * cst, rb, of, fh[0], fh[1]);
+  if (MODE <= 2) io.store_priv(a.acc, rb, of, o1[0], o1[1]);
   if (MODE == 3) io.store(a.uhat, of, o0[0], o0[1]);
 }
 
 // Z: forward transform along the last axis, stage combine, inverse transform
 // (in place on P). MODE 0..3; MODE < 0: MODE_INIT or MODE_RESTORE (a.mode).
-// FLY: L formed in the kernel from the eigenvalues (FP32 P13 plans).
+// FLY: L formed in the kernel from the eigenvalues (FP32 P13 plans). Memory
+// bound at 256^3 FP32, on 64-byte rows at 256 KB strides: 3.5 TB/s over five
+// fields in stage 0 with every array in the fields' order; with c_tilde and acc
+// in register order and the sweep a step went 1.43 -> 1.34 ms (1.43 in 8-wave
+// blocks on the same GPU). 128^3 FP32 33 -> 18 us per stage.
 template <typename T, int NB, int LAY, int MODE, bool FLY>
 __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wz(StageArgs<T> a, WaveAxis ax, WaveTiles tl) {
   to_member(a);
   extern __shared__ __align__(16) char smem[];
   using XF = WaveXf<T, NB, LAY>;
   const XF xf(ax, smem);
-  WaveRun run(tl.ntiles);
+  WaveRun run(tl);
   typename XF::Vals ya, yb;
   const T* src = a.src ? a.src : a.P;
   auto load = [&](int tile) {
@@ -1330,13 +1438,21 @@ __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wz(StageArgs<T> a, 
   if constexpr (FLY) fill_lam(xf, a, lam);
   __syncthreads();
   for (int tile = run.t; tile < run.t1;) {
+    run.sync();
     const StridedLane<T> ln(tl, xf.n(), tile, xf.i);
-    const RowIO<T, XF> io(xf, tl, ln);
+    const RowIO<T, XF> io(xf, tl, ln, tile, FLY || tl.priv);
     if constexpr (MODE >= 0) {
       // the first retained array, in flight over the transform (FP32)
       typename XF::Vals xa, xb;
-      const T* x1 = MODE <= 1 ? a.uhat : a.acc;
-      if constexpr (XF::F32) io.load_all(x1, xa, xb);
+      auto load_x1 = [&](auto rbc) {
+        constexpr int rb = decltype(rbc)::value;
+        if (!xf.used(rb)) return;
+        if (MODE <= 1)
+          io.load(a.uhat, io.offs(rb), xa[rb], xb[rb]);
+        else
+          io.load_priv(a.acc, rb, io.offs(rb), xa[rb], xb[rb]);
+      };
+      if constexpr (XF::F32) static_for<NB>(load_x1);
       xf.pair(ya, yb);
       float lxy = 0.f;
       T kt = T(0), ha = T(0);
@@ -1349,7 +1465,7 @@ __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wz(StageArgs<T> a, 
       static_for<NB>([&](auto rbc) {
         constexpr int rb = decltype(rbc)::value;
         if (!xf.used(rb)) return;
-        if constexpr (!XF::F32) io.load(x1, io.offs(rb), xa[rb], xb[rb]);
+        if constexpr (!XF::F32) load_x1(rbc);
         float lz[2][4] = {};
         if constexpr (FLY) {
           lam_z(xf, lam, 0, rb, lz[0]);
@@ -1386,6 +1502,7 @@ __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wz(StageArgs<T> a, 
           keep(yb[rb][r]);
         }
     }
+    run.sync();
     const int next = tile + run.step();
     xf.pair_each(
         ya, yb, [&] { if (next < run.t1) load(next); },
@@ -1393,7 +1510,9 @@ __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wz(StageArgs<T> a, 
           io.store(a.P, io.offs(decltype(rbc)::value), va, vb);
         });
     tile = next;
+    run.done();
   }
+  run.drain<2>();
 }
 
 // ------------------------------------------------------------------ adjoint
@@ -1504,7 +1623,7 @@ __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wxadj(StageArgs<T> 
 #pragma unroll
   for (int k = 0; k < RXN_NP_MAX; ++k) pacc[k] = 0.0;
   const T* st = a.st_phys + (long long)a.mode * a.S * total;
-  WaveRun run(tl.ntiles);
+  WaveRun run(tl);
   typename XF::Vals ya, yb;
   auto load = [&](int tile) {
     const XLane<T> ln(tl, a.S, tile, xf.i);
@@ -1581,30 +1700,42 @@ __device__ __forceinline__ float lambda_power(float lam, float ha, float& lg) {
 // weight, then by dL/dkappa = tau Lambda^(alpha/2) and dL/dalpha =
 // L ln(Lambda) / 2, summed per lane and row block in FP32 and beyond in FP64.
 // wxy: cs times the x and y spectral weights of the column.
+// in: what it reads, loaded ahead (wave_adj_fly_in).
+struct AdjIn {
+  float z[4], h[4], c4[4], u[4], f0[4], f1[4], f2[4], f3[4];
+};
+template <int MODE, bool TH, int SIDE, class XF>
+__device__ __forceinline__ void wave_adj_fly_in(const RowIO<float, XF>& io,
+                                                const StageArgs<float>& a, int rb, AdjIn& in) {
+  const long long cst = (long long)a.S * a.g.total;
+  const auto ofs = io.offs(rb);
+  const auto& of = SIDE ? ofs.b : ofs.a;
+  if (MODE <= 1) io.template load_priv1<SIDE>(a.zh, rb, of, in.z);
+  if (MODE >= 1 && MODE <= 3) io.template load_priv1<SIDE>(a.aacc, rb, of, in.c4);
+  if (MODE == 2) {
+    io.template load_priv1<SIDE>(a.ahat, rb, of, in.h);
+    io.template load_priv1<SIDE>(a.gu, rb, of, in.z);
+  }
+  if (TH && MODE <= 2) {
+    io.load1(a.st_uhat, of, in.u);
+    if (MODE == 0 || MODE == 2) io.template load_priv1<SIDE>(a.st_fhat, rb, of, in.f0);
+    if (MODE == 0 || MODE == 1) io.template load_priv1<SIDE>(a.st_fhat + cst, rb, of, in.f1);
+    if (MODE == 0) {
+      io.template load_priv1<SIDE>(a.st_fhat + 2 * cst, rb, of, in.f2);
+      io.template load_priv1<SIDE>(a.st_fhat + 3 * cst, rb, of, in.f3);
+    }
+  }
+}
 template <int MODE, bool TH, int SIDE, class XF>
 __device__ __forceinline__ void wave_adj_fly(const XF& xf, const RowIO<float, XF>& io,
                                              const StageArgs<float>& a, int rb, float lxy,
                                              float wxy, float kt, float ha,
-                                             const float (&lz)[4], float (&v4)[4], double& sk, double& sa) {
-  const long long cst = (long long)a.S * a.g.total;
+                                             const float (&lz)[4], const AdjIn& in, float (&v4)[4],
+                                             double& sk, double& sa) {
   const auto ofs = io.offs(rb);
   const auto& of = SIDE ? ofs.b : ofs.a;
-  float z[4], h[4], c4[4], u[4], f0[4], f1[4], f2[4], f3[4];
-  if (MODE <= 1) io.load1(a.zh, of, z);
-  if (MODE >= 1 && MODE <= 3) io.load1(a.aacc, of, c4);
-  if (MODE == 2) {
-    io.load1(a.ahat, of, h);
-    io.load1(a.gu, of, z);
-  }
-  if (TH && MODE <= 2) {
-    io.load1(a.st_uhat, of, u);
-    if (MODE == 0 || MODE == 2) io.load1(a.st_fhat, of, f0);
-    if (MODE == 0 || MODE == 1) io.load1(a.st_fhat + cst, of, f1);
-    if (MODE == 0) {
-      io.load1(a.st_fhat + 2 * cst, of, f2);
-      io.load1(a.st_fhat + 3 * cst, of, f3);
-    }
-  }
+  const auto &z = in.z, &h = in.h, &c4 = in.c4, &u = in.u;
+  const auto &f0 = in.f0, &f1 = in.f1, &f2 = in.f2, &f3 = in.f3;
   float o1[4], o2[4], o3[4];
   float ak = 0.f, aa = 0.f;
   {
@@ -1662,13 +1793,13 @@ __device__ __forceinline__ void wave_adj_fly(const XF& xf, const RowIO<float, XF
     }
   }
   if (MODE == 0) {
-    io.store1(a.aacc, of, o1);
-    io.store1(a.ahat, of, o2);
-    io.store1(a.gu, of, o3);
+    io.template store_priv1<SIDE>(a.aacc, rb, of, o1);
+    io.template store_priv1<SIDE>(a.ahat, rb, of, o2);
+    io.template store_priv1<SIDE>(a.gu, rb, of, o3);
   } else if (MODE <= 2) {
-    io.template store_rmw<SIDE>(a.aacc, of, o1, rb);
+    io.template store_priv_rmw<SIDE>(a.aacc, rb, of, o1);
   } else {
-    io.store1(a.zh, of, o1);
+    io.template store_priv1<SIDE>(a.zh, rb, of, o1);
   }
   if (TH && MODE <= 2) {
     keep(ak);
@@ -1706,7 +1837,7 @@ __device__ __forceinline__ void wave_adj_tab(const IO& io, const StageArgs<T>& a
   };
   if (mode == 0) {
     T z[4], R[4], Q[4], P[4], P1[4], P2[4];
-    io.load1(a.zh, of, z);
+    io.template load_priv1<SIDE>(a.zh, rb, of, z);
     if (!from_l) {
       coef(C_R, R);
       coef(C_Q, Q);
@@ -1719,10 +1850,10 @@ __device__ __forceinline__ void wave_adj_tab(const IO& io, const StageArgs<T>& a
     double G[4];
     if (a.G) {
       io.load1(a.st_uhat, of, uh);
-      io.load1(a.st_fhat, of, fu);
-      io.load1(a.st_fhat + cst, of, fa);
-      io.load1(a.st_fhat + 2 * cst, of, fb);
-      io.load1(a.st_fhat + 3 * cst, of, fc);
+      io.template load_priv1<SIDE>(a.st_fhat, rb, of, fu);
+      io.template load_priv1<SIDE>(a.st_fhat + cst, rb, of, fa);
+      io.template load_priv1<SIDE>(a.st_fhat + 2 * cst, rb, of, fb);
+      io.template load_priv1<SIDE>(a.st_fhat + 3 * cst, rb, of, fc);
       io.load1(a.G, of, G);
       if (!from_l) {
         dcoef(C_R, dR);
@@ -1753,17 +1884,17 @@ __device__ __forceinline__ void wave_adj_tab(const IO& io, const StageArgs<T>& a
       }
       return cP2 * zz + T(2) * cP * X;
     });
-    io.store1(a.aacc, of, o1);
-    io.store1(a.ahat, of, o2);
-    io.store1(a.gu, of, o3);
+    io.template store_priv1<SIDE>(a.aacc, rb, of, o1);
+    io.template store_priv1<SIDE>(a.ahat, rb, of, o2);
+    io.template store_priv1<SIDE>(a.gu, rb, of, o3);
     if (a.G) io.template store_rmw<SIDE>(a.G, of, G, rb);
   } else if (mode == 1 || mode == 2) {
     const bool b = mode == 1;
     // stage 1: z, aacc;  2: gu, aacc, ahat
     T z[4], c4[4], h[4], Q[4], P[4], P2[4];
-    io.load1(b ? a.zh : a.gu, of, z);
-    io.load1(a.aacc, of, c4);
-    if (!b) io.load1(a.ahat, of, h);
+    io.template load_priv1<SIDE>(b ? a.zh : a.gu, rb, of, z);
+    io.template load_priv1<SIDE>(a.aacc, rb, of, c4);
+    if (!b) io.template load_priv1<SIDE>(a.ahat, rb, of, h);
     if (!from_l) {
       coef(C_Q, Q);
       coef(C_PHI, P);
@@ -1773,7 +1904,7 @@ __device__ __forceinline__ void wave_adj_tab(const IO& io, const StageArgs<T>& a
     double G[4];
     if (a.G) {
       io.load1(a.st_uhat, of, uh);
-      io.load1(a.st_fhat + (b ? cst : 0), of, f);
+      io.template load_priv1<SIDE>(a.st_fhat + (b ? cst : 0), rb, of, f);
       io.load1(a.G, of, G);
       if (!from_l) {
         dcoef(C_Q, dQ);
@@ -1792,20 +1923,20 @@ __device__ __forceinline__ void wave_adj_tab(const IO& io, const StageArgs<T>& a
       if (b) return (from_l ? T(cl[C_PHI2]) : P2[r]) * z[r] + cP * X;
       return z[r] + cP * A;
     });
-    io.template store_rmw<SIDE>(a.aacc, of, o1, rb);
+    io.template store_priv_rmw<SIDE>(a.aacc, rb, of, o1);
     if (a.G) io.template store_rmw<SIDE>(a.G, of, G, rb);
   } else {
     // 3: z <- aacc + X;  MODE_INIT: X is the transformed cotangent of u(T)
     const bool init = mode != 3;
     T c4[4], P3[4], o1[4];
-    if (!init) io.load1(a.aacc, of, c4);
+    if (!init) io.template load_priv1<SIDE>(a.aacc, rb, of, c4);
     if (!from_l) coef(C_PHI3, P3);
     each([&](int r, T X, const double* cl, const double*) {
       const T zn = init ? X : c4[r] + X;
       o1[r] = zn;
       return !init && a.last ? zn : (from_l ? T(cl[C_PHI3]) : P3[r]) * zn;
     });
-    io.store1(a.zh, of, o1);
+    io.template store_priv1<SIDE>(a.zh, rb, of, o1);
   }
 }
 
@@ -1818,7 +1949,7 @@ __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wzadj(StageArgs<T> 
   extern __shared__ __align__(16) char smem[];
   using XF = WaveXf<T, NB, LAY>;
   const XF xf(ax, smem);
-  WaveRun run(tl.ntiles);
+  WaveRun run(tl);
   typename XF::Vals ya, yb;
   auto load = [&](int tile) {
     const StridedLane<T> ln(tl, xf.n(), tile, xf.i);
@@ -1833,7 +1964,8 @@ __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wzadj(StageArgs<T> 
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
   for (int tile = run.t; tile < run.t1;) {
     const StridedLane<T> ln(tl, xf.n(), tile, xf.i);
-    const RowIO<T, XF> io(xf, tl, ln);
+    const RowIO<T, XF> io(xf, tl, ln, tile, MODE >= 0 || tl.priv);
+    AdjIn in[2];
     xf.pair(ya, yb);
     if constexpr (MODE >= 0) {
       int x, y;
@@ -1849,10 +1981,12 @@ __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wzadj(StageArgs<T> 
         constexpr int rb = decltype(rbc)::value;
         if (!xf.used(rb)) return;
         float lz[4];
+        wave_adj_fly_in<MODE, TH, 0>(io, a, rb, in[0]);
         lam_z(xf, lam, 0, rb, lz);
-        wave_adj_fly<MODE, TH, 0>(xf, io, a, rb, lxy, wxy, kt, ha, lz, ya[rb], sk, sa);
+        wave_adj_fly<MODE, TH, 0>(xf, io, a, rb, lxy, wxy, kt, ha, lz, in[0], ya[rb], sk, sa);
+        wave_adj_fly_in<MODE, TH, 1>(io, a, rb, in[1]);
         lam_z(xf, lam, 1, rb, lz);
-        wave_adj_fly<MODE, TH, 1>(xf, io, a, rb, lxy, wxy, kt, ha, lz, yb[rb], sk, sa);
+        wave_adj_fly<MODE, TH, 1>(xf, io, a, rb, lxy, wxy, kt, ha, lz, in[1], yb[rb], sk, sa);
         __builtin_amdgcn_sched_barrier(0);
       });
       if constexpr (TH && MODE <= 2) {
@@ -2299,14 +2433,17 @@ __global__ __launch_bounds__(64 * NB) void k_gz(StageArgs<T> a, WaveAxis ax, Wav
   const XF xf(ax);
   const W& w = xf;
   const StridedLane<T> ln(tl, xf.n(), blockIdx.x, xf.i);
-  const RowIO<T, W> io(w, tl, ln);
+  const RowIO<T, W> io(w, tl, ln, blockIdx.x, FLY || tl.priv);
   const auto of = io.offs(xf.rb);
   T va[4] = {}, vb[4] = {};
   typename XF::Rows ma, mb;
   if (xf.on) io.load(a.src ? a.src : a.P, of, va, vb);
   CombineIn<T> in = {};
   if (MODE >= 0 && xf.on) {
-    io.load(MODE <= 1 ? a.uhat : a.acc, of, in.x1[0], in.x1[1]);
+    if (MODE <= 1)
+      io.load(a.uhat, of, in.x1[0], in.x1[1]);
+    else
+      io.load_priv(a.acc, xf.rb, of, in.x1[0], in.x1[1]);
     wave_combine_in<MODE, FLY>(io, a, xf.rb, in);
   }
   xf.pair_rows(ma, mb);
@@ -2389,11 +2526,18 @@ __global__ __launch_bounds__(64 * NB) void k_gzadj(StageArgs<T> a, WaveAxis ax, 
   const XF xf(ax);
   const W& w = xf;
   const StridedLane<T> ln(tl, xf.n(), blockIdx.x, xf.i);
-  const RowIO<T, W> io(w, tl, ln);
+  const RowIO<T, W> io(w, tl, ln, blockIdx.x, MODE >= 0 || tl.priv);
   const auto of = io.offs(xf.rb);
   T va[4] = {}, vb[4] = {};
   typename XF::Rows ma, mb;
   if (xf.on) io.load(a.P, of, va, vb);
+  AdjIn in[2] = {};
+  if constexpr (MODE >= 0) {
+    if (xf.on) {
+      wave_adj_fly_in<MODE, TH, 0>(io, a, xf.rb, in[0]);
+      wave_adj_fly_in<MODE, TH, 1>(io, a, xf.rb, in[1]);
+    }
+  }
   xf.pair_rows(ma, mb);
   float lz[2][4] = {}, lxy = 0.f;
   int x = 0, y = 0;
@@ -2409,8 +2553,8 @@ __global__ __launch_bounds__(64 * NB) void k_gzadj(StageArgs<T> a, WaveAxis ax, 
         if (a.n2 > 1 && (y == 0 || y == (int)a.n1 - 1)) wxy *= 0.5f;
       }
       double sk = 0.0, sa = 0.0;
-      wave_adj_fly<MODE, TH, 0>(w, io, a, xf.rb, lxy, wxy, kt, ha, lz[0], va, sk, sa);
-      wave_adj_fly<MODE, TH, 1>(w, io, a, xf.rb, lxy, wxy, kt, ha, lz[1], vb, sk, sa);
+      wave_adj_fly<MODE, TH, 0>(w, io, a, xf.rb, lxy, wxy, kt, ha, lz[0], in[0], va, sk, sa);
+      wave_adj_fly<MODE, TH, 1>(w, io, a, xf.rb, lxy, wxy, kt, ha, lz[1], in[1], vb, sk, sa);
       if constexpr (TH && MODE <= 2) {
         acc[0] += ln.o == 0 ? sk : 0.0;
         acc[1] += ln.o == 0 ? sa : 0.0;

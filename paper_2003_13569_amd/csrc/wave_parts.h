@@ -1,7 +1,9 @@
 // The size classes of the wave engine (wave.h). A class NB holds axes of up to
 // 32 NB points (n odd: 32 NB - 1, periodic: 32 NB - 1). The library is built
 // from one translation unit per class (wave_part.hip with SFRDE_PART) and the
-// host code (SFRDE_IN_PARTS); sfrde.hip alone, without either, holds them all.
+// host code (SFRDE_IN_PARTS). sfrde.hip alone, without either, holds none of them:
+// a build for checks of the host code, which refuses plans with engine axes (all
+// classes in one unit take a quarter of an hour to compile).
 #pragma once
 
 #include "wave.h"
@@ -16,8 +18,15 @@ enum {
   WC_COUNT
 };
 
+#if defined(SFRDE_PART) || defined(SFRDE_IN_PARTS)
 template <int C>
 WaveKernels wave_class();
+#else
+template <int C>
+WaveKernels wave_class() {
+  return WaveKernels{};
+}
+#endif
 
 #define SFRDE_WAVE_CLASS(C, T, NB, LAY) \
   template <>                           \
@@ -26,10 +35,8 @@ WaveKernels wave_class();
   }
 #if defined(SFRDE_PART)
 #define SFRDE_HAS(C) (SFRDE_PART == C)
-#elif defined(SFRDE_IN_PARTS)
-#define SFRDE_HAS(C) 0
 #else
-#define SFRDE_HAS(C) 1
+#define SFRDE_HAS(C) 0
 #endif
 #if SFRDE_HAS(0)
 SFRDE_WAVE_CLASS(WC_F32_2X, float, 2, WL_EXACT)
