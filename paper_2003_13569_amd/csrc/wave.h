@@ -1103,7 +1103,8 @@ struct StageIn {
 // X: inverse-x, reaction, forward-x (in place on P). SRC: the reactions with a
 // manufactured source (a kernel of their own: the source is a long function).
 // Bound at 256^3 FP32 by its chain at two waves per SIMD (244 registers): 86 us
-// (3.1 TB/s), 99 in the phases of an 8-wave block; 128^3 FP32 33 -> 15.5 us.
+// (3.1 TB/s), 99 in the phases of an 8-wave block; 128^3 FP32 27 -> 15.5 us,
+// FP64 71 -> 35.
 template <typename T, int NB, int LAY, bool SRC>
 __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wx(StageArgs<T> a, WaveAxis ax, WaveTiles tl) {
   to_member(a);
@@ -1218,7 +1219,7 @@ __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wsy(SingleArgs<T> a
 // both lie in one outer block): every matrix fragment read from LDS serves two
 // products, and rows move in 128-byte pieces, 8 bytes per lane. One transform
 // needs no registers beside the operands, so the second column fits. Memory
-// bound: 256^3 54 us (4.9 TB/s; one column per lane 66), 128^3 9.7 us.
+// bound: 256^3 54 us (4.9 TB/s; one column per lane 60), 128^3 18 -> 9.7 us.
 template <int NB, int LAY>
 __global__ __launch_bounds__(512) void k_wsy2(SingleArgs<float> a, WaveAxis ax, WaveTiles tl) {
   to_member(a);
@@ -1418,7 +1419,8 @@ __device__ __forceinline__ void wave_combine_out(const IO& io, const StageArgs<T
 // bound at 256^3 FP32, on 64-byte rows at 256 KB strides: 3.5 TB/s over five
 // fields in stage 0 with every array in the fields' order; with c_tilde and acc
 // in register order and the sweep a step went 1.43 -> 1.34 ms (1.43 in 8-wave
-// blocks on the same GPU). 128^3 FP32 33 -> 18 us per stage.
+// blocks on the same GPU; the four stages 168 to 137 us there, 158 to 124 here). 128^3 FP32 32-36 -> 18 us a
+// stage, FP64 76-85 -> 42-55.
 template <typename T, int NB, int LAY, int MODE, bool FLY>
 __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wz(StageArgs<T> a, WaveAxis ax, WaveTiles tl) {
   to_member(a);
@@ -2026,7 +2028,8 @@ __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wzadj(StageArgs<T> 
 // product, one more in FP32 for the column scale). Every product and sum is
 // the wave engine's, in its order: the results are the same bit for bit. The
 // code of a stage appears once, not once per row block, which a kernel of one
-// pass (cold instruction cache) needs most.
+// pass (cold instruction cache) needs most. Bound by that chain: 64^2 FP64 X 16.8
+// (8-wave block) -> 4.6 us, Z 12 -> 6; 256^2 FP32 X 15 -> 8.1, Z 13 -> 7.3.
 template <typename T, int NB, int LAY>
 struct GroupXf : WaveXf<T, NB, LAY> {
   using W = WaveXf<T, NB, LAY>;
