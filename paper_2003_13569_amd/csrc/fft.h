@@ -23,17 +23,22 @@
 // order, read back at l + 64 e). Nothing is shared between wavefronts: there
 // is no barrier, and the launch can be cut into blocks of any size.
 //
-// On the x axis of two-species plans the two lines are the two species of one
-// row, so the reaction is lane-local between the inverse and the forward
-// transform; on strided axes they are adjacent columns. Twiddles (cos, sin of
+// The two lines of a pair are of one species: H(a) and H(b) are separated from
+// sums of both, so each carries rounding errors of the size of the larger line
+// (with the two species of a row as a pair, a species 10^-6 of the other came
+// out 2 % off in FP32). On the x axis they are neighbouring rows, and the
+// wavefronts of a row pair's two species sit side by side in one block and show
+// each other their stage values through LDS for the reaction; on strided axes
+// they are neighbouring columns of one outer block. Twiddles (cos, sin of
 // 2 pi m / N) come from a table built in FP64 on the host.
 //
 // A launch of 512^2 points is bound by the length of one wavefront's chain
-// (512 wavefronts on 256 CUs). 512^2 Gray-Scott, FP32, per launch, against
-// blocks of 256 threads with the tile in LDS, two of four wavefronts in the FFT
-// and block barriers between stages: X 14.4 -> 6.1 us, Z 22.4 -> 12.6 us; a step
-// 155 -> 76 us (FP64 168 -> 94); 1024^2 363 -> 256 (FP64 416 -> 283); 256^3
-// 6.99 -> 4.02 ms (FP64 8.80 -> 4.84).
+// (512 wavefronts on 256 CUs). Gray-Scott steps against blocks of 256 threads
+// with the tile in LDS, two of four wavefronts in the FFT and block barriers
+// between stages: 512^2 155 -> 78 us (FP64 168 -> 97); 1024^2 363 -> 258 (FP64
+// 416 -> 290); FHN 256^3 6.99 -> 4.02 ms (FP64 8.80 -> 4.96). Showing each other
+// the stage values costs two barriers per x launch: with the two species of a
+// row as a pair these steps took 76 (94), 255 (283) us and 4.03 (4.84) ms.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -185,6 +190,23 @@ struct WaveFft {
     }
     sync();
   }
+  // This wavefront's values where the wavefront of the other species (the next
+  // or the one before in the block) finds them, and that one's values of points
+  // lane + 64 e. Between show() and seen(), and from the last seen() to the next
+  // transform: a barrier of the block.
+  __device__ __forceinline__ void show(const Vals& a, const Vals& b) const {
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      xr[at(lane + 64 * e)] = a[e];
+      xi[at(lane + 64 * e)] = b[e];
+    }
+  }
+  __device__ __forceinline__ void seen(int e, T& a, T& b) const {
+    const bool odd = (threadIdx.x >> 6) & 1;
+    const T* o = odd ? xr - 2 * PART : xr + 2 * PART;
+    a = o[at(lane + 64 * e)];
+    b = o[PART + at(lane + 64 * e)];
+  }
   // Hartley transforms of the lines in a and b, in place.
   __device__ __forceinline__ void hartley(Vals& a, Vals& b) const {
     if constexpr (N == 256) {
@@ -221,14 +243,15 @@ struct WaveFft {
   }
 };
 
-// Pairs of an axis: x axis: S = 1: lines 2q, 2q + 1; S >= 2: species 2h, 2h + 1
-// of line q / ((S + 1) / 2). Strided: columns 2q, 2q + 1 counted over every
-// outer block (species included). A last pair without a partner repeats its
-// line (and stores it twice).
+// Pairs of an axis. x axis: pair q holds lines 2k, 2k + 1 of species q mod S, k =
+// q / S (the species of one k are neighbours). Strided: pair q holds columns 2k,
+// 2k + 1 of outer block q / per, k = q mod per. A last line without a partner is
+// repeated (and stored twice).
 struct FftPairs {
-  long long lines;   // x: per species; strided: of every outer block
+  long long lines;   // x: per species
   long long inner;   // strided
   int npairs;
+  int per;           // strided: pairs per outer block
 };
 
 // The wavefront's pair, -1 past the last. Blocks are dealt to the XCDs in turn;
@@ -243,20 +266,19 @@ __device__ __forceinline__ int fft_pair(int npairs) {
 
 struct FftXPair {
   long long la, lb;  // lines
-  int sa, sb;        // species
+  int sp;            // species
   __device__ __forceinline__ FftXPair(const FftPairs& fp, int S, int q) {
-    if (S == 1) {
-      la = 2LL * q;
-      lb = la + 1 < fp.lines ? la + 1 : la;
-      sa = sb = 0;
-    } else {
-      const int h = (S + 1) / 2;
-      la = lb = q / h;
-      sa = 2 * (q % h);
-      sb = sa + 1 < S ? sa + 1 : sa;
-    }
+    const unsigned k = (unsigned)q / (unsigned)S;
+    sp = (int)((unsigned)q - k * (unsigned)S);
+    la = 2LL * k;
+    lb = la + 1 < fp.lines ? la + 1 : la;
   }
 };
+
+// Whether the reaction couples two species (their wavefronts exchange values).
+__device__ __forceinline__ bool fft_coupled(int kind) {
+  return kind >= RXN_FHN && kind <= RXN_GM;  // uniform
+}
 
 // Column pair of a strided axis, with the interface of RowIO (wave.h): "side"
 // a / b are the two columns, row block rb the points lane + 64 (4 rb + r).
@@ -266,14 +288,10 @@ struct FftCols {
   long long oa, ob, step;              // elements; step: 64 rows
   bool adj;                            // b follows a in memory
   __device__ __forceinline__ FftCols(const FftPairs& fp, int n, int q, int lane) {
-    const long long c0 = 2LL * q, c1 = c0 + 1 < fp.lines ? c0 + 1 : c0;
-    const unsigned inner = (unsigned)fp.inner;
-    const unsigned o0 = (unsigned)c0 / inner, o1 = (unsigned)c1 / inner;
-    oa = (long long)o0 * n * fp.inner + ((unsigned)c0 - o0 * inner);
-    ob = (long long)o1 * n * fp.inner + ((unsigned)c1 - o1 * inner);
-    adj = ob == oa + 1;
-    oa += lane * fp.inner;
-    ob += lane * fp.inner;
+    const unsigned o = (unsigned)q / (unsigned)fp.per, c = 2u * ((unsigned)q - o * (unsigned)fp.per);
+    adj = c + 1u < (unsigned)fp.inner;
+    oa = ((long long)o * n + lane) * fp.inner + c;
+    ob = oa + (adj ? 1 : 0);
     step = 64 * fp.inner;
   }
   struct Off {
@@ -400,27 +418,42 @@ __device__ __forceinline__ void fft_store_line(T* p, int lane, const T (&v)[E]) 
   for (int e = 0; e < E; ++e) p[lane + 64 * e] = v[e];
 }
 
-// f of the pair's stage values; true if a value was not finite.
-template <int KIND, int E, typename T>
-__device__ __forceinline__ bool fft_react(const StageArgs<T>& a, const FftXPair& pr, int n, int lane,
-                                          T (&va)[E], T (&vb)[E]) {
+// f of the pair's stage values; true if a value was not finite. Two coupled
+// species: every wavefront of the block comes here (two barriers).
+template <int KIND, typename T, class FT>
+__device__ __forceinline__ bool fft_react(const StageArgs<T>& a, const FftXPair& pr, const FT& ft,
+                                          int n, T (&va)[FT::E], T (&vb)[FT::E]) {
+  constexpr bool TWO = KIND >= RXN_FHN && KIND <= RXN_GM;
   const RxnT<T> rx(a.rxn);
+  const int sp = pr.sp;  // uniform
+  const T lin = sp == 0 ? rx.lin[0] : sp == 1 ? rx.lin[1] : sp == 2 ? rx.lin[2] : rx.lin[3];
   T chk = T(0);
+  if constexpr (TWO) {
+    ft.show(va, vb);
+    __syncthreads();
+  }
 #pragma unroll
-  for (int e = 0; e < E; ++e) {
+  for (int e = 0; e < FT::E; ++e) {
     const T u[2] = {va[e], vb[e]};
     T f[2];
     if constexpr (KIND == RXN_LINEAR) {
-      auto lin = [&](int s) { return s == 0 ? rx.lin[0] : s == 1 ? rx.lin[1] : s == 2 ? rx.lin[2] : rx.lin[3]; };
-      f[0] = lin(pr.sa) * u[0];
-      f[1] = lin(pr.sb) * u[1];
+      f[0] = lin * u[0];
+      f[1] = lin * u[1];
     } else if constexpr (KIND >= RXN_HUXLEY_MMS) {
       rxn_eval_k<T, 1, KIND>(rx, &u[0], &f[0]);
       rxn_eval_k<T, 1, KIND>(rx, &u[1], &f[1]);
-      f[0] += T(mms_source_call(a.rxn, a.t, pr.la * n + lane + 64 * e, a.n0, a.n1));
-      f[1] += T(mms_source_call(a.rxn, a.t, pr.lb * n + lane + 64 * e, a.n0, a.n1));
+      f[0] += T(mms_source_call(a.rxn, a.t, pr.la * n + ft.lane + 64 * e, a.n0, a.n1));
+      f[1] += T(mms_source_call(a.rxn, a.t, pr.lb * n + ft.lane + 64 * e, a.n0, a.n1));
     } else {
-      rxn_eval_k<T, 2, KIND>(rx, u, f);
+      T w[2];
+      ft.seen(e, w[0], w[1]);
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const T uv[2] = {sp == 0 ? u[k] : w[k], sp == 0 ? w[k] : u[k]};
+        T o[2];
+        rxn_eval_k<T, 2, KIND>(rx, uv, o);
+        f[k] = sp == 0 ? o[0] : o[1];
+      }
     }
     chk = fma(u[0], T(0), chk);
     chk = fma(u[1], T(0), chk);
@@ -429,6 +462,7 @@ __device__ __forceinline__ bool fft_react(const StageArgs<T>& a, const FftXPair&
     va[e] = f[0];
     vb[e] = f[1];
   }
+  if constexpr (TWO) __syncthreads();
   return !(chk == T(0));
 }
 
@@ -440,9 +474,15 @@ __global__ __launch_bounds__(256) void k_fx(StageArgs<T> a, FftPairs fp) {
   extern __shared__ __align__(16) char smem[];
   const WaveFft<T, N> ft(smem, a.Mt);
   const int q = fft_pair(fp.npairs);
-  if (q < 0) return;
+  if (q < 0) {
+    if (!SRC && fft_coupled(a.rxn.kind)) {  // the barriers of fft_react
+      __syncthreads();
+      __syncthreads();
+    }
+    return;
+  }
   const FftXPair pr(fp, a.S, q);
-  const long long oa = pr.sa * a.g.total + pr.la * N, ob = pr.sb * a.g.total + pr.lb * N;
+  const long long oa = pr.sp * a.g.total + pr.la * N, ob = pr.sp * a.g.total + pr.lb * N;
   typename WaveFft<T, N>::Vals va, vb;
   fft_load_line(a.P + oa, ft.lane, va);
   fft_load_line(a.P + ob, ft.lane, vb);
@@ -454,15 +494,15 @@ __global__ __launch_bounds__(256) void k_fx(StageArgs<T> a, FftPairs fp) {
   }
   bool bad;
   if constexpr (SRC) {
-    bad = a.rxn.kind == RXN_HUXLEY_MMS ? fft_react<RXN_HUXLEY_MMS>(a, pr, N, ft.lane, va, vb)
-                                       : fft_react<RXN_FISHER_MMS>(a, pr, N, ft.lane, va, vb);
+    bad = a.rxn.kind == RXN_HUXLEY_MMS ? fft_react<RXN_HUXLEY_MMS>(a, pr, ft, N, va, vb)
+                                       : fft_react<RXN_FISHER_MMS>(a, pr, ft, N, va, vb);
   } else {
     switch (a.rxn.kind) {  // uniform
-      case RXN_LINEAR: bad = fft_react<RXN_LINEAR>(a, pr, N, ft.lane, va, vb); break;
-      case RXN_FHN: bad = fft_react<RXN_FHN>(a, pr, N, ft.lane, va, vb); break;
-      case RXN_GRAY_SCOTT: bad = fft_react<RXN_GRAY_SCOTT>(a, pr, N, ft.lane, va, vb); break;
-      case RXN_SCHNAKENBERG: bad = fft_react<RXN_SCHNAKENBERG>(a, pr, N, ft.lane, va, vb); break;
-      default: bad = fft_react<RXN_GM>(a, pr, N, ft.lane, va, vb); break;
+      case RXN_LINEAR: bad = fft_react<RXN_LINEAR>(a, pr, ft, N, va, vb); break;
+      case RXN_FHN: bad = fft_react<RXN_FHN>(a, pr, ft, N, va, vb); break;
+      case RXN_GRAY_SCOTT: bad = fft_react<RXN_GRAY_SCOTT>(a, pr, ft, N, va, vb); break;
+      case RXN_SCHNAKENBERG: bad = fft_react<RXN_SCHNAKENBERG>(a, pr, ft, N, va, vb); break;
+      default: bad = fft_react<RXN_GM>(a, pr, ft, N, va, vb); break;
     }
   }
   if (bad) a.flag[0] = 1;
@@ -481,7 +521,7 @@ __global__ __launch_bounds__(256) void k_fsx(SingleArgs<T> a, FftPairs fp) {
   const int q = fft_pair(fp.npairs);
   if (q < 0) return;
   const FftXPair pr(fp, a.S, q);
-  const long long oa = pr.sa * a.g.total + pr.la * N, ob = pr.sb * a.g.total + pr.lb * N;
+  const long long oa = pr.sp * a.g.total + pr.la * N, ob = pr.sp * a.g.total + pr.lb * N;
   typename WaveFft<T, N>::Vals va, vb;
   fft_load_line(a.src + oa, ft.lane, va);
   fft_load_line(a.src + ob, ft.lane, vb);
@@ -571,39 +611,57 @@ __global__ __launch_bounds__(256) void k_fz(StageArgs<T> a, FftPairs fp) {
   io.store_all(a.P, va, vb);
 }
 
-// Adjoint reaction of the pair (species 0, 1 of two-species plans).
-template <int KIND, int E, typename T>
+// Adjoint reaction of the pair at its stage values ua, ub; wa, wb: those of the
+// other species of a coupled plan (two barriers, as in fft_react). Parameter
+// partials: a point's are counted once, by the wavefront of species 0 where two
+// are coupled, and a repeated line not again.
+template <int KIND, typename T, class FT>
 __device__ __forceinline__ void fft_adj_react(const StageArgs<T>& a, const FftXPair& pr,
-                                              T (&ga)[E], T (&gb)[E], const T (&ua)[E],
-                                              const T (&ub)[E], double* pacc) {
-  const bool wp = a.rp_acc != nullptr;
-  // a repeated line or species counts once
-  const bool two = pr.la != pr.lb || pr.sa != pr.sb;
-  auto lin = [&](int s) { return T(s == 0 ? a.rxn.p[0] : s == 1 ? a.rxn.p[1] : s == 2 ? a.rxn.p[2] : a.rxn.p[3]); };
+                                              const FT& ft, T (&ga)[FT::E], T (&gb)[FT::E],
+                                              const T (&ua)[FT::E], const T (&ub)[FT::E],
+                                              const T (&wa)[FT::E], const T (&wb)[FT::E],
+                                              double* pacc) {
+  constexpr bool TWO = KIND >= RXN_FHN && KIND <= RXN_GM;
+  const int sp = pr.sp;  // uniform
+  const bool wp = a.rp_acc != nullptr && !(TWO && sp != 0);
+  const double wt[2] = {1.0, pr.lb != pr.la ? 1.0 : 0.0};
+  const T lin = T(sp == 0 ? a.rxn.p[0] : sp == 1 ? a.rxn.p[1] : sp == 2 ? a.rxn.p[2] : a.rxn.p[3]);
+  if constexpr (TWO) {
+    ft.show(ga, gb);
+    __syncthreads();
+  }
 #pragma unroll
-  for (int e = 0; e < E; ++e) {
+  for (int e = 0; e < FT::E; ++e) {
     const T g[2] = {ga[e], gb[e]}, u[2] = {ua[e], ub[e]};
     T o[2];
     if constexpr (KIND == RXN_LINEAR) {
-      o[0] = lin(pr.sa) * g[0];
-      o[1] = lin(pr.sb) * g[1];
+      o[0] = lin * g[0];
+      o[1] = lin * g[1];
       if (wp) {
-        const double ca = double(g[0] * u[0]), cb = two ? double(g[1] * u[1]) : 0.0;
+        const double c = wt[0] * double(g[0] * u[0]) + wt[1] * double(g[1] * u[1]);
 #pragma unroll
-        for (int s = 0; s < MAX_SPECIES; ++s) {
-          pacc[s] += pr.sa == s ? ca : 0.0;
-          pacc[s] += pr.sb == s ? cb : 0.0;
-        }
+        for (int s = 0; s < MAX_SPECIES; ++s) pacc[s] += sp == s ? c : 0.0;
       }
     } else if constexpr (KIND >= RXN_HUXLEY_MMS) {
       rxn_adjoint_k<T, 1, KIND>(a.rxn, &u[0], &g[0], &o[0], 1.0, pacc, false);
       rxn_adjoint_k<T, 1, KIND>(a.rxn, &u[1], &g[1], &o[1], 1.0, pacc, false);
     } else {
-      rxn_adjoint_k<T, 2, KIND>(a.rxn, u, g, o, 1.0, pacc, wp);
+      T h[2];
+      ft.seen(e, h[0], h[1]);
+      const T w[2] = {wa[e], wb[e]};
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const T uv[2] = {sp == 0 ? u[k] : w[k], sp == 0 ? w[k] : u[k]};
+        const T gv[2] = {sp == 0 ? g[k] : h[k], sp == 0 ? h[k] : g[k]};
+        T r[2];
+        rxn_adjoint_k<T, 2, KIND>(a.rxn, uv, gv, r, wt[k], pacc, wp);
+        o[k] = sp == 0 ? r[0] : r[1];
+      }
     }
     ga[e] = o[0];
     gb[e] = o[1];
   }
+  if constexpr (TWO) __syncthreads();
 }
 
 // X, adjoint. (Every wavefront of a block reaches the block sums.)
@@ -619,26 +677,35 @@ __global__ __launch_bounds__(256) void k_fxadj(StageArgs<T> a, FftPairs fp) {
   const int q = fft_pair(fp.npairs);
   if (q >= 0) {
     const FftXPair pr(fp, a.S, q);
-    const long long oa = pr.sa * a.g.total + pr.la * N, ob = pr.sb * a.g.total + pr.lb * N;
-    typename FT::Vals va, vb, ua, ub;
+    const bool two = fft_coupled(a.rxn.kind);
+    const long long oa = pr.sp * a.g.total + pr.la * N, ob = pr.sp * a.g.total + pr.lb * N;
+    typename FT::Vals va, vb, ua, ub, wa = {}, wb = {};
     fft_load_line(a.P + oa, ft.lane, va);
     fft_load_line(a.P + ob, ft.lane, vb);
     const T* st = a.st_phys + (long long)a.mode * a.S * a.g.total;
     fft_load_line(st + oa, ft.lane, ua);
     fft_load_line(st + ob, ft.lane, ub);
+    if (two) {
+      const long long other = pr.sp == 0 ? a.g.total : -a.g.total;
+      fft_load_line(st + oa + other, ft.lane, wa);
+      fft_load_line(st + ob + other, ft.lane, wb);
+    }
     ft.hartley(va, vb);
     switch (a.rxn.kind) {  // uniform
-      case RXN_LINEAR: fft_adj_react<RXN_LINEAR>(a, pr, va, vb, ua, ub, pacc); break;
-      case RXN_FHN: fft_adj_react<RXN_FHN>(a, pr, va, vb, ua, ub, pacc); break;
-      case RXN_GRAY_SCOTT: fft_adj_react<RXN_GRAY_SCOTT>(a, pr, va, vb, ua, ub, pacc); break;
-      case RXN_SCHNAKENBERG: fft_adj_react<RXN_SCHNAKENBERG>(a, pr, va, vb, ua, ub, pacc); break;
-      case RXN_GM: fft_adj_react<RXN_GM>(a, pr, va, vb, ua, ub, pacc); break;
-      case RXN_HUXLEY_MMS: fft_adj_react<RXN_HUXLEY_MMS>(a, pr, va, vb, ua, ub, pacc); break;
-      default: fft_adj_react<RXN_FISHER_MMS>(a, pr, va, vb, ua, ub, pacc); break;
+      case RXN_LINEAR: fft_adj_react<RXN_LINEAR>(a, pr, ft, va, vb, ua, ub, wa, wb, pacc); break;
+      case RXN_FHN: fft_adj_react<RXN_FHN>(a, pr, ft, va, vb, ua, ub, wa, wb, pacc); break;
+      case RXN_GRAY_SCOTT: fft_adj_react<RXN_GRAY_SCOTT>(a, pr, ft, va, vb, ua, ub, wa, wb, pacc); break;
+      case RXN_SCHNAKENBERG: fft_adj_react<RXN_SCHNAKENBERG>(a, pr, ft, va, vb, ua, ub, wa, wb, pacc); break;
+      case RXN_GM: fft_adj_react<RXN_GM>(a, pr, ft, va, vb, ua, ub, wa, wb, pacc); break;
+      case RXN_HUXLEY_MMS: fft_adj_react<RXN_HUXLEY_MMS>(a, pr, ft, va, vb, ua, ub, wa, wb, pacc); break;
+      default: fft_adj_react<RXN_FISHER_MMS>(a, pr, ft, va, vb, ua, ub, wa, wb, pacc); break;
     }
     ft.hartley(va, vb);
     fft_store_line(a.P + oa, ft.lane, va);
     fft_store_line(a.P + ob, ft.lane, vb);
+  } else if (fft_coupled(a.rxn.kind)) {  // the barriers of fft_adj_react
+    __syncthreads();
+    __syncthreads();
   }
   if (a.rp_acc) block_add_partials(reinterpret_cast<double*>(smem), pacc, a.rxn.np, a.rp_acc);
 }

@@ -661,14 +661,16 @@ int setup_fft_axis(sfrde_plan_s* p, int axis) {
   FftPairs& f = p->fft[axis];
   f.inner = 1;
   for (int a = 0; a < axis; ++a) f.inner *= p->n[a];
-  const long long lines = p->total / n;  // per species
-  f.lines = axis == 0 ? lines : lines * p->S;
-  const long long pairs =
-      axis == 0 ? (p->S == 1 ? (lines + 1) / 2 : lines * ((p->S + 1) / 2)) : (f.lines + 1) / 2;
+  f.lines = p->total / n;  // per species
+  const long long per = axis == 0 ? (f.lines + 1) / 2 : (f.inner + 1) / 2;
+  const long long pairs = per * p->S * (axis == 0 ? 1 : f.lines / f.inner);
   // 32-bit pair and column numbers
-  if (f.lines >= (1LL << 31) || pairs >= (1LL << 31) - 64) return SFRDE_OK;
+  if (pairs >= (1LL << 31) - 64) return SFRDE_OK;
+  f.per = (int)per;
   f.npairs = (int)pairs;
   p->wpb_f[axis] = pairs * p->B >= 4LL * p->n_cu ? 4 : pairs * p->B >= 2LL * p->n_cu ? 2 : 1;
+  // (two species of a row pair share a block)
+  if (axis == 0 && p->S == 2) p->wpb_f[axis] = std::max(2u, p->wpb_f[axis]);
   const double pi = 3.14159265358979323846;
   std::vector<T> tw((size_t)2 * n);
   for (long long m = 0; m < n; ++m) {
