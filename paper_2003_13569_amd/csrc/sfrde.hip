@@ -497,9 +497,8 @@ int setup_wave_axis(sfrde_plan_s* p, int axis) {
   long long inner = 1;
   for (int a = 0; a < axis; ++a) inner *= p->n[a];
   // 32-bit lane offsets within a tile of a strided axis, 32-bit line numbers
-  const long long reach = (inner % 16 ? 2 : 1) * (n + 32) * inner * (long long)p->w;
   const long long lines = axis == 0 ? p->total / n : (long long)p->S * (p->total / n);
-  if (axis > 0 && reach >= (1LL << 32)) return SFRDE_OK;
+  if (axis > 0 && !wave_reach_ok(n, inner, (long long)p->w)) return SFRDE_OK;
   if (lines >= (1LL << 31) - 64) return SFRDE_OK;
   const WaveClass* wc = nullptr;
   TRY(wave_class_info(c, &wc));

@@ -584,9 +584,16 @@ struct WaveXf {
 };
 
 // ------------------------------------------------------------------ lines
+// Whether the rows of 16 lines of a strided axis lie within 2^32 bytes of the
+// first line, values of w bytes (a tile reaches into the next outer block where
+// the inner extent is not a multiple of 16). Arrays of wider values beside them
+// have their offsets scaled in 64 bits (RowIO).
+inline bool wave_reach_ok(long long n, long long inner, long long w) {
+  return (inner % 16 ? 2 : 1) * (n + 32) * inner * w < (1LL << 32);
+}
+
 // This lane's column of a strided tile: a uniform tile base and a 32-bit byte
-// offset per lane (engine axes have at most 288 points, so 16 lines and
-// their rows lie within 2^32 bytes of the base: host-checked).
+// offset per lane (wave_reach_ok: the host gives the engine no other axis).
 template <typename T>
 struct StridedLane {
   long long base;   // element offset of the tile's first line (uniform)
@@ -719,6 +726,15 @@ struct RowIO {
   __device__ __forceinline__ char* at(U* f, const Side& o) const {
     return reinterpret_cast<char*>(f + base) + o.rb * (sizeof(U) / sizeof(T));
   }
+  // A lane's byte offset in an array of U. Twice the 32-bit offset of an FP32 value
+  // does not fit 32 bits (an FP64 array beside FP32 fields).
+  template <typename U>
+  __device__ __forceinline__ static auto bytes_of(unsigned v) {
+    if constexpr (sizeof(U) == sizeof(T))
+      return v;
+    else
+      return (unsigned long long)v * (sizeof(U) / sizeof(T));
+  }
   template <typename U>
   __device__ __forceinline__ void load(const U* f, const Off& o, U (&va)[4], U (&vb)[4]) const {
     load1(f, o.a, va);
@@ -733,16 +749,14 @@ struct RowIO {
   template <typename U>
   __device__ __forceinline__ void load1(const U* f, const Side& o, U (&v)[4]) const {
     const char* p = at(f, o);
-    constexpr unsigned k = sizeof(U) / sizeof(T);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) v[r] = *reinterpret_cast<const U*>(p + o.v[r] * k);
+    for (int r = 0; r < 4; ++r) v[r] = *reinterpret_cast<const U*>(p + bytes_of<U>(o.v[r]));
   }
   template <typename U>
   __device__ __forceinline__ void store1(U* f, const Side& o, const U (&v)[4]) const {
     char* p = at(f, o);
-    constexpr unsigned k = sizeof(U) / sizeof(T);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) *reinterpret_cast<U*>(p + o.v[r] * k) = v[r];
+    for (int r = 0; r < 4; ++r) *reinterpret_cast<U*>(p + bytes_of<U>(o.v[r])) = v[r];
   }
   // store of an array that this pass also read: side b of a row block is
   // loaded after side a is stored, so a point that stands on both sides is
@@ -754,10 +768,9 @@ struct RowIO {
       return;
     }
     char* p = at(f, o);
-    constexpr unsigned k = sizeof(U) / sizeof(T);
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-      if (xf.vb(rb, r)) *reinterpret_cast<U*>(p + o.v[r] * k) = v[r];
+      if (xf.vb(rb, r)) *reinterpret_cast<U*>(p + bytes_of<U>(o.v[r])) = v[r];
   }
   // ---- private arrays
   struct alignas(sizeof(T) * 2) Vec { T v[4]; };

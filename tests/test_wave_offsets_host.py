@@ -1,0 +1,35 @@
+"""The matrix-core engine's addresses on grids near its 32-bit limits, on the
+CPU: its row accesses compiled for the host (tests/host/row_io.hip)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def row_io(tmp_path_factory):
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    if not os.path.exists(hipcc):
+        pytest.skip("hipcc not found")
+    exe = str(tmp_path_factory.mktemp("row_io") / "row_io")
+    subprocess.run([hipcc, "-O1", "-std=c++17", "--offload-arch=gfx950", "-Xclang",
+                    "-target-feature", "-Xclang", "-packed-fp32-ops",
+                    "-Wno-unused-command-line-argument", "-I", os.path.join(ROOT, "include"), "-I",
+                    os.path.join(ROOT, "paper_2003_13569_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "host", "row_io.hip"), "-o", exe],
+                   check=True, capture_output=True, text=True)
+    return exe
+
+
+# last axes of up to 16 blocks whose FP32 offsets fit 32 bits, with a tile across
+# the species boundary (inner extent not a multiple of 16): FP64 offsets past 2^32
+# in the first three
+@pytest.mark.parametrize("ny,nx,nz", [(1023, 1023, 401), (901, 900, 351), (1023, 1022, 477),
+                                      (513, 511, 289), (5, 3, 67)])
+def test_rows_of_fp64_arrays_beside_fp32_fields(row_io, ny, nx, nz):
+    res = subprocess.run([row_io, str(ny), str(nx), str(nz)], capture_output=True, text=True,
+                         timeout=120)
+    assert res.returncode == 0, res.stdout + res.stderr
