@@ -651,6 +651,7 @@ int launch_wave(sfrde_plan_s* p, int axis, int kernel, Args& a) {
 // wavefront per pair of lines, every CU its share of the wavefronts before a
 // block gets a second one (wavefronts of a block share the cache lines of
 // strided axes).
+constexpr unsigned FFT_WAVES = 4;  // wavefronts per block at most
 template <typename T>
 int setup_fft_axis(sfrde_plan_s* p, int axis) {
   const long long n = p->n[axis];
@@ -667,7 +668,8 @@ int setup_fft_axis(sfrde_plan_s* p, int axis) {
   if (pairs >= (1LL << 31) - 64) return SFRDE_OK;
   f.per = (int)per;
   f.npairs = (int)pairs;
-  p->wpb_f[axis] = pairs * p->B >= 4LL * p->n_cu ? 4 : pairs * p->B >= 2LL * p->n_cu ? 2 : 1;
+  p->wpb_f[axis] =
+      pairs * p->B >= 4LL * p->n_cu ? FFT_WAVES : pairs * p->B >= 2LL * p->n_cu ? 2 : 1;
   // (two species of a row pair share a block)
   if (axis == 0 && p->S == 2) p->wpb_f[axis] = std::max(2u, p->wpb_f[axis]);
   const double pi = 3.14159265358979323846;
@@ -678,11 +680,12 @@ int setup_fft_axis(sfrde_plan_s* p, int axis) {
   }
   TRY(dev_alloc(p, &p->tw[axis], tw.size() * sizeof(T)));
   HIPCHECK(hipMemcpy(p->tw[axis], tw.data(), tw.size() * sizeof(T), hipMemcpyHostToDevice));
+  // (the limit belongs to the kernels, not to the plan: what any plan launches)
   const FftKernels k = fft_kernels<T>(n);
   for (const void* fn : k.fn)
     if (fn)
       HIPCHECK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   (int)(p->wpb_f[axis] * k.lds)));
+                                   (int)(FFT_WAVES * k.lds)));
   p->use_f[axis] = true;
   return SFRDE_OK;
 }
