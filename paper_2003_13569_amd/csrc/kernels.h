@@ -474,16 +474,67 @@ __device__ __forceinline__ void stage_coefs_tab(int mode, const T* cf, long long
   }
 }
 
-// Forward stage combine: buf holds the transformed reaction (full spectral);
-// replaced by cs times the next stage's spectral value.
+// Forward stage combine of point i of the [S][total] fields: fh is the
+// transformed reaction (full spectral); returns cs times the next stage's
+// spectral value.
+template <typename T>
+__device__ __forceinline__ T combine_point(const StageArgs<T>& a, long long i, T fh) {
+  const long long cst = (long long)a.S * a.g.total;
+  T out, c0 = T(0), c1 = T(0), c2 = T(0), c3 = T(0);
+  if (a.mode <= 3) {
+    if (a.ltab)
+      stage_coefs_L<T>(a.mode, a.ltab[i], a.tau, c0, c1, c2, c3);
+    else
+      stage_coefs_tab<T>(a.mode, a.coef + i, cst, c0, c1, c2, c3);
+  }
+  switch (a.mode) {
+    case 0: {
+      const T uh = a.uhat[i];
+      if (a.st_uhat) a.st_uhat[i] = uh;
+      if (a.st_fhat) a.st_fhat[i] = fh;
+      const T av = dec_mul(c0, uh) + c1 * fh;
+      a.ctil[i] = dec_mul(c0, av) - c1 * fh;
+      a.acc[i] = dec_mul(c2, uh) + c3 * fh;
+      out = av;
+      break;
+    }
+    case 1: {
+      if (a.st_fhat) a.st_fhat[1 * cst + i] = fh;
+      const T uh = a.uhat[i];
+      out = dec_mul(c0, uh) + c1 * fh;
+      a.acc[i] += c2 * fh;
+      break;
+    }
+    case 2: {
+      if (a.st_fhat) a.st_fhat[2 * cst + i] = fh;
+      out = a.ctil[i] + T(2) * c1 * fh;
+      a.acc[i] += c2 * fh;
+      break;
+    }
+    case 3: {
+      if (a.st_fhat) a.st_fhat[3 * cst + i] = fh;
+      const T un = a.acc[i] + c2 * fh;
+      a.uhat[i] = un;
+      out = un;
+      break;
+    }
+    case MODE_INIT:
+      a.uhat[i] = fh;
+      out = fh;
+      break;
+    default:  // MODE_RESTORE: the tile was loaded from the spectral state
+      out = fh;
+      break;
+  }
+  return a.cs * out;
+}
+
+// The same in place on a tile.
 template <typename T>
 __device__ __forceinline__ void pw_combine(const StageArgs<T>& a, T* buf, long long tile) {
   const Geom& g = a.g;
   const TileRef tr = tile_ref(g, tile);
-  const int S = a.S;
   const int ne = g.n * g.W;
-  const long long tot = g.total;
-  const long long cst = (long long)S * tot;
   for (int e = threadIdx.x; e < ne; e += blockDim.x) {
     int j, w;
     unpack(g, e, j, w);
@@ -491,55 +542,7 @@ __device__ __forceinline__ void pw_combine(const StageArgs<T>& a, T* buf, long l
     if (!elem(g, tr, j, w, idx)) continue;
     for (int s = 0; s < g.spt; ++s) {
       T& cell = buf[(s * g.n + j) * g.pitch + w];
-      const T fh = cell;
-      const long long i = s * tot + idx;
-      T out, c0 = T(0), c1 = T(0), c2 = T(0), c3 = T(0);
-      if (a.mode <= 3) {
-        if (a.ltab)
-          stage_coefs_L<T>(a.mode, a.ltab[i], a.tau, c0, c1, c2, c3);
-        else
-          stage_coefs_tab<T>(a.mode, a.coef + i, cst, c0, c1, c2, c3);
-      }
-      switch (a.mode) {
-        case 0: {
-          const T uh = a.uhat[i];
-          if (a.st_uhat) a.st_uhat[i] = uh;
-          if (a.st_fhat) a.st_fhat[i] = fh;
-          const T av = dec_mul(c0, uh) + c1 * fh;
-          a.ctil[i] = dec_mul(c0, av) - c1 * fh;
-          a.acc[i] = dec_mul(c2, uh) + c3 * fh;
-          out = av;
-          break;
-        }
-        case 1: {
-          if (a.st_fhat) a.st_fhat[1 * cst + i] = fh;
-          const T uh = a.uhat[i];
-          out = dec_mul(c0, uh) + c1 * fh;
-          a.acc[i] += c2 * fh;
-          break;
-        }
-        case 2: {
-          if (a.st_fhat) a.st_fhat[2 * cst + i] = fh;
-          out = a.ctil[i] + T(2) * c1 * fh;
-          a.acc[i] += c2 * fh;
-          break;
-        }
-        case 3: {
-          if (a.st_fhat) a.st_fhat[3 * cst + i] = fh;
-          const T un = a.acc[i] + c2 * fh;
-          a.uhat[i] = un;
-          out = un;
-          break;
-        }
-        case MODE_INIT:
-          a.uhat[i] = fh;
-          out = fh;
-          break;
-        default:  // MODE_RESTORE: the tile was loaded from the spectral state
-          out = fh;
-          break;
-      }
-      cell = a.cs * out;
+      cell = combine_point(a, s * g.total + idx, cell);
     }
   }
 }
@@ -642,17 +645,80 @@ __device__ __forceinline__ void p13_table_derivs(double L, double tau, double* c
   d[C_PHI3] = (tau * (3.0 + 2.0 * L) - c[C_PHI3] * dD) * iD;
 }
 
+// Adjoint combine of point i: X is the transformed cotangent; returns cs times
+// the next stage's.
+template <typename T>
+__device__ __forceinline__ T adj_combine_point(const StageArgs<T>& a, long long i, T X) {
+  const long long cst = (long long)a.S * a.g.total;
+  // FP64 P13 plans: the coefficients and their derivatives formed from L
+  // (one table read per point instead of up to eleven)
+  const bool from_l = std::is_same<T, double>::value && a.ltab != nullptr;
+  const T* cf = a.coef + i;
+  const T* dc = a.dcoef ? a.dcoef + i : nullptr;
+  double cl[NCOEF], dl[NCOEF];
+  if (from_l) p13_table_derivs(double(a.ltab[i]), double(a.tau), cl, dl);
+  auto C = [&](int q) -> T { return from_l ? T(cl[q]) : cf[q * cst]; };
+  auto Dq = [&](int q) -> T { return from_l ? T(dl[q]) : dc[q * cst]; };
+  T out;
+  switch (a.mode) {
+    case 0: {
+      const T z = a.zh[i];
+      const T dQ = C(C_Q), cP = C(C_PHI);
+      a.aacc[i] = dec_mul(C(C_R), z);
+      a.ahat[i] = dec_mul(dQ, X);
+      a.gu[i] = C(C_PHI1) * z - cP * X;
+      out = C(C_PHI2) * z + T(2) * cP * X;
+      if (a.G) {
+        const T uh = a.st_uhat[i];
+        const T fu = a.st_fhat[0 * cst + i], fa = a.st_fhat[1 * cst + i];
+        const T fb = a.st_fhat[2 * cst + i], fc = a.st_fhat[3 * cst + i];
+        const T ah = dec_mul(dQ, uh) + cP * fu;
+        const T s1 = Dq(C_R) * uh + Dq(C_PHI1) * fu + Dq(C_PHI2) * (fa + fb) + Dq(C_PHI3) * fc;
+        const T s2 = Dq(C_Q) * ah + Dq(C_PHI) * (T(2) * fb - fu);
+        a.G[i] += double(z) * double(s1) + double(X) * double(s2);
+      }
+      break;
+    }
+    case 1: {
+      const T z = a.zh[i];
+      a.aacc[i] += dec_mul(C(C_Q), X);
+      out = C(C_PHI2) * z + C(C_PHI) * X;
+      if (a.G) {
+        const T uh = a.st_uhat[i], fa = a.st_fhat[1 * cst + i];
+        a.G[i] += double(X) * double(Dq(C_Q) * uh + Dq(C_PHI) * fa);
+      }
+      break;
+    }
+    case 2: {
+      const T A = a.ahat[i] + X;
+      a.aacc[i] += dec_mul(C(C_Q), A);
+      out = a.gu[i] + C(C_PHI) * A;
+      if (a.G) {
+        const T uh = a.st_uhat[i], fu = a.st_fhat[0 * cst + i];
+        a.G[i] += double(A) * double(Dq(C_Q) * uh + Dq(C_PHI) * fu);
+      }
+      break;
+    }
+    case 3: {
+      const T zn = a.aacc[i] + X;
+      a.zh[i] = zn;
+      out = a.last ? zn : C(C_PHI3) * zn;
+      break;
+    }
+    default:  // MODE_INIT: X is the transformed cotangent of u(T)
+      a.zh[i] = X;
+      out = C(C_PHI3) * X;
+      break;
+  }
+  return a.cs * out;
+}
+
+// The same in place on a tile.
 template <typename T>
 __device__ __forceinline__ void pw_adj_combine(const StageArgs<T>& a, T* buf, long long tile) {
   const Geom& g = a.g;
   const TileRef tr = tile_ref(g, tile);
-  const int S = a.S;
   const int ne = g.n * g.W;
-  const long long tot = g.total;
-  const long long cst = (long long)S * tot;
-  // FP64 P13 plans: the coefficients and their derivatives formed from L
-  // (one table read per point instead of up to eleven)
-  const bool from_l = std::is_same<T, double>::value && a.ltab != nullptr;
   for (int e = threadIdx.x; e < ne; e += blockDim.x) {
     int j, w;
     unpack(g, e, j, w);
@@ -660,66 +726,7 @@ __device__ __forceinline__ void pw_adj_combine(const StageArgs<T>& a, T* buf, lo
     if (!elem(g, tr, j, w, idx)) continue;
     for (int s = 0; s < g.spt; ++s) {
       T& cell = buf[(s * g.n + j) * g.pitch + w];
-      const T X = cell;
-      const long long i = s * tot + idx;
-      const T* cf = a.coef + i;
-      const T* dc = a.dcoef ? a.dcoef + i : nullptr;
-      double cl[NCOEF], dl[NCOEF];
-      if (from_l) p13_table_derivs(double(a.ltab[i]), double(a.tau), cl, dl);
-      auto C = [&](int q) -> T { return from_l ? T(cl[q]) : cf[q * cst]; };
-      auto Dq = [&](int q) -> T { return from_l ? T(dl[q]) : dc[q * cst]; };
-      T out;
-      switch (a.mode) {
-        case 0: {
-          const T z = a.zh[i];
-          const T dQ = C(C_Q), cP = C(C_PHI);
-          a.aacc[i] = dec_mul(C(C_R), z);
-          a.ahat[i] = dec_mul(dQ, X);
-          a.gu[i] = C(C_PHI1) * z - cP * X;
-          out = C(C_PHI2) * z + T(2) * cP * X;
-          if (a.G) {
-            const T uh = a.st_uhat[i];
-            const T fu = a.st_fhat[0 * cst + i], fa = a.st_fhat[1 * cst + i];
-            const T fb = a.st_fhat[2 * cst + i], fc = a.st_fhat[3 * cst + i];
-            const T ah = dec_mul(dQ, uh) + cP * fu;
-            const T s1 = Dq(C_R) * uh + Dq(C_PHI1) * fu + Dq(C_PHI2) * (fa + fb) + Dq(C_PHI3) * fc;
-            const T s2 = Dq(C_Q) * ah + Dq(C_PHI) * (T(2) * fb - fu);
-            a.G[i] += double(z) * double(s1) + double(X) * double(s2);
-          }
-          break;
-        }
-        case 1: {
-          const T z = a.zh[i];
-          a.aacc[i] += dec_mul(C(C_Q), X);
-          out = C(C_PHI2) * z + C(C_PHI) * X;
-          if (a.G) {
-            const T uh = a.st_uhat[i], fa = a.st_fhat[1 * cst + i];
-            a.G[i] += double(X) * double(Dq(C_Q) * uh + Dq(C_PHI) * fa);
-          }
-          break;
-        }
-        case 2: {
-          const T A = a.ahat[i] + X;
-          a.aacc[i] += dec_mul(C(C_Q), A);
-          out = a.gu[i] + C(C_PHI) * A;
-          if (a.G) {
-            const T uh = a.st_uhat[i], fu = a.st_fhat[0 * cst + i];
-            a.G[i] += double(A) * double(Dq(C_Q) * uh + Dq(C_PHI) * fu);
-          }
-          break;
-        }
-        case 3: {
-          const T zn = a.aacc[i] + X;
-          a.zh[i] = zn;
-          out = a.last ? zn : C(C_PHI3) * zn;
-          break;
-        }
-        default:  // MODE_INIT: X is the transformed cotangent of u(T)
-          a.zh[i] = X;
-          out = C(C_PHI3) * X;
-          break;
-      }
-      cell = a.cs * out;
+      cell = adj_combine_point(a, s * g.total + idx, cell);
     }
   }
 }
@@ -831,6 +838,27 @@ __global__ __launch_bounds__(NTHREADS) void k_zadj(StageArgs<T> a) {
   __syncthreads();
   dense_transform(buf, a.g.spt, a.g, a.Mt);
   store_tile(a.g, tile, buf, a.P, a.g.spt);
+}
+
+// Last axis of one point (the padding axis of 1D plans): its transform is the
+// identity, so that the combine is all there is, one point per thread. Bound by
+// a launch and its few loads. Steps of 1D FHN plans, the identity as a product in
+// the engine / this: 64 points FP64 52 / 43 us, 300 points FP32 56 / 51, FP64
+// 171 / 159 (in the dense kernels 70, 82 and 197).
+constexpr int POINT_THREADS = 64;
+template <typename T>
+__global__ __launch_bounds__(POINT_THREADS) void k_zpoint(StageArgs<T> a) {
+  to_member(a);
+  const long long i = (long long)blockIdx.x * POINT_THREADS + threadIdx.x;
+  if (i >= (long long)a.S * a.g.total) return;
+  a.P[i] = combine_point(a, i, (a.src ? a.src : a.P)[i]);
+}
+template <typename T>
+__global__ __launch_bounds__(POINT_THREADS) void k_zadjpoint(StageArgs<T> a) {
+  to_member(a);
+  const long long i = (long long)blockIdx.x * POINT_THREADS + threadIdx.x;
+  if (i >= (long long)a.S * a.g.total) return;
+  a.P[i] = adj_combine_point(a, i, a.P[i]);
 }
 
 // One transform along one axis, src -> dst (may alias), with optional

@@ -241,10 +241,6 @@ int expected_nparams(int reaction, int S) {
 std::vector<double> axis_matrix_t(int bc, long long n) {
   const double pi = 3.14159265358979323846;
   std::vector<double> Mt((size_t)n * n);
-  if (n == 1) {  // the one-point padding axis of a 1D plan: the identity
-    Mt[0] = 1.0;
-    return Mt;
-  }
   for (long long k = 0; k < n; ++k) {
     for (long long j = 0; j < n; ++j) {
       double v;
@@ -392,8 +388,10 @@ int wave_class_info(int c, const WaveClass** out) {
 
 // Size class of an axis, -1 if the engine has none.
 int wave_class_of(int dtype, int bc, long long n, bool source) {
-  // (the one-point padding axis of a 1D plan is an odd axis on every boundary)
-  const bool per = bc == SFRDE_BC_PERIODIC && n > 1, f32 = dtype == SFRDE_F32;
+  // the one-point padding axis of a 1D plan has no transform (k_zpoint; as a
+  // product with the identity it rounded FP32 values to two binary16 terms)
+  if (n == 1) return -1;
+  const bool per = bc == SFRDE_BC_PERIODIC, f32 = dtype == SFRDE_F32;
   const long long half = per ? n / 2 + 1 : (n + 1) / 2;  // positions of an even axis
   const bool odd = !per && n % 2 == 1;
   const int c2 = f32 ? WC_F32_2X : WC_F64_2X, c4 = f32 ? WC_F32_4X : WC_F64_4X;
@@ -421,7 +419,7 @@ int wave_class_of(int dtype, int bc, long long n, bool source) {
 WaveAxis wave_axis(int bc, long long n) {
   WaveAxis x{};
   x.n = (int)n;
-  x.periodic = bc == SFRDE_BC_PERIODIC && n > 1;
+  x.periodic = bc == SFRDE_BC_PERIODIC;
   auto blocks = [](int c) { return (c + 15) / 16; };
   if (x.periodic) {
     const int half = (int)(n / 2) + 1;  // p = 0 .. n/2
@@ -467,7 +465,7 @@ struct WaveMatrix {
     } else if (bc == SFRDE_BC_DIRICHLET) {
       trig.resize(2 * (n + 1));
       for (long long m = 0; m < 2 * (n + 1); ++m) trig[m] = sin(pi * double(m) / double(n + 1));
-    } else if (n > 1) {
+    } else {
       trig.resize(2 * (n - 1));
       for (long long m = 0; m < 2 * (n - 1); ++m) trig[m] = cos(pi * double(m) / double(n - 1));
     }
@@ -481,7 +479,6 @@ struct WaveMatrix {
     const bool fixed = !(q >= g.blo && q < g.bhi);
     if (half && fixed) return 0.0;
     const double f = fixed ? 0.5 : 1.0;
-    if (n == 1) return f;  // padding axis of a 1D plan: the identity
     const long long a = g.a0 + (long long)x.da * q;
     if (x.periodic) return half ? trig2[(row * a) % n] : f * trig[(row * a) % n];
     const long long k = 2LL * row + half;
@@ -815,6 +812,11 @@ int launch_x(sfrde_plan_s* p, int stage, double t, T* st_phys) {
   return SFRDE_OK;
 }
 
+// Grid of the last-axis kernels of an axis of one point.
+dim3 point_grid(const sfrde_plan_s* p) {
+  return dim3((unsigned)((p->S * p->total + POINT_THREADS - 1) / POINT_THREADS), (unsigned)p->B);
+}
+
 // uhat: the spectral state this stage reads (stages 0, 1) or writes (stage
 // 3); NULL: the plan's own.
 template <typename T>
@@ -830,7 +832,9 @@ int launch_z(sfrde_plan_s* p, int mode, const void* src, T* st_fhat, T* uhat = n
     TRY(launch_wave(p, ax, mode > 3 ? WK_ZINIT : (p->lfly ? WK_ZFLY : WK_Z) + mode, a));
   } else if (p->use_f[ax]) {
     TRY(launch_fft<T>(p, ax, mode > 3 ? WK_ZINIT : WK_Z + mode, a));
-  } else
+  } else if (p->n[ax] == 1)
+    hipLaunchKernelGGL(k_zpoint<T>, point_grid(p), dim3(POINT_THREADS), 0, p->stream, a);
+  else
     hipLaunchKernelGGL(k_zstage<T>, dim3((unsigned)a.g.ntiles, p->B), dim3(NTHREADS),
                        p->lds[ax], p->stream, a);
   prof_stop(p, pk);
@@ -1021,7 +1025,9 @@ int launch_zadj(sfrde_plan_s* p, int mode, const StepStore<T>* st, int last) {
     TRY(launch_wave(p, ax, k, a));
   } else if (p->use_f[ax]) {
     TRY(launch_fft<T>(p, ax, WK_ZADJ, a));
-  } else
+  } else if (p->n[ax] == 1)
+    hipLaunchKernelGGL(k_zadjpoint<T>, point_grid(p), dim3(POINT_THREADS), 0, p->stream, a);
+  else
     hipLaunchKernelGGL(k_zadj<T>, dim3((unsigned)a.g.ntiles, p->B), dim3(NTHREADS),
                        p->lds[ax], p->stream, a);
   prof_stop(p, pk);
@@ -1410,7 +1416,7 @@ int build_plan(sfrde_plan_s* p) {
       TRY(setup_fft_axis<float>(p, a));
     else
       TRY(setup_fft_axis<double>(p, a));
-    if (p->wcls[a] < 0 && !p->use_f[a]) {
+    if (p->wcls[a] < 0 && !p->use_f[a] && p->n[a] > 1) {
       if (p->dtype == SFRDE_F32)
         TRY(upload_matrix<float>(p, a));
       else
