@@ -194,10 +194,10 @@ int sfrde_backward(sfrde_plan_t plan, const void* ckpt, int64_t nsteps,
  * allocate device memory at call time (code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc). Same arguments, results
  * and errors as sfrde_backward, computed by the same kernels; the backward
- * buffers (adjoint fields, the segment store of ckpt_every steps, gradient
- * partials) live in one static device array of SFRDE_NOALLOC_SCRATCH_BYTES
- * per GPU, which the library holds from its first plan on that GPU until the
- * process ends, instead of plan memory allocated on first use. The call
+ * buffers (adjoint fields, the segment store of ckpt_every steps) live in one
+ * static device array of SFRDE_NOALLOC_SCRATCH_BYTES per GPU (and 1 MiB more
+ * for gradient partials), which the library holds from its first plan on that
+ * GPU until the process ends, instead of plan memory allocated on first use. The call
  * makes no device allocation and frees nothing.
  * Limits: the buffers need about (5 + 9 * min(ckpt_every, nsteps)) fields
  * of [B][S][...] dtype (plus one FP64 field and six dtype fields when the

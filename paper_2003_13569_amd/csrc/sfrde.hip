@@ -75,8 +75,12 @@ constexpr long long RED_PER_MEMBER = 2 * MAX_SPECIES + MAX_PARAMS;
 // itself (in host code the name is a stand-in, not a device address): it
 // uses the address hipGetSymbolAddress returns on each device, looked up
 // once per device at plan set-up.
+// Behind it a part for the gradients' block partials, whose size follows the launch
+// grids (0.2 MB at most on the engine's, but for ensembles of thousands): the
+// fields alone decide whether a request fits.
 constexpr size_t SCRATCH_BYTES = (size_t)SFRDE_NOALLOC_SCRATCH_BYTES;
-static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES];
+constexpr size_t PARTIAL_BYTES = 1 << 20;
+static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES + PARTIAL_BYTES];
 
 constexpr int MAX_DEVICES = 64;
 std::mutex g_scratch_mu;
@@ -1118,6 +1122,12 @@ int carve_backward_buffers(sfrde_plan_s* p, long long seg_steps, bool want_theta
     *ptr = base + off;
     off += round256(bytes);
   };
+  size_t poff = 0;
+  auto take_partials = [&](double** ptr, size_t bytes) {
+    if (poff + bytes > PARTIAL_BYTES) return take((void**)ptr, bytes);
+    *ptr = (double*)(base + SCRATCH_BYTES + poff);
+    poff += round256(bytes);
+  };
   take(&p->Pa, f);
   take(&p->zh, f);
   take(&p->aacc, f);
@@ -1132,7 +1142,7 @@ int carve_backward_buffers(sfrde_plan_s* p, long long seg_steps, bool want_theta
   p->rp_acc = nullptr;
   bool fill_dcoef = false;
   if (want_theta && p->thp_on) {
-    take((void**)&p->thp, (size_t)4 * thp_blocks(p) * sizeof(double));
+    take_partials(&p->thp, (size_t)4 * thp_blocks(p) * sizeof(double));
   } else if (want_theta) {
     take((void**)&p->G, field_elems(p) * sizeof(double));
     // FP64 P13 plans form the coefficient derivatives from L in the combine
@@ -1141,7 +1151,8 @@ int carve_backward_buffers(sfrde_plan_s* p, long long seg_steps, bool want_theta
       fill_dcoef = true;
     }
   }
-  if (want_p) take((void**)&p->rp_acc, (size_t)p->B * MAX_PARAMS * rp_blocks(p) * sizeof(double));
+  if (want_p)
+    take_partials(&p->rp_acc, (size_t)p->B * MAX_PARAMS * rp_blocks(p) * sizeof(double));
   const long long need = RED_OUT + (long long)p->B * RED_PER_MEMBER;
   take((void**)&p->red, (size_t)need * sizeof(double));
   p->red_len = need;
