@@ -180,6 +180,7 @@ __device__ __forceinline__ void dense_transform(T* buf, int S, const Geom& g,
       const T* mr = Mt + (long long)j * n + kg;
 #pragma unroll
       for (int q = 0; q < KMAX; ++q) {
+        if (q * KG >= n) break;  // uniform: a narrow tile has few rows per thread
         if (kg + q * KG < n) acc[q] += mr[q * KG] * v;
       }
     }
@@ -785,19 +786,27 @@ __global__ __launch_bounds__(NTHREADS) void k_xstage(StageArgs<T> a) {
 }
 
 // Z kernel, forward: forward transform along the last axis, stage combine,
-// inverse transform (in place on P).
+// inverse transform (in place on P). Bound by the products' loads of the matrix
+// from L2, which need wavefronts: one copy of the product and four wavefronts per
+// SIMD (with two copies 170 registers, two wavefronts). 700 x 40 x 30 FP32, 13
+// launches: 90 ms with two wavefronts, 49 with four, 39.5 with the products'
+// uniform exit.
 template <typename T>
-__global__ __launch_bounds__(NTHREADS) void k_zstage(StageArgs<T> a) {
+__global__ __launch_bounds__(NTHREADS, 4) void k_zstage(StageArgs<T> a) {
   to_member(a);
   extern __shared__ __align__(16) unsigned char smem_raw[];
   T* buf = reinterpret_cast<T*>(smem_raw);
   const long long tile = blockIdx.x;
   load_tile(a.g, tile, a.src ? a.src : a.P, buf, a.g.spt);
   __syncthreads();
-  if (!a.src) dense_transform(buf, a.g.spt, a.g, a.Mt);
-  pw_combine(a, buf, tile);
-  __syncthreads();
-  dense_transform(buf, a.g.spt, a.g, a.Mt);
+#pragma unroll 1
+  for (int pass = a.src ? 1 : 0; pass < 2; ++pass) {
+    if (pass == 1) {
+      pw_combine(a, buf, tile);
+      __syncthreads();
+    }
+    dense_transform(buf, a.g.spt, a.g, a.Mt);
+  }
   store_tile(a.g, tile, buf, a.P, a.g.spt);
 }
 
