@@ -422,12 +422,17 @@ __device__ __forceinline__ void fft_store_line(T* p, int lane, const T (&v)[E]) 
 // species: every wavefront of the block comes here (two barriers).
 template <int KIND, typename T, class FT>
 __device__ __forceinline__ bool fft_react(const StageArgs<T>& a, const FftXPair& pr, const FT& ft,
-                                          int n, T (&va)[FT::E], T (&vb)[FT::E]) {
+                                          T (&va)[FT::E], T (&vb)[FT::E]) {
   constexpr bool TWO = KIND >= RXN_FHN && KIND <= RXN_GM;
   const RxnT<T> rx(a.rxn);
   const int sp = pr.sp;  // uniform
   const T lin = sp == 0 ? rx.lin[0] : sp == 1 ? rx.lin[1] : sp == 2 ? rx.lin[2] : rx.lin[3];
   T chk = T(0);
+  MmsLine ml[2] = {};
+  if constexpr (KIND >= RXN_HUXLEY_MMS) {
+    ml[0] = mms_line(a.rxn, a.t, pr.la % a.n1);
+    ml[1] = mms_line(a.rxn, a.t, pr.lb % a.n1);
+  }
   if constexpr (TWO) {
     ft.show(va, vb);
     __syncthreads();
@@ -442,8 +447,8 @@ __device__ __forceinline__ bool fft_react(const StageArgs<T>& a, const FftXPair&
     } else if constexpr (KIND >= RXN_HUXLEY_MMS) {
       rxn_eval_k<T, 1, KIND>(rx, &u[0], &f[0]);
       rxn_eval_k<T, 1, KIND>(rx, &u[1], &f[1]);
-      f[0] += T(mms_source_call(a.rxn, a.t, pr.la * n + ft.lane + 64 * e, a.n0, a.n1));
-      f[1] += T(mms_source_call(a.rxn, a.t, pr.lb * n + ft.lane + 64 * e, a.n0, a.n1));
+      f[0] += T(mms_source<KIND>(ml[0], ft.lane + 64 * e));
+      f[1] += T(mms_source<KIND>(ml[1], ft.lane + 64 * e));
     } else {
       T w[2];
       ft.seen(e, w[0], w[1]);
@@ -494,15 +499,15 @@ __global__ __launch_bounds__(256) void k_fx(StageArgs<T> a, FftPairs fp) {
   }
   bool bad;
   if constexpr (SRC) {
-    bad = a.rxn.kind == RXN_HUXLEY_MMS ? fft_react<RXN_HUXLEY_MMS>(a, pr, ft, N, va, vb)
-                                       : fft_react<RXN_FISHER_MMS>(a, pr, ft, N, va, vb);
+    bad = a.rxn.kind == RXN_HUXLEY_MMS ? fft_react<RXN_HUXLEY_MMS>(a, pr, ft, va, vb)
+                                       : fft_react<RXN_FISHER_MMS>(a, pr, ft, va, vb);
   } else {
     switch (a.rxn.kind) {  // uniform
-      case RXN_LINEAR: bad = fft_react<RXN_LINEAR>(a, pr, ft, N, va, vb); break;
-      case RXN_FHN: bad = fft_react<RXN_FHN>(a, pr, ft, N, va, vb); break;
-      case RXN_GRAY_SCOTT: bad = fft_react<RXN_GRAY_SCOTT>(a, pr, ft, N, va, vb); break;
-      case RXN_SCHNAKENBERG: bad = fft_react<RXN_SCHNAKENBERG>(a, pr, ft, N, va, vb); break;
-      default: bad = fft_react<RXN_GM>(a, pr, ft, N, va, vb); break;
+      case RXN_LINEAR: bad = fft_react<RXN_LINEAR>(a, pr, ft, va, vb); break;
+      case RXN_FHN: bad = fft_react<RXN_FHN>(a, pr, ft, va, vb); break;
+      case RXN_GRAY_SCOTT: bad = fft_react<RXN_GRAY_SCOTT>(a, pr, ft, va, vb); break;
+      case RXN_SCHNAKENBERG: bad = fft_react<RXN_SCHNAKENBERG>(a, pr, ft, va, vb); break;
+      default: bad = fft_react<RXN_GM>(a, pr, ft, va, vb); break;
     }
   }
   if (bad) a.flag[0] = 1;

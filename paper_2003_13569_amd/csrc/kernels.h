@@ -306,28 +306,59 @@ __device__ __forceinline__ void to_member(StageArgs<T>& a) {
 //              K2 = 3 kappa (40 pi^2)^(alpha/2)/16, K3 = kappa (72 pi^2)^(alpha/2)/16
 //   Example 1: (alpha, K1, -, K3, h) with K1 = 3 kappa (2 pi)^alpha/4,
 //              K3 = kappa (6 pi)^alpha/4
-__device__ __forceinline__ double mms_source(const Rxn& r, double t, long long idx,
-                                             long long n0, long long n1) {
+// In two parts: what the points of one x line share (y index i1), and a point of
+// it. All in values, so that a call of the second part needs no stack. X launches
+// of 160^2 FP64 points 42 us with the whole source per point (in phases over 512
+// threads 30), 22 in two parts.
+struct MmsLine {
+  double ta, dta;     // t^alpha and its derivative; Example 1: e^-t
+  double c1y, c3y;    // cos(2 pi y), cos(6 pi y)
+  double k1, k2, k3;  // K1..K3
+  double h;           // x spacing
+};
+__device__ __forceinline__ MmsLine mms_line(const Rxn& r, double t, long long i1) {
   const double* c = r.p + MMS_P0;
-  const long long i0 = idx % n0;
+  MmsLine m{0.0, 0.0, 0.0, 0.0, c[1], c[2], c[3], c[4]};
   if (r.kind == RXN_FISHER_MMS) {
-    // u = e^-t sin^3(2 pi x), sin^3 = (3 sin(2 pi x) - sin(6 pi x))/4, interior nodes
-    const double x = double(i0 + 1) * c[4];
-    const double s1 = sinpi(2.0 * x), s3 = sinpi(6.0 * x);
-    const double e = exp(-t), s13 = s1 * s1 * s1;
-    return -2.0 * e * s13 + e * (c[1] * s1 - c[3] * s3) + e * e * s13 * s13;
+    m.ta = exp(-t);
+    return m;
   }
-  // u = t^alpha C(x) C(y), C = cos^3(2 pi .) = (3 cos(2 pi .) + cos(6 pi .))/4
-  const long long i1 = (idx / n0) % n1;
-  const double x = double(i0) * c[4], y = double(i1) * c[5];
-  const double c1x = cospi(2.0 * x), c3x = cospi(6.0 * x);
-  const double c1y = cospi(2.0 * y), c3y = cospi(6.0 * y);
-  const double cc = c1x * c1x * c1x * c1y * c1y * c1y;
-  const double phi = c[1] * c1x * c1y + c[2] * (c3x * c1y + c1x * c3y) + c[3] * c3x * c3y;
-  const double ta = t > 0.0 ? pow(t, c[0]) : 0.0;
-  const double dta = t > 0.0 ? c[0] * ta / t : 0.0;
-  const double w = ta * cc;
-  return dta * cc + ta * phi - w * (1.0 - w) * (w - 1.0);
+  const double y = double(i1) * c[5];
+  m.c1y = cospi(2.0 * y);
+  m.c3y = cospi(6.0 * y);
+  m.ta = t > 0.0 ? pow(t, c[0]) : 0.0;
+  m.dta = t > 0.0 ? c[0] * m.ta / t : 0.0;
+  return m;
+}
+template <int KIND>
+__device__ __forceinline__ double mms_point(double i0, double h, double ta, double dta, double c1y,
+                                            double c3y, double k1, double k2, double k3) {
+  if constexpr (KIND == RXN_FISHER_MMS) {
+    // u = e^-t sin^3(2 pi x), sin^3 = (3 sin(2 pi x) - sin(6 pi x))/4, interior nodes
+    const double x = (i0 + 1.0) * h;
+    const double s1 = sinpi(2.0 * x), s3 = sinpi(6.0 * x);
+    const double s13 = s1 * s1 * s1;
+    return -2.0 * ta * s13 + ta * (k1 * s1 - k3 * s3) + ta * ta * s13 * s13;
+  } else {
+    // u = t^alpha C(x) C(y), C = cos^3(2 pi .) = (3 cos(2 pi .) + cos(6 pi .))/4
+    const double x = i0 * h;
+    const double c1x = cospi(2.0 * x), c3x = cospi(6.0 * x);
+    const double cc = c1x * c1x * c1x * c1y * c1y * c1y;
+    const double phi = k1 * c1x * c1y + k2 * (c3x * c1y + c1x * c3y) + k3 * c3x * c3y;
+    const double w = ta * cc;
+    return dta * cc + ta * phi - w * (1.0 - w) * (w - 1.0);
+  }
+}
+// A call per point (a long function, many points per thread).
+template <int KIND>
+static __device__ __attribute__((noinline)) double mms_call(double i0, double h, double ta,
+                                                            double dta, double c1y, double c3y,
+                                                            double k1, double k2, double k3) {
+  return mms_point<KIND>(i0, h, ta, dta, c1y, c3y, k1, k2, k3);
+}
+template <int KIND>
+__device__ __forceinline__ double mms_source(const MmsLine& m, int i0) {
+  return mms_call<KIND>(double(i0), m.h, m.ta, m.dta, m.c1y, m.c3y, m.k1, m.k2, m.k3);
 }
 
 // Forward reaction: buf holds the stage value (physical); replaced by f.
@@ -357,7 +388,8 @@ __device__ __forceinline__ bool pw_reaction_n(const StageArgs<T>& a, T* buf, lon
     rxn_eval_k<T, NS, KIND>(rx, u, f);
     if constexpr (NS == 1 && KIND >= RXN_HUXLEY_MMS) {
       const long long idx = tr.base + (long long)j * tr.rs + (long long)w * tr.cs;
-      f[0] += T(mms_source(a.rxn, a.t, idx, a.n0, a.n1));
+      const MmsLine m = mms_line(a.rxn, a.t, (idx / a.n0) % a.n1);
+      f[0] += T(mms_source<KIND>(m, (int)(idx % a.n0)));
     }
 #pragma unroll
     for (int s = 0; s < NS; ++s) {

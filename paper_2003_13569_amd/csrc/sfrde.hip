@@ -1533,7 +1533,7 @@ int sfrde_plan_batch(sfrde_plan_t* out, int32_t batch, int32_t ndim, const int64
     r.np = nparams;
     for (int k = 0; k < nparams; ++k) r.p[k] = params[(size_t)b * nparams + k];
     if (reaction >= RXN_HUXLEY_MMS) {
-      // source constants of Examples 1 and 2 (Section 5.1), see mms_source()
+      // source constants of Examples 1 and 2 (Section 5.1), see mms_line()
       const double pi = 3.14159265358979323846, a = alpha[(size_t)b * nspecies],
                    k = kappa[(size_t)b * nspecies];
       double* c = r.p + MMS_P0;

@@ -961,16 +961,11 @@ __device__ __forceinline__ double line_weight(long long line, long long n1, long
 // f of the stage values in ya, yb (in place). Two-species columns hold one
 // species each, its partner 8 lanes away; every lane forms both components
 // and keeps its own. Returns whether a value was not finite.
-static __device__ __attribute__((noinline)) double mms_source_call(const Rxn& r, double t, long long idx,
-                                                            long long n0, long long n1) {
-  return mms_source(r, t, idx, n0, n1);
-}
-
 template <int KIND, typename T, class XF>
 __device__ __forceinline__ void wave_react_rb(const XF& xf, const StageArgs<T>& a,
                                               const RxnT<T>& rx, const XLane<T>& ln,
-                                              const PosOff<XF>& po, int rb, T (&va)[4],
-                                              T (&vb)[4], T& chk) {
+                                              const PosOff<XF>& po, const MmsLine& ml, int rb,
+                                              T (&va)[4], T (&vb)[4], T& chk) {
   const T lin = ln.sp == 0 ? rx.lin[0] : ln.sp == 1 ? rx.lin[1] : ln.sp == 2 ? rx.lin[2] : rx.lin[3];
 #pragma unroll
   for (int side = 0; side < 2; ++side)
@@ -987,8 +982,7 @@ __device__ __forceinline__ void wave_react_rb(const XF& xf, const StageArgs<T>& 
         rxn_eval_k<T, 1, KIND>(rx, u, o);
         unsigned ia, ib;
         po.at(po.lane, rb, r, ia, ib);
-        const long long idx = ln.line * xf.n() + (side ? ib : ia);
-        f = o[0] + T(mms_source_call(a.rxn, a.t, idx, a.n0, a.n1));
+        f = o[0] + T(mms_source<KIND>(ml, (int)(side ? ib : ia)));
       } else {
         const T oth = ror8(own);
         const T u[2] = {ln.sp == 0 ? own : oth, ln.sp == 0 ? oth : own};
@@ -1006,8 +1000,8 @@ __device__ __forceinline__ void wave_react_rb(const XF& xf, const StageArgs<T>& 
 
 template <int KIND, typename T, class XF>
 __device__ __forceinline__ bool wave_react_k(const XF& xf, const StageArgs<T>& a,
-                                             const XLane<T>& ln, typename XF::Vals& ya,
-                                             typename XF::Vals& yb) {
+                                             const XLane<T>& ln, const MmsLine& ml,
+                                             typename XF::Vals& ya, typename XF::Vals& yb) {
   const RxnT<T> rx(a.rxn);
   const PosOff<XF> po(xf, 1u, 0u);
   T chk = T(0);
@@ -1015,26 +1009,26 @@ __device__ __forceinline__ bool wave_react_k(const XF& xf, const StageArgs<T>& a
     constexpr int rb = decltype(rbc)::value;
     if (!xf.used(rb)) return;
     __builtin_amdgcn_sched_barrier(0);
-    wave_react_rb<KIND>(xf, a, rx, ln, po, rb, ya[rb], yb[rb], chk);
+    wave_react_rb<KIND>(xf, a, rx, ln, po, ml, rb, ya[rb], yb[rb], chk);
   });
   return !(chk == T(0));
 }
 
 template <bool SRC, typename T, class XF>
 __device__ __forceinline__ bool wave_react(const XF& xf, const StageArgs<T>& a,
-                                           const XLane<T>& ln, typename XF::Vals& ya,
-                                           typename XF::Vals& yb) {
+                                           const XLane<T>& ln, const MmsLine& ml,
+                                           typename XF::Vals& ya, typename XF::Vals& yb) {
   if constexpr (SRC) {
-    if (a.rxn.kind == RXN_HUXLEY_MMS) return wave_react_k<RXN_HUXLEY_MMS>(xf, a, ln, ya, yb);
-    return wave_react_k<RXN_FISHER_MMS>(xf, a, ln, ya, yb);
+    if (a.rxn.kind == RXN_HUXLEY_MMS) return wave_react_k<RXN_HUXLEY_MMS>(xf, a, ln, ml, ya, yb);
+    return wave_react_k<RXN_FISHER_MMS>(xf, a, ln, ml, ya, yb);
   }
   __builtin_amdgcn_sched_barrier(0);
   switch (a.rxn.kind) {  // uniform
-    case RXN_LINEAR: return wave_react_k<RXN_LINEAR>(xf, a, ln, ya, yb);
-    case RXN_FHN: return wave_react_k<RXN_FHN>(xf, a, ln, ya, yb);
-    case RXN_GRAY_SCOTT: return wave_react_k<RXN_GRAY_SCOTT>(xf, a, ln, ya, yb);
-    case RXN_SCHNAKENBERG: return wave_react_k<RXN_SCHNAKENBERG>(xf, a, ln, ya, yb);
-    default: return wave_react_k<RXN_GM>(xf, a, ln, ya, yb);
+    case RXN_LINEAR: return wave_react_k<RXN_LINEAR>(xf, a, ln, ml, ya, yb);
+    case RXN_FHN: return wave_react_k<RXN_FHN>(xf, a, ln, ml, ya, yb);
+    case RXN_GRAY_SCOTT: return wave_react_k<RXN_GRAY_SCOTT>(xf, a, ln, ml, ya, yb);
+    case RXN_SCHNAKENBERG: return wave_react_k<RXN_SCHNAKENBERG>(xf, a, ln, ml, ya, yb);
+    default: return wave_react_k<RXN_GM>(xf, a, ln, ml, ya, yb);
   }
 }
 
@@ -1137,10 +1131,12 @@ __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wx(StageArgs<T> a, 
   __syncthreads();
   for (int tile = run.t; tile < run.t1;) {
     const XLane<T> ln(tl, a.S, tile, xf.i);
+    MmsLine ml{};
+    if constexpr (SRC) ml = mms_line(a.rxn, a.t, ln.line % a.n1);
     xf.pair(ya, yb);
     if (a.st_phys)
       store_stage(xf, tl, ln, tile, total, a.st_phys + (long long)a.mode * a.S * total, ya, yb);
-    bad |= wave_react<SRC>(xf, a, ln, ya, yb);
+    bad |= wave_react<SRC>(xf, a, ln, ml, ya, yb);
     // (x lines are loaded after the stores: beside the operands their vectors
     // do not fit the registers)
     store_lines<T>(xf, tl, a.S, total, tile, a.P, ya, yb, [] {}, NoWeight{});
@@ -2319,6 +2315,8 @@ __global__ __launch_bounds__(64 * NB) void k_gx(StageArgs<T> a, WaveAxis ax, Wav
   if (xf.on) load_line_rb<T>(xf, a.P + ln.sp * total + ln.line * xf.n(), va, vb);
   xf.pair_rows(ma, mb);
   xf.nat_rows(me, mo);
+  MmsLine ml{};
+  if constexpr (SRC) ml = mms_line(a.rxn, a.t, ln.line % a.n1);
   xf.pair_shared(smem, 0, ma, mb, va, vb);
   if (xf.on) {
     const PosOff<W> po(xf, 1u, 0u);
@@ -2345,16 +2343,16 @@ __global__ __launch_bounds__(64 * NB) void k_gx(StageArgs<T> a, WaveAxis ax, Wav
     const W& w = xf;
     if constexpr (SRC) {
       if (a.rxn.kind == RXN_HUXLEY_MMS)
-        wave_react_rb<RXN_HUXLEY_MMS>(w, a, rx, ln, po, xf.rb, va, vb, chk);
+        wave_react_rb<RXN_HUXLEY_MMS>(w, a, rx, ln, po, ml, xf.rb, va, vb, chk);
       else
-        wave_react_rb<RXN_FISHER_MMS>(w, a, rx, ln, po, xf.rb, va, vb, chk);
+        wave_react_rb<RXN_FISHER_MMS>(w, a, rx, ln, po, ml, xf.rb, va, vb, chk);
     } else {
       switch (a.rxn.kind) {  // uniform
-        case RXN_LINEAR: wave_react_rb<RXN_LINEAR>(w, a, rx, ln, po, xf.rb, va, vb, chk); break;
-        case RXN_FHN: wave_react_rb<RXN_FHN>(w, a, rx, ln, po, xf.rb, va, vb, chk); break;
-        case RXN_GRAY_SCOTT: wave_react_rb<RXN_GRAY_SCOTT>(w, a, rx, ln, po, xf.rb, va, vb, chk); break;
-        case RXN_SCHNAKENBERG: wave_react_rb<RXN_SCHNAKENBERG>(w, a, rx, ln, po, xf.rb, va, vb, chk); break;
-        default: wave_react_rb<RXN_GM>(w, a, rx, ln, po, xf.rb, va, vb, chk); break;
+        case RXN_LINEAR: wave_react_rb<RXN_LINEAR>(w, a, rx, ln, po, ml, xf.rb, va, vb, chk); break;
+        case RXN_FHN: wave_react_rb<RXN_FHN>(w, a, rx, ln, po, ml, xf.rb, va, vb, chk); break;
+        case RXN_GRAY_SCOTT: wave_react_rb<RXN_GRAY_SCOTT>(w, a, rx, ln, po, ml, xf.rb, va, vb, chk); break;
+        case RXN_SCHNAKENBERG: wave_react_rb<RXN_SCHNAKENBERG>(w, a, rx, ln, po, ml, xf.rb, va, vb, chk); break;
+        default: wave_react_rb<RXN_GM>(w, a, rx, ln, po, ml, xf.rb, va, vb, chk); break;
       }
     }
     if (!(chk == T(0))) a.flag[0] = 1;
