@@ -564,15 +564,15 @@ __global__ __launch_bounds__(256) void k_fz(StageArgs<T> a, FftPairs fp) {
   typename FT::Vals va, vb;
   io.load_all(a.src ? a.src : a.P, va, vb);
   if constexpr (MODE >= 0) {
-    auto run = [&](auto tab) {
-      constexpr int TAB = decltype(tab)::value;
+    auto run = [&](auto co) {
+      constexpr int CO = decltype(co)::value;
       // the retained arrays in flight over the transform, where they fit
       constexpr bool AHEAD = FT::E * sizeof(T) <= 64;
       CombineIn<T> in[FT::E / 4];
       auto read = [&](auto rbc) {
         constexpr int rb = decltype(rbc)::value;
         io.load(MODE <= 1 ? a.uhat : a.acc, io.offs(rb), in[rb].x1[0], in[rb].x1[1]);
-        wave_combine_in<MODE, false, TAB>(io, a, rb, in[rb]);
+        wave_combine_in<MODE, CO>(io, a, rb, in[rb]);
       };
       if constexpr (AHEAD) static_for<FT::E / 4>(read);
       ft.hartley(va, vb);
@@ -586,7 +586,7 @@ __global__ __launch_bounds__(256) void k_fz(StageArgs<T> a, FftPairs fp) {
           ya[r] = va[4 * rb + r];
           yb[r] = vb[4 * rb + r];
         }
-        wave_combine_out<MODE, false, TAB>(io, a, rb, 0.f, T(0), T(0), lz, in[rb], ya, yb);
+        wave_combine_out<MODE, CO>(io, a, rb, 0.f, T(0), T(0), lz, in[rb], ya, yb);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           va[4 * rb + r] = ya[r];
@@ -595,9 +595,9 @@ __global__ __launch_bounds__(256) void k_fz(StageArgs<T> a, FftPairs fp) {
       });
     };
     if (a.ltab)
-      run(std::integral_constant<int, 1>{});
+      run(std::integral_constant<int, CO_LTAB>{});
     else
-      run(std::integral_constant<int, 0>{});
+      run(std::integral_constant<int, CO_TABS>{});
   } else {
     if (!a.src) ft.hartley(va, vb);
     if (a.mode == MODE_INIT) io.store_all(a.uhat, va, vb);

@@ -833,7 +833,8 @@ int launch_z(sfrde_plan_s* p, int mode, const void* src, T* st_fhat, T* uhat = n
   if (uhat) a.uhat = uhat;
   const long long pk = prof_start(p, KC_Z);
   if (p->wcls[ax] >= 0) {
-    TRY(launch_wave(p, ax, mode > 3 ? WK_ZINIT : (p->lfly ? WK_ZFLY : WK_Z) + mode, a));
+    const int k = p->lfly ? WK_ZFLY : p->ltab ? WK_Z : WK_ZTABS;
+    TRY(launch_wave(p, ax, mode > 3 ? WK_ZINIT : k + mode, a));
   } else if (p->use_f[ax]) {
     TRY(launch_fft<T>(p, ax, mode > 3 ? WK_ZINIT : WK_Z + mode, a));
   } else if (p->n[ax] == 1)

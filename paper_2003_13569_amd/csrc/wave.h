@@ -1339,34 +1339,35 @@ __device__ __forceinline__ void lam_z(const XF& xf, const float* lam, int side, 
   v[3] = q.w;
 }
 
-// What the stage combine of a row block reads, both sides (TAB: whether the plan
-// has the table of L, -1 asked at run time): the retained arrays
+// Where a Z kernel's coefficients come from: L formed in the kernel, the table of
+// L, the tables of the coefficients. (At compile time: a choice at run time put
+// the values read into scratch memory, 12 to 136 bytes per lane.)
+enum { CO_FLY = 0, CO_LTAB = 1, CO_TABS = 2 };
+
+// What the stage combine of a row block reads, both sides: the retained arrays
 // x1 (stages 0, 1: u_hat; 2, 3: acc; loaded by the caller) and x2 (stage 1:
 // acc; 2: c_tilde), L (in t0) or the coefficients.
 template <typename T>
 struct CombineIn {
   T x1[2][4], x2[2][4], t0[2][4], t1[2][4], t2[2][4], t3[2][4];
 };
-template <int MODE, bool FLY, int TAB = -1, typename T, class IO>
+template <int MODE, int CO, typename T, class IO>
 __device__ __forceinline__ void wave_combine_in(const IO& io, const StageArgs<T>& a, int rb,
                                                 CombineIn<T>& in) {
   const long long cst = (long long)a.S * a.g.total;
   const auto of = io.offs(rb);
-  if constexpr (!FLY) {
-    if (TAB < 0 ? a.ltab != nullptr : TAB) {
-      io.load(a.ltab, of, in.t0[0], in.t0[1]);
-    } else {
-      if (MODE <= 1) io.load(a.coef + C_Q * cst, of, in.t0[0], in.t0[1]);
-      if (MODE <= 2) io.load(a.coef + C_PHI * cst, of, in.t1[0], in.t1[1]);
-      io.load(a.coef + (MODE == 0 ? C_R : MODE == 3 ? C_PHI3 : C_PHI2) * cst, of, in.t2[0], in.t2[1]);
-      if (MODE == 0) io.load(a.coef + C_PHI1 * cst, of, in.t3[0], in.t3[1]);
-    }
+  if constexpr (CO == CO_LTAB) io.load(a.ltab, of, in.t0[0], in.t0[1]);
+  if constexpr (CO == CO_TABS) {
+    if (MODE <= 1) io.load(a.coef + C_Q * cst, of, in.t0[0], in.t0[1]);
+    if (MODE <= 2) io.load(a.coef + C_PHI * cst, of, in.t1[0], in.t1[1]);
+    io.load(a.coef + (MODE == 0 ? C_R : MODE == 3 ? C_PHI3 : C_PHI2) * cst, of, in.t2[0], in.t2[1]);
+    if (MODE == 0) io.load(a.coef + C_PHI1 * cst, of, in.t3[0], in.t3[1]);
   }
   if (MODE == 1 || MODE == 2) io.load_priv(MODE == 1 ? a.acc : a.ctil, rb, of, in.x2[0], in.x2[1]);
 }
 
 // Stage combine (MODE 0..3) of a row block, both sides.
-template <int MODE, bool FLY, int TAB = -1, typename T, class IO>
+template <int MODE, int CO, typename T, class IO>
 __device__ __forceinline__ void wave_combine_out(const IO& io, const StageArgs<T>& a, int rb,
                                                  float lxy, T kt, T ha, const float (&lz)[2][4],
                                                  const CombineIn<T>& in, T (&va)[4], T (&vb)[4]) {
@@ -1378,14 +1379,14 @@ __device__ __forceinline__ void wave_combine_out(const IO& io, const StageArgs<T
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       T c0 = T(0), c1 = T(0), c2 = T(0), c3 = T(0);
-      if constexpr (FLY) {
+      if constexpr (CO == CO_FLY) {
         // Lambda is 0 or at least the smallest nonzero eigenvalue, far from
         // denormals: the hardware log2 / exp2 (about 1 ulp) suffice, and give
         // 0 at Lambda = 0 (log2 0 = -inf, alpha > 0) without a branch
         const float L =
             kt * __builtin_amdgcn_exp2f(ha * __builtin_amdgcn_logf(lxy + lz[side][r]));
         stage_coefs_L<T>(MODE, L, a.tau, c0, c1, c2, c3);
-      } else if (TAB < 0 ? a.ltab != nullptr : TAB) {
+      } else if constexpr (CO == CO_LTAB) {
         stage_coefs_L<T>(MODE, in.t0[side][r], a.tau, c0, c1, c2, c3);
       } else {
         if (MODE <= 1) c0 = in.t0[side][r];
@@ -1424,13 +1425,13 @@ __device__ __forceinline__ void wave_combine_out(const IO& io, const StageArgs<T
 
 // Z: forward transform along the last axis, stage combine, inverse transform
 // (in place on P). MODE 0..3; MODE < 0: MODE_INIT or MODE_RESTORE (a.mode).
-// FLY: L formed in the kernel from the eigenvalues (FP32 P13 plans). Memory
+// CO: CO_FLY for FP32 P13 plans. Memory
 // bound at 256^3 FP32, on 64-byte rows at 256 KB strides: 3.5 TB/s over five
 // fields in stage 0 with every array in the fields' order; with c_tilde and acc
 // in register order and the sweep a step went 1.43 -> 1.34 ms (1.43 in 8-wave
 // blocks on the same GPU; the four stages 168 to 137 us there, 158 to 124 here). 128^3 FP32 32-36 -> 18 us a
 // stage, FP64 76-85 -> 42-55.
-template <typename T, int NB, int LAY, int MODE, bool FLY>
+template <typename T, int NB, int LAY, int MODE, int CO>
 __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wz(StageArgs<T> a, WaveAxis ax, WaveTiles tl) {
   to_member(a);
   extern __shared__ __align__(16) char smem[];
@@ -1446,12 +1447,12 @@ __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wz(StageArgs<T> a, 
   if (run.t < run.t1) load(run.t);
   xf.copy_table(smem);
   float* lam = reinterpret_cast<float*>(smem + XF::lds_bytes());
-  if constexpr (FLY) fill_lam(xf, a, lam);
+  if constexpr (CO == CO_FLY) fill_lam(xf, a, lam);
   __syncthreads();
   for (int tile = run.t; tile < run.t1;) {
     run.sync();
     const StridedLane<T> ln(tl, xf.n(), tile, xf.i);
-    const RowIO<T, XF> io(xf, tl, ln, tile, FLY || tl.priv);
+    const RowIO<T, XF> io(xf, tl, ln, tile, CO == CO_FLY || tl.priv);
     if constexpr (MODE >= 0) {
       // the first retained array, in flight over the transform (FP32)
       typename XF::Vals xa, xb;
@@ -1467,7 +1468,7 @@ __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wz(StageArgs<T> a, 
       xf.pair(ya, yb);
       float lxy = 0.f;
       T kt = T(0), ha = T(0);
-      if constexpr (FLY) {
+      if constexpr (CO == CO_FLY) {
         int x, y;
         lxy = lam_xy(a, lam + 32 * NB, ln.ib, x, y);
         kt = pick_species(a.kt, ln.o);
@@ -1478,7 +1479,7 @@ __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wz(StageArgs<T> a, 
         if (!xf.used(rb)) return;
         if constexpr (!XF::F32) load_x1(rbc);
         float lz[2][4] = {};
-        if constexpr (FLY) {
+        if constexpr (CO == CO_FLY) {
           lam_z(xf, lam, 0, rb, lz[0]);
           lam_z(xf, lam, 1, rb, lz[1]);
         }
@@ -1488,8 +1489,8 @@ __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wz(StageArgs<T> a, 
           in.x1[0][r] = xa[rb][r];
           in.x1[1][r] = xb[rb][r];
         }
-        wave_combine_in<MODE, FLY>(io, a, rb, in);
-        wave_combine_out<MODE, FLY>(io, a, rb, lxy, kt, ha, lz, in, ya[rb], yb[rb]);
+        wave_combine_in<MODE, CO>(io, a, rb, in);
+        wave_combine_out<MODE, CO>(io, a, rb, lxy, kt, ha, lz, in, ya[rb], yb[rb]);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           keep(ya[rb][r]);
@@ -2438,7 +2439,7 @@ __device__ __forceinline__ float group_lam(const XF& xf, const StageArgs<T>& a, 
 }
 
 // Z of one tile (k_wz).
-template <typename T, int NB, int LAY, int MODE, bool FLY>
+template <typename T, int NB, int LAY, int MODE, int CO>
 __global__ __launch_bounds__(64 * NB) void k_gz(StageArgs<T> a, WaveAxis ax, WaveTiles tl) {
   to_member(a);
   extern __shared__ __align__(16) char smem[];
@@ -2447,7 +2448,7 @@ __global__ __launch_bounds__(64 * NB) void k_gz(StageArgs<T> a, WaveAxis ax, Wav
   const XF xf(ax);
   const W& w = xf;
   const StridedLane<T> ln(tl, xf.n(), blockIdx.x, xf.i);
-  const RowIO<T, W> io(w, tl, ln, blockIdx.x, FLY || tl.priv);
+  const RowIO<T, W> io(w, tl, ln, blockIdx.x, CO == CO_FLY || tl.priv);
   const auto of = io.offs(xf.rb);
   T va[4] = {}, vb[4] = {};
   typename XF::Rows ma, mb;
@@ -2458,12 +2459,12 @@ __global__ __launch_bounds__(64 * NB) void k_gz(StageArgs<T> a, WaveAxis ax, Wav
       io.load(a.uhat, of, in.x1[0], in.x1[1]);
     else
       io.load_priv(a.acc, xf.rb, of, in.x1[0], in.x1[1]);
-    wave_combine_in<MODE, FLY>(io, a, xf.rb, in);
+    wave_combine_in<MODE, CO>(io, a, xf.rb, in);
   }
   xf.pair_rows(ma, mb);
   float lz[2][4] = {}, lxy = 0.f;
   T kt = T(0), ha = T(0);
-  if constexpr (FLY) {
+  if constexpr (CO == CO_FLY) {
     int x, y;
     lxy = group_lam(xf, a, ln.ib, lz, x, y);
     kt = pick_species(a.kt, ln.o);
@@ -2471,7 +2472,7 @@ __global__ __launch_bounds__(64 * NB) void k_gz(StageArgs<T> a, WaveAxis ax, Wav
   }
   if (MODE >= 0 || !a.src) xf.pair_shared(smem, 0, ma, mb, va, vb);
   if constexpr (MODE >= 0) {
-    if (xf.on) wave_combine_out<MODE, FLY>(io, a, xf.rb, lxy, kt, ha, lz, in, va, vb);
+    if (xf.on) wave_combine_out<MODE, CO>(io, a, xf.rb, lxy, kt, ha, lz, in, va, vb);
   } else {
     if (a.mode == MODE_INIT && xf.on) io.store(a.uhat, of, va, vb);
 #pragma unroll
@@ -2595,8 +2596,9 @@ enum {
   WK_SY,      // one transform, strided axis
   WK_SY2,     // the same with two columns per lane (FP32, even inner extent)
   WK_ZINIT,   // Z: MODE_INIT, MODE_RESTORE
-  WK_Z,       // Z stages 0..3
-  WK_ZFLY = WK_Z + 4,  // Z stages with L formed in the kernel (FP32, not odd axes)
+  WK_Z,       // Z stages 0..3, the table of L
+  WK_ZTABS = WK_Z + 4,    // Z stages, the tables of the coefficients
+  WK_ZFLY = WK_ZTABS + 4,  // Z stages with L formed in the kernel (FP32, not odd axes)
   WK_XADJ = WK_ZFLY + 4,  // X adjoint, without / with parameter partials
   WK_ZADJ = WK_XADJ + 2,  // Z adjoint from tables
   WK_ZADJFLY,             // Z adjoint, L formed in the kernel: modes 0 .. MODE_INIT
@@ -2614,10 +2616,14 @@ struct WaveKernels {
 template <typename T, int NB, int LAY, bool FN, int MODE = 3>
 void wave_z_kernels(WaveKernels& k) {
   constexpr bool FLY = LAY != WL_ODD && sizeof(T) == 4 && FN;
-  k.grp[WK_Z + MODE] = reinterpret_cast<const void*>(&k_gz<T, NB, LAY, MODE, false>);
-  if constexpr (FLY) k.grp[WK_ZFLY + MODE] = reinterpret_cast<const void*>(&k_gz<T, NB, LAY, MODE, true>);
-  if constexpr (FN) k.fn[WK_Z + MODE] = reinterpret_cast<const void*>(&k_wz<T, NB, LAY, MODE, false>);
-  if constexpr (FLY) k.fn[WK_ZFLY + MODE] = reinterpret_cast<const void*>(&k_wz<T, NB, LAY, MODE, true>);
+  k.grp[WK_Z + MODE] = reinterpret_cast<const void*>(&k_gz<T, NB, LAY, MODE, CO_LTAB>);
+  k.grp[WK_ZTABS + MODE] = reinterpret_cast<const void*>(&k_gz<T, NB, LAY, MODE, CO_TABS>);
+  if constexpr (FLY) k.grp[WK_ZFLY + MODE] = reinterpret_cast<const void*>(&k_gz<T, NB, LAY, MODE, CO_FLY>);
+  if constexpr (FN) {
+    k.fn[WK_Z + MODE] = reinterpret_cast<const void*>(&k_wz<T, NB, LAY, MODE, CO_LTAB>);
+    k.fn[WK_ZTABS + MODE] = reinterpret_cast<const void*>(&k_wz<T, NB, LAY, MODE, CO_TABS>);
+  }
+  if constexpr (FLY) k.fn[WK_ZFLY + MODE] = reinterpret_cast<const void*>(&k_wz<T, NB, LAY, MODE, CO_FLY>);
   if constexpr (MODE > 0) wave_z_kernels<T, NB, LAY, FN, MODE - 1>(k);
 }
 
@@ -2648,7 +2654,7 @@ WaveKernels wave_kernels() {
     k.grp[WK_XSRC] = reinterpret_cast<const void*>(&k_gx<T, NB, LAY, true>);
   k.grp[WK_SX] = reinterpret_cast<const void*>(&k_gsx<T, NB, LAY>);
   k.grp[WK_SY] = reinterpret_cast<const void*>(&k_gsy<T, NB, LAY>);
-  k.grp[WK_ZINIT] = reinterpret_cast<const void*>(&k_gz<T, NB, LAY, -1, false>);
+  k.grp[WK_ZINIT] = reinterpret_cast<const void*>(&k_gz<T, NB, LAY, -1, CO_LTAB>);
   k.grp[WK_XADJ] = reinterpret_cast<const void*>(&k_gxadj<T, NB, LAY, false>);
   k.grp[WK_XADJ + 1] = reinterpret_cast<const void*>(&k_gxadj<T, NB, LAY, true>);
   k.grp[WK_ZADJ] = reinterpret_cast<const void*>(&k_gzadj<T, NB, LAY, -1, false>);
@@ -2660,7 +2666,7 @@ WaveKernels wave_kernels() {
     k.fn[WK_SX] = reinterpret_cast<const void*>(&k_wsx<T, NB, LAY>);
     k.fn[WK_SY] = reinterpret_cast<const void*>(&k_wsy<T, NB, LAY>);
     if constexpr (sizeof(T) == 4) k.fn[WK_SY2] = reinterpret_cast<const void*>(&k_wsy2<NB, LAY>);
-    k.fn[WK_ZINIT] = reinterpret_cast<const void*>(&k_wz<T, NB, LAY, -1, false>);
+    k.fn[WK_ZINIT] = reinterpret_cast<const void*>(&k_wz<T, NB, LAY, -1, CO_LTAB>);
     k.fn[WK_XADJ] = reinterpret_cast<const void*>(&k_wxadj<T, NB, LAY, false>);
     k.fn[WK_XADJ + 1] = reinterpret_cast<const void*>(&k_wxadj<T, NB, LAY, true>);
     k.fn[WK_ZADJ] = reinterpret_cast<const void*>(&k_wzadj<T, NB, LAY, -1, false>);
