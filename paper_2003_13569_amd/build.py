@@ -15,7 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 SRC = os.path.join(HERE, "csrc", "sfrde.hip")
 PART = os.path.join(HERE, "csrc", "wave_part.hip")
-NPARTS = 23  # classes of csrc/wave_parts.h, one translation unit each
+NPARTS = 28  # classes of csrc/wave_parts.h, one translation unit each
 LIB = os.path.join(HERE, "libsfrde.so")
 
 FLAGS = [

@@ -411,7 +411,11 @@ int wave_class_of(int dtype, int bc, long long n, bool source) {
   // periodic axes of 256 and 512 points run as FFTs: 256^2 FP64 102 us per step
   // against 196 (FP32 equal), 512^2 FP32 153 against 152 for the products
   if (per && (n == 256 || n == 512)) return -1;
-  if (!f32 && half <= (odd ? 128 : 144)) return odd ? WC_F64_8O : WC_F64_9E;
+  if (!f32 && half <= (odd ? 128 : 144)) {  // the class whose blocks the axis fills
+    if (odd) return (n - 1) / 2 / 2 + 1 <= 48 ? WC_F64_6O : WC_F64_8O;  // points of segment 0
+    return half <= 80 ? WC_F64_5E : half <= 96 ? WC_F64_6E : half <= 112 ? WC_F64_7E
+         : half <= 128 ? WC_F64_8E : WC_F64_9E;
+  }
   // to 512 points on the group kernels (the dense kernels / these, per step:
   // 300 x 333 FP32 6280 / 117 us, 390 x 280 FP64 7257 / 313, 512^2 Dirichlet
   // FP32 10983 / 152); beyond, the matrix of an axis leaves the caches

@@ -197,7 +197,8 @@ __device__ __forceinline__ double ror8(double v) {
 //         position 32 ks + (e < 4 ? 4 g + e : 12 + 4 g + e);
 //   FP64: [half][ks][g][row], position 4 ks + g.
 // LDSA: read from LDS (copied there by the constructor's caller), else from
-// global memory (FP64 axes past 128 points: the matrix does not fit).
+// global memory (FP64 axes past 192 points: the matrix does not fit). 192^3 FP64
+// in steps with the matrix of 6 blocks in LDS / from global memory: 2.09 / 2.36 ms.
 template <typename T, int NB>
 struct WaveTab;
 template <int NB>
@@ -213,12 +214,26 @@ struct WaveTab<double, NB> {
 
 template <typename T, int NB>
 constexpr bool wave_lds_a() {
-  return WaveTab<T, NB>::bytes <= 128 * 1024;
+  return WaveTab<T, NB>::bytes <= 144 * 1024;
+}
+
+// Classes whose row blocks are all in use (WaveXf).
+template <typename T, int NB>
+constexpr bool wave_full() {
+  return sizeof(T) == 8 && NB > 4 && NB < 9;
 }
 
 template <typename T, int NB, int LAY>
 struct WaveXf {
   static constexpr bool EX = LAY == WL_EXACT, ODD = LAY == WL_ODD;
+  // FP64 axes of 129 to 256 points: a class for each number of row blocks, all of
+  // them in use (with 9 of them the registers do not last: 100 spilled). A matrix
+  // from global memory is read ahead, the next product's entries while this one
+  // runs; with blocks left out at run time the compiler cannot count the loads in
+  // flight and waits for all of them. Per launch, FP64, one class of 9 blocks / one
+  // for each: 240^3 X 708 / 435 us, Y 298 / 230, Z 703 / 594; 150^3 X 149 / 77, Y 62 /
+  // 48, Z 143 / 96 (8-wave phases 170, 109, 219).
+  static constexpr bool FULL = wave_full<T, NB>();
   static_assert(!ODD || NB % 2 == 0, "two segments of NB / 2 row blocks");
   using Tab = WaveTab<T, NB>;
   static constexpr bool F32 = std::is_same<T, float>::value;
@@ -263,7 +278,7 @@ struct WaveXf {
   __device__ __forceinline__ static constexpr int seg(int rb) { return ODD && 2 * rb >= NB ? 1 : 0; }
   __device__ __forceinline__ static constexpr int sb(int rb) { return seg(rb) ? rb - NB / 2 : rb; }
   __device__ __forceinline__ bool used(int rb) const {
-    return EX || sb(rb) < (seg(rb) ? ax.nb1 : ax.nb);
+    return EX || FULL || sb(rb) < (seg(rb) ? ax.nb1 : ax.nb);
   }
   // position in the segment of register r of row block rb
   __device__ __forceinline__ int q(int rb, int r) const { return 16 * sb(rb) + PR * r + PG * g; }
@@ -557,7 +572,7 @@ struct WaveXf {
     if constexpr (!LDSA) fetch<0>(lnat, A[0]);
     static_for<NB>([&](auto rbc) {
       constexpr int rb = decltype(rbc)::value;
-      if (!EX && 16 * rb >= rows_e) return;
+      if (!EX && (!FULL || (ODD && rb + 1 == NB)) && 16 * rb >= rows_e) return;
       T e[4], d[4];
       const unsigned lo = lnat + rb * 16 * UB;
       if constexpr (LDSA) {

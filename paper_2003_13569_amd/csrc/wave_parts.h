@@ -1,5 +1,6 @@
 // The size classes of the wave engine (wave.h). A class NB holds axes of up to
-// 32 NB points (n odd: 32 NB - 1, periodic: 32 NB - 1). The library is built
+// 32 NB points (n odd: 32 NB - 1, periodic: 32 NB - 1); FP64 classes of 5 to 8
+// blocks those that fill all of them (wave_full). The library is built
 // from one translation unit per class (wave_part.hip with SFRDE_PART) and the
 // host code (SFRDE_IN_PARTS). sfrde.hip alone, without either, holds none of them:
 // a build for checks of the host code, which refuses plans with engine axes (all
@@ -15,6 +16,7 @@ enum {
   WC_F32_8X, WC_F32_8E, WC_F32_8O, WC_F64_2X, WC_F64_2E, WC_F64_2O,
   WC_F64_4X, WC_F64_4E, WC_F64_4O, WC_F64_8X, WC_F64_8O, WC_F64_9E,
   WC_F32_6X, WC_F32_16E, WC_F32_16O, WC_F64_16E, WC_F64_16O,
+  WC_F64_5E, WC_F64_6E, WC_F64_7E, WC_F64_8E, WC_F64_6O,
   WC_COUNT
 };
 
@@ -106,6 +108,21 @@ SFRDE_WAVE_CLASS(WC_F64_16E, double, 16, WL_EVEN)
 #endif
 #if SFRDE_HAS(22)
 SFRDE_WAVE_CLASS(WC_F64_16O, double, 16, WL_ODD)
+#endif
+#if SFRDE_HAS(23)
+SFRDE_WAVE_CLASS(WC_F64_5E, double, 5, WL_EVEN)
+#endif
+#if SFRDE_HAS(24)
+SFRDE_WAVE_CLASS(WC_F64_6E, double, 6, WL_EVEN)
+#endif
+#if SFRDE_HAS(25)
+SFRDE_WAVE_CLASS(WC_F64_7E, double, 7, WL_EVEN)
+#endif
+#if SFRDE_HAS(26)
+SFRDE_WAVE_CLASS(WC_F64_8E, double, 8, WL_EVEN)
+#endif
+#if SFRDE_HAS(27)
+SFRDE_WAVE_CLASS(WC_F64_6O, double, 6, WL_ODD)
 #endif
 #undef SFRDE_HAS
 #undef SFRDE_WAVE_CLASS
