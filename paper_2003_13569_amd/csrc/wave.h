@@ -141,17 +141,20 @@ struct WaveTiles {
 struct WaveRun {
   int t, t1, rounds, stride;
   __device__ __forceinline__ explicit WaveRun(const WaveTiles& tl) : WaveRun(tl, tl.ntiles) {}
-  __device__ __forceinline__ WaveRun(const WaveTiles& tl, int ntiles) {
-    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int waves = (int)(blockDim.x >> 6), all = (int)gridDim.x * waves;
-    if (tl.sweep && ntiles > all) {
-      t = (int)blockIdx.x * waves + w;
+  __device__ __forceinline__ WaveRun(const WaveTiles& tl, int ntiles)
+      : WaveRun(ntiles, tl.sweep, (int)blockIdx.x, (int)gridDim.x,
+                __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), (int)(blockDim.x >> 6)) {}
+  // wave w of `waves` in block `block` of `grid`
+  __device__ __forceinline__ WaveRun(int ntiles, int sweep, int block, int grid, int w, int waves) {
+    const int all = grid * waves;
+    if (sweep && ntiles > all) {
+      t = block * waves + w;
       t1 = ntiles;
       stride = all;
-      rounds = (ntiles - (int)blockIdx.x * waves + all - 1) / all;
+      rounds = (ntiles - block * waves + all - 1) / all;
     } else {
-      t = (int)((long long)blockIdx.x * ntiles / gridDim.x) + w;
-      t1 = (int)(((long long)blockIdx.x + 1) * ntiles / gridDim.x);
+      t = (int)((long long)block * ntiles / grid) + w;
+      t1 = (int)(((long long)block + 1) * ntiles / grid);
       stride = waves;
       rounds = 0;
     }

@@ -1,5 +1,6 @@
-"""The matrix-core engine's addresses on grids near its 32-bit limits, on the
-CPU: its row accesses compiled for the host (tests/host/row_io.hip)."""
+"""Index arithmetic of the matrix-core engine compiled for the host (tests/host):
+its row accesses on grids near the 32-bit limits (row_io.hip), and the tiles and
+barriers of its waves (wave_run.hip)."""
 import os
 import shutil
 import subprocess
@@ -9,19 +10,29 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-@pytest.fixture(scope="module")
-def row_io(tmp_path_factory):
+def _build(name, tmp_path_factory):
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     if not os.path.exists(hipcc):
         pytest.skip("hipcc not found")
-    exe = str(tmp_path_factory.mktemp("row_io") / "row_io")
+    exe = str(tmp_path_factory.mktemp(name) / name)
     subprocess.run([hipcc, "-O1", "-std=c++17", "--offload-arch=gfx950", "-Xclang",
                     "-target-feature", "-Xclang", "-packed-fp32-ops",
                     "-Wno-unused-command-line-argument", "-I", os.path.join(ROOT, "include"), "-I",
                     os.path.join(ROOT, "paper_2003_13569_amd", "csrc"),
-                    os.path.join(ROOT, "tests", "host", "row_io.hip"), "-o", exe],
+                    os.path.join(ROOT, "tests", "host", name + ".hip"), "-o", exe],
                    check=True, capture_output=True, text=True)
     return exe
+
+
+@pytest.fixture(scope="module")
+def row_io(tmp_path_factory):
+    return _build("row_io", tmp_path_factory)
+
+
+def test_every_tile_once_and_barriers_of_a_block_match(tmp_path_factory):
+    res = subprocess.run([_build("wave_run", tmp_path_factory)], capture_output=True, text=True,
+                         timeout=120)
+    assert res.returncode == 0, res.stdout + res.stderr
 
 
 # last axes of up to 16 blocks whose FP32 offsets fit 32 bits, with a tile across
