@@ -935,8 +935,6 @@ __global__ __launch_bounds__(NTHREADS) void k_single(SingleArgs<T> a) {
   const Geom& g = a.g;
   const long long tile = blockIdx.x;
   const TileRef tr = tile_ref(g, tile);
-  // tiles hold g.spt species (strided axes may hold one, with the species
-  // index in the outer block)
   const int S = g.spt;
   load_tile(g, tile, a.src, buf, S);
   __syncthreads();

@@ -400,7 +400,10 @@ int wave_class_of(int dtype, int bc, long long n, bool source) {
   const bool odd = !per && n % 2 == 1;
   const int c2 = f32 ? WC_F32_2X : WC_F64_2X, c4 = f32 ? WC_F32_4X : WC_F64_4X;
   const int lay = odd ? 2 : 1;
-  // exact classes (they have no kernel for manufactured sources)
+  // exact classes, multiples of 64 points: no index of theirs is checked or clamped,
+  // and the last axis has register order (they have no kernel for manufactured
+  // sources). 192^3 FP32 in its own class / in the 8-block one: 604 / 835 us a step,
+  // 192^2 65 / 74; FP64 192 points have the 6-block class without padding
   if (!per && !source && n == 64) return c2;
   if (!per && !source && n == 128) return c4;
   if (!per && !source && n == 192 && f32) return WC_F32_6X;
