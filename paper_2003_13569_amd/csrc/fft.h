@@ -35,7 +35,8 @@
 // A launch of 512^2 points is bound by the length of one wavefront's chain
 // (512 wavefronts on 256 CUs). Gray-Scott steps against blocks of 256 threads
 // with the tile in LDS, two of four wavefronts in the FFT and block barriers
-// between stages: 512^2 155 -> 78 us (FP64 168 -> 97); 1024^2 363 -> 258 (FP64
+// between stages: 512^2 155 -> 78 us (x launches 14.4 -> 6.5, the last axis' 22.4 ->
+// 12.7; FP64 168 -> 97); 1024^2 363 -> 258 (FP64
 // 416 -> 290); FHN 256^3 6.99 -> 4.02 ms (FP64 8.80 -> 4.96). Showing each other
 // the stage values costs two barriers per x launch: with the two species of a
 // row as a pair these steps took 76 (94), 255 (283) us and 4.03 (4.84) ms.

@@ -411,17 +411,18 @@ int wave_class_of(int dtype, int bc, long long n, bool source) {
   if (half <= 32) return c2 + lay;
   if (half <= 64) return c4 + lay;
   if (f32 && half <= 128) return WC_F32_8X + lay;
-  // periodic axes of 256 and 512 points run as FFTs: 256^2 FP64 102 us per step
-  // against 196 (FP32 equal), 512^2 FP32 153 against 152 for the products
-  if (per && (n == 256 || n == 512)) return -1;
+  // periodic axes of 256 points run as FFTs (as those of 512 and 1024, which have no
+  // class): launches of 256^2 FP64, products / FFT: X 26.8 / 8.1, Z 25.2 / 8.5 us
+  if (per && n == 256) return -1;
   if (!f32 && half <= (odd ? 128 : 144)) {  // the class whose blocks the axis fills
     if (odd) return (n - 1) / 2 / 2 + 1 <= 48 ? WC_F64_6O : WC_F64_8O;  // points of segment 0
     return half <= 80 ? WC_F64_5E : half <= 96 ? WC_F64_6E : half <= 112 ? WC_F64_7E
          : half <= 128 ? WC_F64_8E : WC_F64_9E;
   }
-  // to 512 points on the group kernels (the dense kernels / these, per step:
-  // 300 x 333 FP32 6280 / 117 us, 390 x 280 FP64 7257 / 313, 512^2 Dirichlet
-  // FP32 10983 / 152); beyond, the matrix of an axis leaves the caches
+  // to 512 points on the group kernels (launches of the dense kernels / these: 300 x
+  // 333 FP32 X 351 / 14.4, Z 289 / 16.2 us, 390 points FP64 Z 485 / 48, 512^2
+  // Dirichlet FP32 X 630 / 19, Z 611 / 20); beyond, the matrix of an axis leaves the
+  // caches
   if (half > 256) return -1;
   return (f32 ? WC_F32_16E : WC_F64_16E) + (odd ? 1 : 0);
 }

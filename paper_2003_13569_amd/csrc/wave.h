@@ -1447,8 +1447,8 @@ __device__ __forceinline__ void wave_combine_out(const IO& io, const StageArgs<T
 // bound at 256^3 FP32, on 64-byte rows at 256 KB strides: 3.5 TB/s over five
 // fields in stage 0 with every array in the fields' order; with c_tilde and acc
 // in register order and the sweep a step went 1.43 -> 1.34 ms (1.43 in 8-wave
-// blocks on the same GPU; the four stages 168 to 137 us there, 158 to 124 here). 128^3 FP32 32-36 -> 18 us a
-// stage, FP64 76-85 -> 42-55.
+// blocks on the same GPU; the four stages 168 to 137 us there, 156 to 120 here). 128^3
+// FP32 32-36 -> 17-20 us a stage, FP64 76-85 -> 43-54.
 template <typename T, int NB, int LAY, int MODE, int CO>
 __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wz(StageArgs<T> a, WaveAxis ax, WaveTiles tl) {
   to_member(a);
@@ -2057,7 +2057,7 @@ __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wzadj(StageArgs<T> 
 // the wave engine's, in its order: the results are the same bit for bit. The
 // code of a stage appears once, not once per row block, which a kernel of one
 // pass (cold instruction cache) needs most. Bound by that chain: 64^2 FP64 X 16.8
-// (8-wave block) -> 4.6 us, Z 12 -> 6; 256^2 FP32 X 15 -> 8.1, Z 13 -> 7.3.
+// (8-wave block) -> 4.4 us, Z 12 -> 5; 256^2 FP32 X 15 -> 7.8, Z 13 -> 7.4.
 template <typename T, int NB, int LAY>
 struct GroupXf : WaveXf<T, NB, LAY> {
   using W = WaveXf<T, NB, LAY>;
