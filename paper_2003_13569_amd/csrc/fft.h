@@ -27,8 +27,8 @@
 // sums of both, so each carries rounding errors of the size of the larger line
 // (with the two species of a row as a pair, a species 10^-6 of the other came
 // out 2 % off in FP32). On the x axis they are neighbouring rows, and the
-// wavefronts of a row pair's two species sit side by side in one block and show
-// each other their stage values through LDS for the reaction; on strided axes
+// wavefronts of a row pair's two species sit side by side in one block and trade
+// lines through LDS for the reaction; on strided axes
 // they are neighbouring columns of one outer block. Twiddles (cos, sin of
 // 2 pi m / N) come from a table built in FP64 on the host.
 //
@@ -36,10 +36,11 @@
 // (512 wavefronts on 256 CUs). Gray-Scott steps against blocks of 256 threads
 // with the tile in LDS, two of four wavefronts in the FFT and block barriers
 // between stages: 512^2 155 -> 78 us (x launches 14.4 -> 6.5, the last axis' 22.4 ->
-// 12.7; FP64 168 -> 97); 1024^2 363 -> 258 (FP64
-// 416 -> 290); FHN 256^3 6.99 -> 4.02 ms (FP64 8.80 -> 4.96). Showing each other
-// the stage values costs two barriers per x launch: with the two species of a
-// row as a pair these steps took 76 (94), 255 (283) us and 4.03 (4.84) ms.
+// 12.7; FP64 168 -> 96); 1024^2 363 -> 258 (FP64 416 -> 290); FHN 256^3 6.99 ->
+// 4.00 ms (FP64 8.80 -> 4.95). Trading lines costs three barriers per x launch: with
+// the two species of a row as a pair these steps took 76 (93), 255 (282) us and 4.03
+// (4.85) ms. (Showing the other wavefront both lines, two barriers but every
+// reaction twice: FP64 97 us, 512^2; adjoint of 1024^2 FP64 5.01 ms against 4.76.)
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -191,22 +192,17 @@ struct WaveFft {
     }
     sync();
   }
-  // This wavefront's values where the wavefront of the other species (the next
-  // or the one before in the block) finds them, and that one's values of points
-  // lane + 64 e. Between show() and seen(), and from the last seen() to the next
-  // transform: a barrier of the block.
-  __device__ __forceinline__ void show(const Vals& a, const Vals& b) const {
+  // What this wavefront gives for what the wavefront of the other species gives, by
+  // half `part` of the buffers (one barrier; one more before that half is written
+  // again).
+  __device__ __forceinline__ void trade(int part, const Vals& give, Vals& got) const {
+    T* m = part ? xi : xr;
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-      xr[at(lane + 64 * e)] = a[e];
-      xi[at(lane + 64 * e)] = b[e];
-    }
-  }
-  __device__ __forceinline__ void seen(int e, T& a, T& b) const {
-    const bool odd = (threadIdx.x >> 6) & 1;
-    const T* o = odd ? xr - 2 * PART : xr + 2 * PART;
-    a = o[at(lane + 64 * e)];
-    b = o[PART + at(lane + 64 * e)];
+    for (int e = 0; e < E; ++e) m[at(lane + 64 * e)] = give[e];
+    __syncthreads();
+    const T* o = (threadIdx.x >> 6) & 1 ? m - 2 * PART : m + 2 * PART;
+#pragma unroll
+    for (int e = 0; e < E; ++e) got[e] = o[at(lane + 64 * e)];
   }
   // Hartley transforms of the lines in a and b, in place.
   __device__ __forceinline__ void hartley(Vals& a, Vals& b) const {
@@ -276,6 +272,8 @@ struct FftXPair {
   }
 };
 
+// Barriers of a reaction that couples two species (fft_react, fft_adj_react).
+constexpr int FFT_TRADE_BARRIERS = 3;
 // Whether the reaction couples two species (their wavefronts exchange values).
 __device__ __forceinline__ bool fft_coupled(int kind) {
   return kind >= RXN_FHN && kind <= RXN_GM;  // uniform
@@ -419,56 +417,69 @@ __device__ __forceinline__ void fft_store_line(T* p, int lane, const T (&v)[E]) 
   for (int e = 0; e < E; ++e) p[lane + 64 * e] = v[e];
 }
 
-// f of the pair's stage values; true if a value was not finite. Two coupled
-// species: every wavefront of the block comes here (two barriers).
+// f of the pair's stage values; true if a value was not finite. Two coupled species:
+// line a in the wavefront of species 0, line b in that of species 1; the wavefronts
+// trade lines before and after.
 template <int KIND, typename T, class FT>
 __device__ __forceinline__ bool fft_react(const StageArgs<T>& a, const FftXPair& pr, const FT& ft,
                                           T (&va)[FT::E], T (&vb)[FT::E]) {
-  constexpr bool TWO = KIND >= RXN_FHN && KIND <= RXN_GM;
   const RxnT<T> rx(a.rxn);
   const int sp = pr.sp;  // uniform
-  const T lin = sp == 0 ? rx.lin[0] : sp == 1 ? rx.lin[1] : sp == 2 ? rx.lin[2] : rx.lin[3];
   T chk = T(0);
-  MmsLine ml[2] = {};
-  if constexpr (KIND >= RXN_HUXLEY_MMS) {
-    ml[0] = mms_line(a.rxn, a.t, pr.la % a.n1);
-    ml[1] = mms_line(a.rxn, a.t, pr.lb % a.n1);
-  }
-  if constexpr (TWO) {
-    ft.show(va, vb);
-    __syncthreads();
-  }
+  if constexpr (KIND >= RXN_FHN && KIND <= RXN_GM) {
+    T give[FT::E], got[FT::E];
 #pragma unroll
-  for (int e = 0; e < FT::E; ++e) {
-    const T u[2] = {va[e], vb[e]};
-    T f[2];
-    if constexpr (KIND == RXN_LINEAR) {
-      f[0] = lin * u[0];
-      f[1] = lin * u[1];
-    } else if constexpr (KIND >= RXN_HUXLEY_MMS) {
-      rxn_eval_k<T, 1, KIND>(rx, &u[0], &f[0]);
-      rxn_eval_k<T, 1, KIND>(rx, &u[1], &f[1]);
-      f[0] += T(mms_source<KIND>(ml[0], ft.lane + 64 * e));
-      f[1] += T(mms_source<KIND>(ml[1], ft.lane + 64 * e));
-    } else {
-      T w[2];
-      ft.seen(e, w[0], w[1]);
+    for (int e = 0; e < FT::E; ++e) give[e] = sp == 0 ? vb[e] : va[e];
+    ft.trade(0, give, got);
 #pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        const T uv[2] = {sp == 0 ? u[k] : w[k], sp == 0 ? w[k] : u[k]};
-        T o[2];
-        rxn_eval_k<T, 2, KIND>(rx, uv, o);
-        f[k] = sp == 0 ? o[0] : o[1];
-      }
+    for (int e = 0; e < FT::E; ++e) {
+      const T own = sp == 0 ? va[e] : vb[e];
+      const T u[2] = {sp == 0 ? own : got[e], sp == 0 ? got[e] : own};
+      T f[2];
+      rxn_eval_k<T, 2, KIND>(rx, u, f);
+      chk = fma(u[0], T(0), chk);
+      chk = fma(u[1], T(0), chk);
+      chk = fma(f[0], T(0), chk);
+      chk = fma(f[1], T(0), chk);
+      va[e] = sp == 0 ? f[0] : f[1];
+      give[e] = sp == 0 ? f[1] : f[0];
     }
-    chk = fma(u[0], T(0), chk);
-    chk = fma(u[1], T(0), chk);
-    chk = fma(f[0], T(0), chk);
-    chk = fma(f[1], T(0), chk);
-    va[e] = f[0];
-    vb[e] = f[1];
+    ft.trade(1, give, got);
+#pragma unroll
+    for (int e = 0; e < FT::E; ++e) {
+      const T own = va[e];
+      va[e] = sp == 0 ? own : got[e];
+      vb[e] = sp == 0 ? got[e] : own;
+    }
+    __syncthreads();
+  } else {
+    const T lin = sp == 0 ? rx.lin[0] : sp == 1 ? rx.lin[1] : sp == 2 ? rx.lin[2] : rx.lin[3];
+    MmsLine ml[2] = {};
+    if constexpr (KIND >= RXN_HUXLEY_MMS) {
+      ml[0] = mms_line(a.rxn, a.t, pr.la % a.n1);
+      ml[1] = mms_line(a.rxn, a.t, pr.lb % a.n1);
+    }
+#pragma unroll
+    for (int e = 0; e < FT::E; ++e) {
+      const T u[2] = {va[e], vb[e]};
+      T f[2];
+      if constexpr (KIND == RXN_LINEAR) {
+        f[0] = lin * u[0];
+        f[1] = lin * u[1];
+      } else {
+        rxn_eval_k<T, 1, KIND>(rx, &u[0], &f[0]);
+        rxn_eval_k<T, 1, KIND>(rx, &u[1], &f[1]);
+        f[0] += T(mms_source<KIND>(ml[0], ft.lane + 64 * e));
+        f[1] += T(mms_source<KIND>(ml[1], ft.lane + 64 * e));
+      }
+      chk = fma(u[0], T(0), chk);
+      chk = fma(u[1], T(0), chk);
+      chk = fma(f[0], T(0), chk);
+      chk = fma(f[1], T(0), chk);
+      va[e] = f[0];
+      vb[e] = f[1];
+    }
   }
-  if constexpr (TWO) __syncthreads();
   return !(chk == T(0));
 }
 
@@ -481,10 +492,8 @@ __global__ __launch_bounds__(256) void k_fx(StageArgs<T> a, FftPairs fp) {
   const WaveFft<T, N> ft(smem, a.Mt);
   const int q = fft_pair(fp.npairs);
   if (q < 0) {
-    if (!SRC && fft_coupled(a.rxn.kind)) {  // the barriers of fft_react
-      __syncthreads();
-      __syncthreads();
-    }
+    if (!SRC && fft_coupled(a.rxn.kind))
+      for (int k = 0; k < FFT_TRADE_BARRIERS; ++k) __syncthreads();
     return;
   }
   const FftXPair pr(fp, a.S, q);
@@ -617,57 +626,64 @@ __global__ __launch_bounds__(256) void k_fz(StageArgs<T> a, FftPairs fp) {
   io.store_all(a.P, va, vb);
 }
 
-// Adjoint reaction of the pair at its stage values ua, ub; wa, wb: those of the
-// other species of a coupled plan (two barriers, as in fft_react). Parameter
-// partials: a point's are counted once, by the wavefront of species 0 where two
-// are coupled, and a repeated line not again.
+// Adjoint reaction. Uncoupled species: of the pair's lines at their stage values ua,
+// ub. Two coupled species: of line a in the wavefront of species 0 and of line b in
+// that of species 1, ua and ub the two species' stage values of that line; the
+// wavefronts trade lines before and after (three barriers with the one that lets
+// the next transform write). So each point's Jacobian and parameter partials are
+// formed once. Parameter partials: a repeated line does not count again.
 template <int KIND, typename T, class FT>
 __device__ __forceinline__ void fft_adj_react(const StageArgs<T>& a, const FftXPair& pr,
                                               const FT& ft, T (&ga)[FT::E], T (&gb)[FT::E],
                                               const T (&ua)[FT::E], const T (&ub)[FT::E],
-                                              const T (&wa)[FT::E], const T (&wb)[FT::E],
                                               double* pacc) {
-  constexpr bool TWO = KIND >= RXN_FHN && KIND <= RXN_GM;
   const int sp = pr.sp;  // uniform
-  const bool wp = a.rp_acc != nullptr && !(TWO && sp != 0);
-  const double wt[2] = {1.0, pr.lb != pr.la ? 1.0 : 0.0};
-  const T lin = T(sp == 0 ? a.rxn.p[0] : sp == 1 ? a.rxn.p[1] : sp == 2 ? a.rxn.p[2] : a.rxn.p[3]);
-  if constexpr (TWO) {
-    ft.show(ga, gb);
-    __syncthreads();
-  }
+  const bool wp = a.rp_acc != nullptr;
+  const double wb = pr.lb != pr.la ? 1.0 : 0.0;
+  if constexpr (KIND >= RXN_FHN && KIND <= RXN_GM) {
+    T give[FT::E], got[FT::E];
 #pragma unroll
-  for (int e = 0; e < FT::E; ++e) {
-    const T g[2] = {ga[e], gb[e]}, u[2] = {ua[e], ub[e]};
-    T o[2];
-    if constexpr (KIND == RXN_LINEAR) {
-      o[0] = lin * g[0];
-      o[1] = lin * g[1];
-      if (wp) {
-        const double c = wt[0] * double(g[0] * u[0]) + wt[1] * double(g[1] * u[1]);
+    for (int e = 0; e < FT::E; ++e) give[e] = sp == 0 ? gb[e] : ga[e];
+    ft.trade(0, give, got);
 #pragma unroll
-        for (int s = 0; s < MAX_SPECIES; ++s) pacc[s] += sp == s ? c : 0.0;
-      }
-    } else if constexpr (KIND >= RXN_HUXLEY_MMS) {
-      rxn_adjoint_k<T, 1, KIND>(a.rxn, &u[0], &g[0], &o[0], 1.0, pacc, false);
-      rxn_adjoint_k<T, 1, KIND>(a.rxn, &u[1], &g[1], &o[1], 1.0, pacc, false);
-    } else {
-      T h[2];
-      ft.seen(e, h[0], h[1]);
-      const T w[2] = {wa[e], wb[e]};
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        const T uv[2] = {sp == 0 ? u[k] : w[k], sp == 0 ? w[k] : u[k]};
-        const T gv[2] = {sp == 0 ? g[k] : h[k], sp == 0 ? h[k] : g[k]};
-        T r[2];
-        rxn_adjoint_k<T, 2, KIND>(a.rxn, uv, gv, r, wt[k], pacc, wp);
-        o[k] = sp == 0 ? r[0] : r[1];
-      }
+    for (int e = 0; e < FT::E; ++e) {
+      const T own = sp == 0 ? ga[e] : gb[e], u[2] = {ua[e], ub[e]};
+      const T g[2] = {sp == 0 ? own : got[e], sp == 0 ? got[e] : own};
+      T o[2];
+      rxn_adjoint_k<T, 2, KIND>(a.rxn, u, g, o, sp == 0 ? 1.0 : wb, pacc, wp);
+      ga[e] = sp == 0 ? o[0] : o[1];
+      give[e] = sp == 0 ? o[1] : o[0];
     }
-    ga[e] = o[0];
-    gb[e] = o[1];
+    ft.trade(1, give, got);
+#pragma unroll
+    for (int e = 0; e < FT::E; ++e) {
+      const T own = ga[e];
+      ga[e] = sp == 0 ? own : got[e];
+      gb[e] = sp == 0 ? got[e] : own;
+    }
+    __syncthreads();
+  } else {
+    const T lin = T(sp == 0 ? a.rxn.p[0] : sp == 1 ? a.rxn.p[1] : sp == 2 ? a.rxn.p[2] : a.rxn.p[3]);
+#pragma unroll
+    for (int e = 0; e < FT::E; ++e) {
+      const T g[2] = {ga[e], gb[e]}, u[2] = {ua[e], ub[e]};
+      T o[2];
+      if constexpr (KIND == RXN_LINEAR) {
+        o[0] = lin * g[0];
+        o[1] = lin * g[1];
+        if (wp) {
+          const double c = double(g[0] * u[0]) + wb * double(g[1] * u[1]);
+#pragma unroll
+          for (int s = 0; s < MAX_SPECIES; ++s) pacc[s] += sp == s ? c : 0.0;
+        }
+      } else {
+        rxn_adjoint_k<T, 1, KIND>(a.rxn, &u[0], &g[0], &o[0], 1.0, pacc, false);
+        rxn_adjoint_k<T, 1, KIND>(a.rxn, &u[1], &g[1], &o[1], 1.0, pacc, false);
+      }
+      ga[e] = o[0];
+      gb[e] = o[1];
+    }
   }
-  if constexpr (TWO) __syncthreads();
 }
 
 // X, adjoint. (Every wavefront of a block reaches the block sums.)
@@ -685,33 +701,28 @@ __global__ __launch_bounds__(256) void k_fxadj(StageArgs<T> a, FftPairs fp) {
     const FftXPair pr(fp, a.S, q);
     const bool two = fft_coupled(a.rxn.kind);
     const long long oa = pr.sp * a.g.total + pr.la * N, ob = pr.sp * a.g.total + pr.lb * N;
-    typename FT::Vals va, vb, ua, ub, wa = {}, wb = {};
+    typename FT::Vals va, vb, ua, ub;
     fft_load_line(a.P + oa, ft.lane, va);
     fft_load_line(a.P + ob, ft.lane, vb);
     const T* st = a.st_phys + (long long)a.mode * a.S * a.g.total;
-    fft_load_line(st + oa, ft.lane, ua);
-    fft_load_line(st + ob, ft.lane, ub);
-    if (two) {
-      const long long other = pr.sp == 0 ? a.g.total : -a.g.total;
-      fft_load_line(st + oa + other, ft.lane, wa);
-      fft_load_line(st + ob + other, ft.lane, wb);
-    }
+    const long long own = pr.sp == 0 ? pr.la * N : pr.lb * N;
+    fft_load_line(st + (two ? own : oa), ft.lane, ua);
+    fft_load_line(st + (two ? a.g.total + own : ob), ft.lane, ub);
     ft.hartley(va, vb);
     switch (a.rxn.kind) {  // uniform
-      case RXN_LINEAR: fft_adj_react<RXN_LINEAR>(a, pr, ft, va, vb, ua, ub, wa, wb, pacc); break;
-      case RXN_FHN: fft_adj_react<RXN_FHN>(a, pr, ft, va, vb, ua, ub, wa, wb, pacc); break;
-      case RXN_GRAY_SCOTT: fft_adj_react<RXN_GRAY_SCOTT>(a, pr, ft, va, vb, ua, ub, wa, wb, pacc); break;
-      case RXN_SCHNAKENBERG: fft_adj_react<RXN_SCHNAKENBERG>(a, pr, ft, va, vb, ua, ub, wa, wb, pacc); break;
-      case RXN_GM: fft_adj_react<RXN_GM>(a, pr, ft, va, vb, ua, ub, wa, wb, pacc); break;
-      case RXN_HUXLEY_MMS: fft_adj_react<RXN_HUXLEY_MMS>(a, pr, ft, va, vb, ua, ub, wa, wb, pacc); break;
-      default: fft_adj_react<RXN_FISHER_MMS>(a, pr, ft, va, vb, ua, ub, wa, wb, pacc); break;
+      case RXN_LINEAR: fft_adj_react<RXN_LINEAR>(a, pr, ft, va, vb, ua, ub, pacc); break;
+      case RXN_FHN: fft_adj_react<RXN_FHN>(a, pr, ft, va, vb, ua, ub, pacc); break;
+      case RXN_GRAY_SCOTT: fft_adj_react<RXN_GRAY_SCOTT>(a, pr, ft, va, vb, ua, ub, pacc); break;
+      case RXN_SCHNAKENBERG: fft_adj_react<RXN_SCHNAKENBERG>(a, pr, ft, va, vb, ua, ub, pacc); break;
+      case RXN_GM: fft_adj_react<RXN_GM>(a, pr, ft, va, vb, ua, ub, pacc); break;
+      case RXN_HUXLEY_MMS: fft_adj_react<RXN_HUXLEY_MMS>(a, pr, ft, va, vb, ua, ub, pacc); break;
+      default: fft_adj_react<RXN_FISHER_MMS>(a, pr, ft, va, vb, ua, ub, pacc); break;
     }
     ft.hartley(va, vb);
     fft_store_line(a.P + oa, ft.lane, va);
     fft_store_line(a.P + ob, ft.lane, vb);
-  } else if (fft_coupled(a.rxn.kind)) {  // the barriers of fft_adj_react
-    __syncthreads();
-    __syncthreads();
+  } else if (fft_coupled(a.rxn.kind)) {
+    for (int k = 0; k < FFT_TRADE_BARRIERS; ++k) __syncthreads();
   }
   if (a.rp_acc) block_add_partials(reinterpret_cast<double*>(smem), pacc, a.rxn.np, a.rp_acc);
 }

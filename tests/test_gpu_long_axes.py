@@ -1,5 +1,5 @@
-"""Axes past 128 points: FP64 classes of 5 to 9 row blocks and the 16-block classes
-at their edges, forward and adjoint with every gradient, as groups (few tiles)
+"""Axes past 128 points: FP64 classes of 5 to 9 row blocks, the 16-block classes and
+the FFT axes at their edges, forward and adjoint with every gradient, as groups (few tiles)
 and as wave kernels (many), on x and on the last axis. Bounds of the repository:
 FP64 1e-10; FP32 2e-5 of the fields, 1e-4 of the state gradient, 1e-3 of the
 parameter gradients.
@@ -82,6 +82,8 @@ def test_long_axes_match_oracle(wl, dtype, exact_basis):
 
 ADJOINT = [
     *[_sch("periodic", s) for s in ((300, 10), (10, 300), (301, 9), (511, 6))],
+    # FFT axes with a row or column without a partner (it counts once)
+    *[_sch("periodic", s) for s in ((7, 256), (256, 7), (3, 5, 512), (1024, 3), (3, 1024))],
     *[_sch(bc, s) for bc in ("neumann", "dirichlet")
       for s in ((300, 7), (9, 301), (302, 14), (511, 6), (6, 512), (150, 161), (240, 201))],
     # wave kernels: the last axis (many columns), the x axis (many lines)
