@@ -280,8 +280,21 @@ struct WaveXf {
   // segment of row block rb, the block within it, and whether it is in use
   __device__ __forceinline__ static constexpr int seg(int rb) { return ODD && 2 * rb >= NB ? 1 : 0; }
   __device__ __forceinline__ static constexpr int sb(int rb) { return seg(rb) ? rb - NB / 2 : rb; }
-  __device__ __forceinline__ bool used(int rb) const {
-    return EX || FULL || sb(rb) < (seg(rb) ? ax.nb1 : ax.nb);
+  // Blocks that hold positions of their own. A block of padding alone (in full
+  // classes the last of segment 1 may be one: 129 and 193 points) repeats the last
+  // position of the block before, which is harmless where values are stored, but
+  // arrays that are read and written would get it twice: the stage combines take
+  // own() blocks only.
+  __device__ __forceinline__ static constexpr bool block_own(int rb, int nb, int nb1) {
+    return EX || (FULL && !(ODD && rb + 1 == NB)) || sb(rb) < (seg(rb) ? nb1 : nb);
+  }
+  __device__ __forceinline__ bool own(int rb) const { return block_own(rb, ax.nb, ax.nb1); }
+  __device__ __forceinline__ bool used(int rb) const { return FULL || own(rb); }
+  // A block that a stage combine leaves out, for the next product (its columns are
+  // zero; blocks not in use hold zeros already).
+  __device__ __forceinline__ static void clear(T (&va)[4], T (&vb)[4]) {
+    if constexpr (FULL)
+      for (int r = 0; r < 4; ++r) va[r] = vb[r] = T(0);
   }
   // position in the segment of register r of row block rb
   __device__ __forceinline__ int q(int rb, int r) const { return 16 * sb(rb) + PR * r + PG * g; }
@@ -1494,7 +1507,7 @@ __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wz(StageArgs<T> a, 
       }
       static_for<NB>([&](auto rbc) {
         constexpr int rb = decltype(rbc)::value;
-        if (!xf.used(rb)) return;
+        if (!xf.own(rb)) return xf.clear(ya[rb], yb[rb]);
         if constexpr (!XF::F32) load_x1(rbc);
         float lz[2][4] = {};
         if constexpr (CO == CO_FLY) {
@@ -2028,7 +2041,7 @@ __global__ __launch_bounds__((wave_threads<T, NB>())) void k_wzadj(StageArgs<T> 
     } else {
       static_for<NB>([&](auto rbc) {
         constexpr int rb = decltype(rbc)::value;
-        if (!xf.used(rb)) return;
+        if (!xf.own(rb)) return xf.clear(ya[rb], yb[rb]);
         wave_adj_tab<0>(io, a, rb, ya[rb]);
         __builtin_amdgcn_sched_barrier(0);
         wave_adj_tab<1>(io, a, rb, yb[rb]);
@@ -2093,7 +2106,7 @@ struct GroupXf : WaveXf<T, NB, LAY> {
       : W(ax_, reinterpret_cast<const char*>(ax_.A)) {
     this->tab = reinterpret_cast<const char*>(ax_.A);  // read once, from global memory
     rb = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    on = W::used(rb);
+    on = W::own(rb);
     lane = threadIdx.x & 63;
   }
   __device__ __forceinline__ void rows_of(int half, unsigned lo, Rows& m) const {

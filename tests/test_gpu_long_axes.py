@@ -64,7 +64,9 @@ FORWARD = [
     *[_sch(bc, s) for bc in ("neumann", "dirichlet")
       for s in ((160, 130), (162, 192), (224, 194), (226, 254), (258, 288), (129, 131), (191, 193),
                 (255, 133), (48, 51, 160), (49, 50, 162), (37, 49, 224), (41, 37, 246), (33, 40, 270),
-                (49, 50, 131), (37, 40, 193), (192, 30, 62))],
+                (49, 50, 131), (37, 40, 193), (192, 30, 62),
+                # a segment that ends with its row block, the other one block longer
+                (129, 20), (193, 21), (129, 54, 52), (193, 47, 46), (47, 48, 193))],
     *[_sch("periodic", s) for s in ((158, 159), (160, 190), (191, 222), (223, 254), (48, 51, 158),
                                     (49, 50, 191), (41, 37, 222))],
 ]
@@ -82,6 +84,8 @@ def test_long_axes_match_oracle(wl, dtype, exact_basis):
 
 ADJOINT = [
     *[_sch("periodic", s) for s in ((300, 10), (10, 300), (301, 9), (511, 6))],
+    *[_sch("dirichlet", s) for s in ((129, 20), (193, 21), (22, 193), (129, 54, 52), (193, 47, 46),
+                                     (47, 48, 193))],
     # FFT axes with a row or column without a partner (it counts once)
     *[_sch("periodic", s) for s in ((7, 256), (256, 7), (3, 5, 512), (1024, 3), (3, 1024))],
     *[_sch(bc, s) for bc in ("neumann", "dirichlet")

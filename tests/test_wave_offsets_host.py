@@ -1,6 +1,7 @@
 """Index arithmetic of the matrix-core engine compiled for the host (tests/host):
-its row accesses on grids near the 32-bit limits (row_io.hip), and the tiles and
-barriers of its waves (wave_run.hip)."""
+its row accesses on grids near the 32-bit limits (row_io.hip), the tiles and
+barriers of its waves (wave_run.hip), and the row blocks of every axis in its size
+class (axis_classes.hip)."""
 import os
 import shutil
 import subprocess
@@ -29,8 +30,11 @@ def row_io(tmp_path_factory):
     return _build("row_io", tmp_path_factory)
 
 
-def test_every_tile_once_and_barriers_of_a_block_match(tmp_path_factory):
-    res = subprocess.run([_build("wave_run", tmp_path_factory)], capture_output=True, text=True,
+# wave_run: every tile once, as many barriers from every wave of a block;
+# axis_classes: every position once, no row block of padding alone
+@pytest.mark.parametrize("name", ["wave_run", "axis_classes"])
+def test_index_arithmetic_of_the_engine(name, tmp_path_factory):
+    res = subprocess.run([_build(name, tmp_path_factory)], capture_output=True, text=True,
                          timeout=120)
     assert res.returncode == 0, res.stdout + res.stderr
 
